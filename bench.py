@@ -300,10 +300,11 @@ def main() -> int:
         bytes_round = np.mean([W.algorithmic_bytes_per_param(
             K, w.mode, averaging=bool(w.period and (t + 1) % w.period == 0),
             momentum=mu is not None, step_ahead=variant == saef.VARIANT_SAEF,
-            mismatch=args.mismatch) for t in timed_ts]) * d
+            mismatch=args.mismatch, one_pass=not split) for t in timed_ts]) * d
 
-    # dominant kernel: worker compression (12 K + K/8 bytes per parameter,
-    # 20 K + K/8 with momentum)
+    # dominant kernel: worker compression (12 K + K/8 bytes per parameter, 20 K
+    # + K/8 with momentum); with the gradient in place (saef_round) and no
+    # averaging due it takes the step ahead along (4 + 4 K more: x in, xh out)
     c_count, c_ms = prof["compress"]
     # Top-K: the iteration end (compression and server step) runs pipelined
     # over tensor groups as one timed span when the plan pipelines it
@@ -313,7 +314,10 @@ def main() -> int:
         c_bytes = (tb["worker"] + (8 * K if mu is not None else 0)
                    + (tb["server"] if tk_pipelined else 0)) * d
     else:
-        c_bytes = ((20 if mu is not None else 12) * K + K / 8) * d
+        stamped = [t for t in timed_ts][::EVENT_EVERY]
+        c_bytes = ((20 if mu is not None else 12) * K + K / 8) * d + np.mean(
+            [0 if split or (w.period and (t + 1) % w.period == 0) else 4 + 4 * K
+             for t in stamped]) * d
     c_gbps = c_bytes / (c_ms / c_count * 1e-3) / 1e9 if c_count else None
     traffic = (traffic_from_profile(args.workload)
                if (mu is None and not split and topk is None) else None)
@@ -373,7 +377,8 @@ def main() -> int:
         "stream_probe_gbps": probe,
         "stream_probe_1r1w_gbps": probe_1r1w,
         "roofline": {"bound": "hbm",
-                     "kernel": ("compress" if topk is None else
+                     "kernel": (("compress" if split else "worker (step ahead and compression)")
+                                if topk is None else
                                 "topk_round_end (worker compression and server step, pipelined "
                                 "over two tensor groups)" if tk_pipelined else
                                 "topk_compress (all passes)"),

@@ -323,7 +323,9 @@ int saef_status(const saef_layout* layout, hipStream_t stream);
  * copy of x_t for local error feedback, 1 = worker compression, 2 = worker
  * scales from the tile sums, 3 = server aggregation, 4 = server scales, 5 =
  * error averaging (with step ahead in the SAEF variant), 6 = mismatch
- * bounds), until the pairs run out; with every > 1 only the 1st, (every+1)-th,
+ * bounds), until the pairs run out (saef_round, saef_round_noalloc and
+ * saef_round_momentum take the step ahead and the worker compression of an
+ * iteration without averaging as one kernel, timed as kind 1); with every > 1 only the 1st, (every+1)-th,
  * ... dispatch of each timed kind since the call is stamped (a sample spread
  * over the run; every < 1 is SAEF_EINVAL).  saef_profile_read waits for the
  * recorded events and returns, per kind, the number of launches timed

@@ -61,6 +61,14 @@ __device__ __forceinline__ void buf_st_word(Buf r, uint32_t off, u64 w) {
   __builtin_amdgcn_raw_buffer_store_b64(v, r, 0, off, 0);
 }
 
+// The same with a byte offset of each lane's own.
+__device__ __forceinline__ void buf_st_lane_word(Buf r, uint32_t off, uint32_t lo, uint32_t hi) {
+  u32x2 v;
+  v.x = lo;
+  v.y = hi;
+  __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 0);
+}
+
 // Sign words of a buffer that no wave writes during the kernel, at a
 // wave-uniform address: read through the scalar cache (s_load), straight
 // into the scalar registers the inline v_cndmask takes as its mask.
@@ -108,11 +116,17 @@ __device__ __forceinline__ float in_vgpr(float v) {
 //   definition says (H = 0 there, a - H = a >= 0).
 // With at most 16 values per lane between flushes, -sum H 2^30 <= 2^53 and
 // |sum trunc((a - H) 2^80)| <= 16 2^49 = 2^53: both fp64 sums are exact.
+// They are then 64-bit integers h and q, S = h 2^50 + q, and a tile of at
+// most 2^13 elements keeps |h|, |q| <= 2^62, so lanes and waves are added as
+// two plain 64-bit sums; one thread per tile forms the 128-bit integer.
+static_assert(kTileElems <= 8192, "a tile's sums h and q fit 64-bit integers");
 struct ExactSum {
   double nh = 0.0;   // -sum of H
   double lq = 0.0;   // sum of trunc((a - H) 2^80)
   float mx = 0.0f;   // largest |v| seen (range check; NaN shows in nh)
   int terms = 0;     // values since the last flush (wave-uniform)
+  int64_t h = 0, q = 0;  // flushed sums
+  bool bad = false;
 
   __device__ __forceinline__ void add(float v) {
     const double a = (double)fabsf(v);
@@ -123,25 +137,11 @@ struct ExactSum {
     mx = fmaxf(mx, fabsf(v));
   }
 
-  // Moves the two fp64 sums into the 128-bit integer (hi, lo) and clears
-  // them: S += (-nh) 2^80 + lq = h 2^50 + lq with h = -nh 2^30.
-  __device__ __forceinline__ void flush(u64& lo, u64& hi, bool& bad) {
+  // Moves the two fp64 sums into the integers and clears them.
+  __device__ __forceinline__ void flush() {
     bad = bad || !(nh == nh) || !(lq == lq);
-    const double h = -nh * 0x1p30;  // integer in [0, 2^53]
-    const uint32_t h_hi = (uint32_t)(h * 0x1p-32);
-    const uint32_t h_lo = (uint32_t)(h - (double)h_hi * 0x1p32);
-    const double q_hd = floor(lq * 0x1p-32);  // lq integer in [-2^53, 2^53]
-    const int32_t q_hi = (int32_t)q_hd;
-    const uint32_t q_lo = (uint32_t)(lq - q_hd * 0x1p32);
-    const u64 hv = ((u64)h_hi << 32) | h_lo;
-    const u64 qv = (u64)(((int64_t)q_hi << 32) | q_lo);  // two's complement
-    // (hi, lo) += hv 2^50 + qv, modulo 2^128 (the lane's total is >= 0)
-    const u64 a_lo = hv << 50;
-    u64 n_lo = lo + a_lo;
-    hi += (hv >> 14) + (n_lo < lo ? 1ull : 0ull);
-    const u64 m_lo = n_lo + qv;
-    hi += (m_lo < n_lo ? 1ull : 0ull) + (q_hi < 0 ? ~0ull : 0ull);
-    lo = m_lo;
+    h += to_i64(-nh * 0x1p30);
+    q += to_i64(lq);
     nh = 0.0;
     lq = 0.0;
     terms = 0;
@@ -149,16 +149,53 @@ struct ExactSum {
 
   // After `count` more values: flush when another pass could break the
   // 16-values-per-lane bound.
-  __device__ __forceinline__ void added(int count, u64& lo, u64& hi, bool& bad) {
+  __device__ __forceinline__ void added(int count) {
     terms += count;
-    if (terms > 8) flush(lo, hi, bad);
+    if (terms > 8) flush();
   }
 
-  __device__ __forceinline__ void finish(u64& lo, u64& hi, bool& bad) {
-    flush(lo, hi, bad);
+  __device__ __forceinline__ void finish() {
+    flush();
     bad = bad || !(mx < 0x1p19f);
   }
+
+  // An integer of magnitude at most 2^53 held in binary64.
+  static __device__ __forceinline__ int64_t to_i64(double v) {
+    const double hd = floor(v * 0x1p-32);
+    const int32_t hi = (int32_t)hd;
+    const uint32_t lo = (uint32_t)(v - hd * 0x1p32);
+    return (int64_t)(((u64)(uint32_t)hi << 32) | lo);
+  }
 };
+
+// Sum of v over the wave, in lane 63: each step adds the lane `ctrl` names
+// with a DPP operand (no LDS round trip: the __shfl_xor form cost six).
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int64_t dpp_add(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, kCtrl, kRows,
+                                                            0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)((u64)v >> 32),
+                                                            kCtrl, kRows, 0xf, false);
+  return v + (int64_t)(((u64)hi << 32) | lo);
+}
+__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
+  v = dpp_add<0x111, 0xf>(v);  // row_shr:1
+  v = dpp_add<0x112, 0xf>(v);  // row_shr:2
+  v = dpp_add<0x114, 0xf>(v);  // row_shr:4
+  v = dpp_add<0x118, 0xf>(v);  // row_shr:8: lane 15 of each row holds its sum
+  v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v = dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// A workgroup barrier that orders LDS accesses only: __syncthreads() also
+// waits for every global store in flight, which keeps a streaming workgroup
+// on its CU until its last store is acknowledged.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
 // Per lane: bit `lane` of the 64-bit mask ? if1 : if0, in one VALU op
 // (v_cndmask with the mask as its lane condition).  The mask must be the

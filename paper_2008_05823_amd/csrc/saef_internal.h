@@ -95,6 +95,16 @@ hipError_t launch_compress(const DevLayout& lay, int K, float lr, float mu, cons
                            float* m, float* e, uint64_t* signs, const float* scales, bool decode,
                            hipStream_t s, const LaunchEvents& ev = LaunchEvents());
 
+// Step ahead and worker compression in one pass (the gradient is in place
+// before the step ahead): launch_step_ahead's xh without averaging, then
+// launch_compress.  decode: as in launch_compress; decode_x: the pending
+// server correction is applied to x on read (requires decode).
+hipError_t launch_worker(const DevLayout& lay, int K, float lr, float mu, const float* g,
+                         float* m, float* e, uint64_t* signs, const float* scales, bool decode,
+                         const float* x, const uint64_t* srv_signs, const float* srv_scales,
+                         bool decode_x, float* xh, hipStream_t s,
+                         const LaunchEvents& ev = LaunchEvents());
+
 // Scales from the tile partial sums: worker rows 0..K-1 into scales[k][l]
 // (server == false) or the server row into scales[l] (server == true).  One
 // kernel, or two when a tensor has more than kFinChunk tiles (fin_split > 1).

@@ -52,6 +52,15 @@ namespace {
 constexpr int kSWaves = SAEF_STREAM_WAVES;
 constexpr int kSBlock = kSWaves * kWave;
 constexpr int kU = SAEF_STREAM_WORDS;
+#ifndef SAEF_WORKER_WAVES
+#define SAEF_WORKER_WAVES 4
+#endif
+#ifndef SAEF_WORKER_WORDS
+#define SAEF_WORKER_WORDS 8
+#endif
+constexpr int kWWaves = SAEF_WORKER_WAVES;  // the pass of step ahead and compression
+constexpr int kWBlock = kWWaves * kWave;
+constexpr int kWU = SAEF_WORKER_WORDS;
 constexpr int kTWaves = SAEF_STEP_WAVES;
 constexpr int kTBlock = kTWaves * kWave;
 constexpr int kTU = SAEF_STEP_WORDS;
@@ -142,57 +151,83 @@ __device__ float scale_from_sum(u64 hi, u64 lo, int64_t n) {
 
 // Stores the exact partial of (row, tile) summed over the workgroup.
 template <int kNW>
-__device__ void block_partial(const DevLayout& lay, int row, int64_t tile, u64 lo, u64 hi,
-                              bool bad) {
-  __shared__ u64 s_lo[kNW];
-  __shared__ u64 s_hi[kNW];
-  wave_sum128(lo, hi);
+__device__ __forceinline__ void block_partial(const DevLayout& lay, int row, int64_t tile,
+                                              ExactSum& acc) {
+  __shared__ int64_t s_h[kNW];
+  __shared__ int64_t s_q[kNW];
+  acc.finish();
+  const int64_t h = wave_sum_i64(acc.h), q = wave_sum_i64(acc.q);
   const int w = threadIdx.x / kWave;
-  if (lane_id() == 0) {
-    s_lo[w] = lo;
-    s_hi[w] = hi;
+  if (lane_id() == kWave - 1) {
+    s_h[w] = h;
+    s_q[w] = q;
   }
-  const int any_bad = __syncthreads_or(bad ? 1 : 0);
+  if (__ballot(acc.bad) != 0ull && lane_id() == 0) atomicOr(lay.status, kStatusRange);
+  lds_barrier();
   if (threadIdx.x != 0) return;
-  u64 tlo = 0, thi = 0;
-  for (int i = 0; i < kNW; ++i) add128(tlo, thi, s_lo[i], s_hi[i]);
+  int64_t th = 0, tq = 0;
+#pragma unroll
+  for (int i = 0; i < kNW; ++i) {
+    th += s_h[i];
+    tq += s_q[i];
+  }
+  // S = th 2^50 + tq (0 <= S < 2^127)
+  u64 lo = (u64)th << 50, hi = (u64)th >> 14;
+  add128(lo, hi, (u64)tq, tq < 0 ? ~0ull : 0ull);
   u64* p = lay.part + ((int64_t)row * lay.n_tiles + tile) * 2;
-  p[0] = tlo;
-  p[1] = thi;
-  if (any_bad) atomicOr(lay.status, kStatusRange);
+  p[0] = lo;
+  p[1] = hi;
 }
 
 // ------------------------------------------------------------------ compress
-// kU words of one worker's tile starting at word w0 (element offsets
+// How a compression pass treats the step ahead of the same iteration: left
+// to its own kernel; xh = x_t - e^(k) written as well, with x plain or (the
+// double-way state) with its pending re-update applied on read.
+constexpr int kXhNone = 0;
+constexpr int kXhPlain = 1;
+constexpr int kXhDec = 2;
+
+// kN words of one worker's tile starting at word w0 (element offsets
 // relative to the tile; the buffer resources cover the tile's elements and
 // sign words, so out-of-range loads read 0 and stores are dropped): with
 // kMom, the momentum buffer m <- fma(mu, m, g) first (one rounding); Delta =
 // fma(lr, m or g, e) (e decoded when kDecode), sign words by ballot,
-// exact-sum terms, Delta stored.  kFull: all kU words are whole words of the
-// tile (no lane masks).
-template <bool kDecode, bool kMom, bool kFull>
-__device__ __forceinline__ void compress_words(int w0, int count, float lr, float mu, Buf rg,
-                                               Buf rm, Buf re, Buf rs, const Corr& c_old,
-                                               ExactSum& acc) {
+// exact-sum terms, Delta stored.  kXh: the step ahead xh = x - e from the
+// same read of e (sx: the server's sign words of the tile).  kFull: all kN
+// words are whole words of the tile (no lane masks).
+template <bool kDecode, bool kMom, int kXh, bool kFull, int kN>
+__device__ __forceinline__ void compress_words(int w0, int nw, int count, float lr, float mu,
+                                               Buf rg, Buf rm, Buf re, Buf rs, Buf rx, Buf rh,
+                                               const uint64_t* __restrict__ sx, const Corr& c_old,
+                                               const Corr& c_x, ExactSum& acc) {
   const int lane = lane_id();
   const uint32_t off0 = (uint32_t)(w0 * 64 + lane) * 4u;
-  float gv[kU], ev[kU], mv[kU];
+  float gv[kN], ev[kN], mv[kN], xv[kN];
+  u64 mx[kN];
+  uint32_t nw_lo = 0, nw_hi = 0;  // lane u: new word u
   // the old words first (every element waits for them; the scheduling
   // barrier keeps the compiler from moving the load behind the others)
-  const u64 ow = kDecode ? buf_ld_words(rs, w0, kU) : 0ull;
+  const u64 ow = kDecode ? buf_ld_words(rs, w0, kN) : 0ull;
   if (kDecode) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int u = 0; u < kU; ++u) {
+  for (int u = 0; u < kN; ++u) {
     mv[u] = kMom ? buf_ld(rm, off0 + 256u * u) : 0.0f;
     gv[u] = buf_ld(rg, off0 + 256u * u);
     ev[u] = buf_ld(re, off0 + 256u * u);
+    xv[u] = kXh != kXhNone ? buf_ld_cached(rx, off0 + 256u * u) : 0.0f;
+    mx[u] = (kXh == kXhDec && (kFull || w0 + u < nw)) ? ld_word_ro(sx + w0 + u) : 0ull;
   }
 #pragma unroll
-  for (int u = 0; u < kU; ++u) {
+  for (int u = 0; u < kN; ++u) {
     const uint32_t off = off0 + 256u * u;
     const bool ok = kFull || (w0 + u) * 64 + lane < count;
     float ev2 = ev[u];
     if (kDecode) ev2 = ev2 - c_old(word_of(ow, u));
+    if (kXh != kXhNone) {
+      float xc = xv[u];
+      if (kXh == kXhDec) xc = xc - c_x(mx[u]);  // x_t = x_{t-1} - C(Delta_t)
+      buf_st(rh, off, xc - ev2);                // x^(k)_{t+1/2} = x_t - e^(k)_t
+    }
     float step = gv[u];
     if (kMom) {
       step = __builtin_fmaf(mu, mv[u], gv[u]);  // m^(k)_{t+1} = mu m^(k)_t + grad
@@ -202,51 +237,59 @@ __device__ __forceinline__ void compress_words(int w0, int count, float lr, floa
     float p = __builtin_fmaf(lr, step, ev2);
     if (!kFull) p = ok ? p : 0.0f;
     const u64 word = __ballot(ok && p >= 0.0f);
-    if (lane == 0) buf_st_word(rs, (uint32_t)(w0 + u) * 8u, word);
+    nw_lo = lane == u ? (uint32_t)word : nw_lo;
+    nw_hi = lane == u ? (uint32_t)(word >> 32) : nw_hi;
     acc.add(p);
     buf_st(re, off, p);
   }
+  // the pass's words in one store (lane u: word u; past the tile: dropped)
+  if (lane < kN) buf_st_lane_word(rs, (uint32_t)(w0 + lane) * 8u, nw_lo, nw_hi);
 }
 
-// Grid: n_tiles * K workgroups; workgroup b handles worker b % K of tile
-// b / K.  Wave w takes words w*kU .. w*kU+kU-1 of the tile, then strides by
-// 4*kU words.
-template <bool kDecode, bool kMom>
-__device__ __forceinline__ void compress_tile(const DevLayout& lay, int K, float lr, float mu,
-                                              const float* __restrict__ g,
+// Worker k's tile ti by a workgroup of kNW waves of kN words per pass: wave
+// w takes words w*kN .. w*kN+kN-1, then strides by kNW*kN words.
+template <bool kDecode, bool kMom, int kXh, int kNW, int kN>
+__device__ __forceinline__ void compress_tile(const DevLayout& lay, int k, int64_t ti, float lr,
+                                              float mu, const float* __restrict__ g,
                                               float* __restrict__ m, float* __restrict__ e,
                                               uint64_t* __restrict__ signs,
-                                              const float* __restrict__ scales) {
-  const unsigned b = blockIdx.x;
-  const int k = (int)(b % (unsigned)K);
-  const int64_t ti = b / (unsigned)K;
+                                              const float* __restrict__ scales,
+                                              const float* __restrict__ x,
+                                              const uint64_t* __restrict__ ss,
+                                              const float* __restrict__ sscales,
+                                              float* __restrict__ xh) {
   const Tile tile = lay.tiles[ti];
   const int wave = wave_id();
   const int64_t row = (int64_t)k * lay.d_pad + tile.start;
+  const int64_t gw0 = tile.start >> 6;
   const uint32_t nbytes = (uint32_t)tile.count * 4u;
   const int nw = (tile.count + 63) >> 6;
   const Buf rg = buf_of(g + row, nbytes);
   const Buf rm = buf_of(kMom ? m + row : g + row, nbytes);
   const Buf re = buf_of(e + row, nbytes);
-  const Buf rs = buf_of(signs + (int64_t)k * (lay.d_pad >> 6) + (tile.start >> 6),
-                        (uint32_t)nw * 8u);
+  const Buf rs = buf_of(signs + (int64_t)k * (lay.d_pad >> 6) + gw0, (uint32_t)nw * 8u);
+  const Buf rx = buf_of(kXh != kXhNone ? x + tile.start : g + row, nbytes);
+  const Buf rh = buf_of(kXh != kXhNone ? xh + row : e + row, nbytes);
+  const uint64_t* sx = kXh == kXhDec ? ss + gw0 : nullptr;
   const Corr c_old(kDecode ? scales[(int64_t)k * lay.L + tile.l] : 0.0f);
+  const Corr c_x(kXh == kXhDec ? sscales[tile.l] : 0.0f);
 
   ExactSum acc;
-  u64 lo = 0, hi = 0;
-  bool bad = false;
-  for (int w0 = wave * kU; w0 < nw; w0 += kSWaves * kU) {
-    if ((w0 + kU) * 64 <= tile.count) {
-      compress_words<kDecode, kMom, true>(w0, tile.count, lr, mu, rg, rm, re, rs, c_old, acc);
+  for (int w0 = wave * kN; w0 < nw; w0 += kNW * kN) {
+    if ((w0 + kN) * 64 <= tile.count) {
+      compress_words<kDecode, kMom, kXh, true, kN>(w0, nw, tile.count, lr, mu, rg, rm, re, rs, rx,
+                                                   rh, sx, c_old, c_x, acc);
     } else {
-      compress_words<kDecode, kMom, false>(w0, tile.count, lr, mu, rg, rm, re, rs, c_old, acc);
+      compress_words<kDecode, kMom, kXh, false, kN>(w0, nw, tile.count, lr, mu, rg, rm, re, rs,
+                                                    rx, rh, sx, c_old, c_x, acc);
     }
-    acc.added(kU, lo, hi, bad);
+    acc.added(kN);
   }
-  acc.finish(lo, hi, bad);
-  block_partial<kSWaves>(lay, k, ti, lo, hi, bad);
+  block_partial<kNW>(lay, k, ti, acc);
 }
 
+// Grid: n_tiles * K workgroups; workgroup b handles worker b % K of tile
+// b / K.
 template <bool kDecode>
 __global__ __launch_bounds__(kSBlock) void k_compress(DevLayout lay, int K, float lr, float mu,
                                                      const float* __restrict__ g,
@@ -254,18 +297,53 @@ __global__ __launch_bounds__(kSBlock) void k_compress(DevLayout lay, int K, floa
                                                      float* __restrict__ e,
                                                      uint64_t* __restrict__ signs,
                                                      const float* __restrict__ scales) {
-  compress_tile<kDecode, false>(lay, K, lr, mu, g, m, e, signs, scales);
+  const unsigned b = blockIdx.x;
+  compress_tile<kDecode, false, kXhNone, kSWaves, kU>(lay, (int)(b % (unsigned)K),
+                                                      b / (unsigned)K, lr, mu, g, m, e, signs,
+                                                      scales, nullptr, nullptr, nullptr, nullptr);
 }
 
-// With momentum (three streams in, two out) at most 5 waves per SIMD: 672
-// against 696 us at 8 waves (resnet50, K = 8); the sign kernel prefers 8
-// (400 against 406 us).
+// With momentum (three streams in, two out) at most 4 waves per SIMD: 665
+// against 674 us at 5 and 690 at 8 (resnet50, K = 8); the sign kernel is as
+// fast at 5 and 8 (400 us, 395 at 5).
 template <bool kDecode>
-__global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 5))) void
+__global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) void
 k_compress_mom(DevLayout lay, int K, float lr, float mu, const float* __restrict__ g,
                float* __restrict__ m, float* __restrict__ e, uint64_t* __restrict__ signs,
                const float* __restrict__ scales) {
-  compress_tile<kDecode, true>(lay, K, lr, mu, g, m, e, signs, scales);
+  const unsigned b = blockIdx.x;
+  compress_tile<kDecode, true, kXhNone, kSWaves, kU>(lay, (int)(b % (unsigned)K),
+                                                     b / (unsigned)K, lr, mu, g, m, e, signs,
+                                                     scales, nullptr, nullptr, nullptr, nullptr);
+}
+
+// ------------------------------------------------------------------ worker step
+// Step ahead and worker compression of one iteration in one pass, for calls
+// that are given the gradient up front: x^(k) = x_t - e^(k) and Delta^(k) =
+// e^(k) + lr g^(k) from one read of e.  Bound by HBM: g and e in, e and xh
+// out, 16 bytes per worker element against 20 for the two kernels.  At
+// resnet50 K = 8, 553-564 us (3.38 GB, 6.0-6.1 TB/s) for 280 + 400 us, at
+// 2^28 parameters 5490 us (6.5 TB/s) for 2980 + 4040 us.  Grid:
+// run_padded_tiles(n_tiles) * K workgroups, one per (tile, worker) in the
+// XCD-aware order of run_tile_of, as in the step ahead: the K workers of a
+// run of tiles follow one another on one XCD and read x from its L2 (worker
+// by worker on one tile, x is fetched K times: 700 against 680 us per
+// iteration; runs of 32, 16 or 8 tiles: 687, 701 and 708).  At most 4 waves
+// per SIMD: two streams in and two out lose to more of them in flight (651
+// us per iteration at 4, 657 at 5, 668 at 8).
+template <bool kDecode, bool kMom, int kXh>
+__global__ __launch_bounds__(kWBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) void
+k_worker(DevLayout lay, int K, float lr, float mu, const float* __restrict__ g,
+         float* __restrict__ m, float* __restrict__ e, uint64_t* __restrict__ signs,
+         const float* __restrict__ scales, const float* __restrict__ x,
+         const uint64_t* __restrict__ ss, const float* __restrict__ sscales,
+         float* __restrict__ xh) {
+  int k;
+  int64_t ti;
+  run_tile_of(blockIdx.x, K, tile_run_shift(lay.n_tiles), k, ti);
+  if (ti >= lay.n_tiles) return;
+  compress_tile<kDecode, kMom, kXh, kWWaves, kWU>(lay, k, ti, lr, mu, g, m, e, signs, scales, x,
+                                                  ss, sscales, xh);
 }
 
 // ------------------------------------------------------------------ finalize
@@ -657,8 +735,6 @@ __global__ __launch_bounds__(kSBlock) void k_aggregate(DevLayout lay, int K, dou
   const Corr c_old((kMode == 1 && kDecode) ? sscales[tile.l] : 0.0f);
   const int64_t W = lay.d_pad >> 6;
   ExactSum acc;
-  u64 lo = 0, hi = 0;
-  bool bad = false;
   for (int w0 = wave_id() * kU; w0 < nw; w0 += kSWaves * kU) {
     if ((w0 + kU) * 64 <= tile.count) {
       aggregate_pass<kMode, kDecode, kAvg, true>(K, inv_k, lay.L, tile.l, W, w0, tile.count,
@@ -669,12 +745,9 @@ __global__ __launch_bounds__(kSBlock) void k_aggregate(DevLayout lay, int K, dou
                                                   signs + gw0, scales, ravg, res, rss, c_old, rx,
                                                   acc);
     }
-    if (kMode == 1) acc.added(kU, lo, hi, bad);
+    if (kMode == 1) acc.added(kU);
   }
-  if (kMode == 1) {
-    acc.finish(lo, hi, bad);
-    block_partial<kSWaves>(lay, lay.k_max, ti, lo, hi, bad);
-  }
+  if (kMode == 1) block_partial<kSWaves>(lay, lay.k_max, ti, acc);
 }
 
 // ------------------------------------------------------------------ materialize
@@ -1062,6 +1135,28 @@ hipError_t launch_compress(const DevLayout& lay, int K, float lr, float mu, cons
     if (decode) SAEF_CMP(k_compress, true); else SAEF_CMP(k_compress, false);
   }
 #undef SAEF_CMP
+  return hipGetLastError();
+}
+
+hipError_t launch_worker(const DevLayout& lay, int K, float lr, float mu, const float* g,
+                         float* m, float* e, uint64_t* signs, const float* scales, bool decode,
+                         const float* x, const uint64_t* srv_signs, const float* srv_scales,
+                         bool decode_x, float* xh, hipStream_t s, const LaunchEvents& ev) {
+  if (decode_x && !decode) return hipErrorInvalidValue;  // never requested
+  const dim3 grid((unsigned)(run_padded_tiles(lay.n_tiles) * K));
+#define SAEF_WK(D, M, X)                                                                        \
+  SAEF_LAUNCH((k_worker<D, M, X>), grid, dim3(kWBlock), 0, s, lay, K, lr, mu, g, m, e, signs, \
+              scales, x, srv_signs, srv_scales, xh)
+  if (m != nullptr) {
+    if (decode_x) SAEF_WK(true, true, kXhDec);
+    else if (decode) SAEF_WK(true, true, kXhPlain);
+    else SAEF_WK(false, true, kXhPlain);
+  } else {
+    if (decode_x) SAEF_WK(true, false, kXhDec);
+    else if (decode) SAEF_WK(true, false, kXhPlain);
+    else SAEF_WK(false, false, kXhPlain);
+  }
+#undef SAEF_WK
   return hipGetLastError();
 }
 

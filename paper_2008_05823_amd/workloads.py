@@ -310,7 +310,7 @@ def topk_algorithmic_bytes_per_param(K: int, density: float, mode: int = 1,
 
 def algorithmic_bytes_per_param(K: int, mode: int = 1, averaging: bool = False,
                                 momentum: bool = False, step_ahead: bool = True,
-                                mismatch: bool = False) -> float:
+                                mismatch: bool = False, one_pass: bool = False) -> float:
     """Bytes the method itself moves per parameter per round.
 
     step ahead: read x and e[k], write xh[k]            4 + 8K
@@ -322,9 +322,12 @@ def algorithmic_bytes_per_param(K: int, mode: int = 1, averaging: bool = False,
     momentum: the worker step also reads and writes m[k]        + 8K
     local error feedback instead of step ahead: read x, write one copy   8
     mismatch bounds: read e[k] and (double-way) e_srv           4K (+ 4)
+    one_pass (the gradient is in place before the step ahead, no averaging): the
+      step ahead and the worker compression read e[k] once        - 4K
     """
     step = (4 + 8 * K) if step_ahead else 8
     comp = (20 if momentum else 12) * K + K / 8
     server = (16 + 1 / 8 + K / 8) if mode == 1 else (8 + K / 8)
     mis = (4 * K + (4 if mode == 1 else 0)) if mismatch else 0
-    return step + comp + server + (4 * K if averaging else 0) + mis
+    shared = 4 * K if one_pass and step_ahead and not averaging else 0
+    return step + comp + server + (4 * K if averaging else 0) + mis - shared
