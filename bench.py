@@ -291,7 +291,8 @@ def main() -> int:
     if topk is not None:
         step_ahead = variant == saef.VARIANT_SAEF
         bytes_round = np.mean([W.topk_algorithmic_bytes_per_param(
-            K, density, w.mode, averaging=bool(w.period and (t + 1) % w.period == 0))["round"]
+            K, density, w.mode, averaging=bool(w.period and (t + 1) % w.period == 0),
+            one_pass=not split)["round"]
             + (8 * K if mu is not None else 0)
             - (0 if step_ahead else (4 + 8 * K) - 8)
             + ((4 * K + (4 if w.mode == 1 else 0)) if args.mismatch else 0)
@@ -314,10 +315,10 @@ def main() -> int:
         c_bytes = (tb["worker"] + (8 * K if mu is not None else 0)
                    + (tb["server"] if tk_pipelined else 0)) * d
     else:
-        stamped = [t for t in timed_ts][::EVENT_EVERY]
-        c_bytes = ((20 if mu is not None else 12) * K + K / 8) * d + np.mean(
-            [0 if split or (w.period and (t + 1) % w.period == 0) else 4 + 4 * K
-             for t in stamped]) * d
+        c_bytes = ((20 if mu is not None else 12) * K + K / 8) * d
+    stamped = list(timed_ts)[::EVENT_EVERY]
+    c_bytes += np.mean([0 if split or (w.period and (t + 1) % w.period == 0) else 4 + 4 * K
+                        for t in stamped]) * d
     c_gbps = c_bytes / (c_ms / c_count * 1e-3) / 1e9 if c_count else None
     traffic = (traffic_from_profile(args.workload)
                if (mu is None and not split and topk is None) else None)

@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -165,6 +166,17 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 bool overlap(const void* p, size_t bytes, const void* q, size_t qbytes) {
   const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
   return a < b + qbytes && b < a + bytes;
+}
+
+// [p, p + bytes) shares memory with one of the (non-null) ranges?
+struct Range {
+  const void* p;
+  size_t bytes;
+};
+bool overlap_any(const void* p, size_t bytes, std::initializer_list<Range> with) {
+  for (const Range& r : with)
+    if (r.p != nullptr && overlap(p, bytes, r.p, r.bytes)) return true;
+  return false;
 }
 
 // Largest grid (workgroups in x) a launch may use.
@@ -582,7 +594,11 @@ int round_impl(const saef_layout* layout, int64_t t, int64_t period, int32_t K, 
   // The gradient is in place, so off the averaging iterations the step ahead
   // shares its pass over e with the compression (resnet50 K = 8: one kernel
   // of 555 us for one of 280 and one of 400).
-  if (period == 0 || (t + 1) % period != 0)
+  // (Not when xh shares memory with a message: the step ahead goes first then.)
+  const size_t wb = (size_t)layout->d_pad / 64 * sizeof(uint64_t), sb = layout->L * sizeof(float);
+  const bool apart = !overlap_any(xh, vb, {{signs, K * wb}, {scales, K * sb}, {srv_signs, wb},
+                                           {srv_scales, sb}});
+  if (apart && (period == 0 || (t + 1) % period != 0))
     return round_end_impl(layout, t, period, K, lr, mu, mode, g, m, e, e_srv, x, signs, scales,
                           srv_signs, srv_scales, stream, dev, xh);
   rc = round_begin_impl(layout, t, period, K, mode, SAEF_VARIANT_SAEF, e, e_srv, x, xh, signs,
@@ -906,13 +922,13 @@ int topk_compress_check(const saef_topk* plan, int32_t K, float lr, float mu, co
 // saef_topk_compress with the pending flags of launch_topk_compress.
 int topk_compress(const saef_topk* plan, int32_t K, float lr, float mu, const float* g,
                   float* m, float* e, uint64_t* sel, uint32_t* rank, float* vals, bool pend_in,
-                  bool pend_out, hipStream_t stream) {
+                  bool pend_out, const saef::TkStep& st, hipStream_t stream) {
   const int rc = topk_compress_check(plan, K, lr, mu, g, m, e, sel, rank, vals);
   if (rc != SAEF_OK) return rc;
   const saef_layout* layout = plan->layout;
   return hip_rc(timed(layout, 1, [&](const saef::LaunchEvents& ev) {
     return saef::launch_topk_compress(layout->dev, plan->dev, plan->all, K, lr, mu, g, m, e, sel,
-                                      rank, vals, pend_in, pend_out, stream, plan->side, ev);
+                                      rank, vals, pend_in, pend_out, st, stream, plan->side, ev);
   }));
 }
 
@@ -953,7 +969,8 @@ int topk_aggregate_check(const saef_topk* plan, int32_t K, int32_t mode, const u
 int saef_topk_compress(const saef_topk* plan, int32_t K, float lr, float mu, const float* g,
                        float* m, float* e, uint64_t* sel, uint32_t* rank, float* vals,
                        hipStream_t stream) {
-  return topk_compress(plan, K, lr, mu, g, m, e, sel, rank, vals, false, false, stream);
+  return topk_compress(plan, K, lr, mu, g, m, e, sel, rank, vals, false, false, saef::TkStep(),
+                       stream);
 }
 
 int saef_topk_materialize(const saef_topk* plan, int32_t K, float* e, const uint64_t* sel,
@@ -984,10 +1001,12 @@ int saef_topk_aggregate(const saef_topk* plan, int32_t K, int32_t mode, const ui
   }));
 }
 
-int saef_topk_round_begin(const saef_topk* plan, int64_t t, int64_t period, int32_t K,
-                          int32_t mode, int32_t variant, float* e, const uint64_t* sel,
-                          const float* e_srv, const float* x, float* xh, double* mismatch,
-                          hipStream_t stream) {
+namespace {
+
+// The argument checks of saef_topk_round_begin.
+int topk_begin_check(const saef_topk* plan, int64_t t, int64_t period, int32_t K, int32_t mode,
+                     int32_t variant, const float* e, const uint64_t* sel, const float* e_srv,
+                     const float* x, const float* xh, const double* mismatch) {
   if (plan == nullptr) return SAEF_EINVAL;
   const saef_layout* layout = plan->layout;
   int rc = check_common(layout, K);
@@ -1019,6 +1038,61 @@ int saef_topk_round_begin(const saef_topk* plan, int64_t t, int64_t period, int3
     if (overlap(sel, wb, e, vb) || overlap(sel, wb, xh, hb) || overlap(sel, wb, x, xb))
       return SAEF_EINVAL;
   }
+  return SAEF_OK;
+}
+
+// saef_topk_round_end; st: the step ahead taken along by the Delta pass.
+int topk_round_end(const saef_topk* plan, int64_t t, int64_t period, int32_t K, float lr,
+                   float mu, int32_t mode, const float* g, float* m, float* e, float* e_srv,
+                   float* x, uint64_t* sel, uint32_t* rank, float* vals, uint64_t* srv_sel,
+                   uint32_t* srv_rank, float* srv_vals, const saef::TkStep& st,
+                   hipStream_t stream) {
+  if (plan == nullptr) return SAEF_EINVAL;
+  if (t < 0 || period < 0) return SAEF_EINVAL;
+  const saef_layout* layout = plan->layout;
+  if (layout == nullptr || K < 1 || K > layout->k_max) return SAEF_EINVAL;
+  const size_t vb = (size_t)K * layout->d_pad * sizeof(float);
+  const size_t xb = layout->d_pad * sizeof(float);
+  if (g != nullptr && x != nullptr && e != nullptr &&
+      (overlap(g, vb, x, xb) || overlap(e, vb, x, xb)))
+    return SAEF_EINVAL;
+  // e is pending unless t = 0 or this iteration's averaging wrote it plain;
+  // the compression leaves its own kept elements pending
+  const bool averaging = period > 0 && (t + 1) % period == 0;
+  const bool pend_in = t > 0 && !averaging;
+  if (plan->pipe.size() >= 2 && plan->side.stream != nullptr) {
+    // pipelined over the plan's parts: one timed span (kind 1) from the
+    // first Delta pass to the last kernel on the caller's stream
+    int rc = topk_compress_check(plan, K, lr, mu, g, m, e, sel, rank, vals);
+    if (rc == SAEF_OK)
+      rc = topk_aggregate_check(plan, K, mode, sel, rank, vals, nullptr, e_srv, srv_sel,
+                                srv_rank, srv_vals, x);
+    if (rc != SAEF_OK) return rc;
+    return hip_rc(timed(layout, 1, [&](const saef::LaunchEvents& ev) {
+      return saef::launch_topk_round_end(layout->dev, plan->dev, plan->pipe.data(),
+                                         (int)plan->pipe.size(), K, lr, mu, mode, g, m, e, sel,
+                                         rank, vals, pend_in, e_srv, srv_sel, srv_rank, srv_vals,
+                                         x, st, stream, plan->side, ev);
+    }));
+  }
+  int rc = topk_compress(plan, K, lr, mu, g, m, e, sel, rank, vals, pend_in, true, st, stream);
+  if (rc != SAEF_OK) return rc;
+  return saef_topk_aggregate(plan, K, mode, sel, rank, vals, nullptr, e_srv, srv_sel, srv_rank,
+                             srv_vals, x, stream);
+}
+
+}  // namespace
+
+int saef_topk_round_begin(const saef_topk* plan, int64_t t, int64_t period, int32_t K,
+                          int32_t mode, int32_t variant, float* e, const uint64_t* sel,
+                          const float* e_srv, const float* x, float* xh, double* mismatch,
+                          hipStream_t stream) {
+  const int rc0 = topk_begin_check(plan, t, period, K, mode, variant, e, sel, e_srv, x, xh,
+                                   mismatch);
+  if (rc0 != SAEF_OK) return rc0;
+  const saef_layout* layout = plan->layout;
+  const bool pending = t > 0;
+  int rc = SAEF_OK;
   const bool averaging = period > 0 && (t + 1) % period == 0;
   const DevLayout& d = layout->dev;
   const int dec = pending ? saef::kDecZero : saef::kDecPlain;
@@ -1053,38 +1127,8 @@ int saef_topk_round_end(const saef_topk* plan, int64_t t, int64_t period, int32_
                         float mu, int32_t mode, const float* g, float* m, float* e, float* e_srv,
                         float* x, uint64_t* sel, uint32_t* rank, float* vals, uint64_t* srv_sel,
                         uint32_t* srv_rank, float* srv_vals, hipStream_t stream) {
-  if (plan == nullptr) return SAEF_EINVAL;
-  if (t < 0 || period < 0) return SAEF_EINVAL;
-  const saef_layout* layout = plan->layout;
-  if (layout == nullptr || K < 1 || K > layout->k_max) return SAEF_EINVAL;
-  const size_t vb = (size_t)K * layout->d_pad * sizeof(float);
-  const size_t xb = layout->d_pad * sizeof(float);
-  if (g != nullptr && x != nullptr && e != nullptr &&
-      (overlap(g, vb, x, xb) || overlap(e, vb, x, xb)))
-    return SAEF_EINVAL;
-  // e is pending unless t = 0 or this iteration's averaging wrote it plain;
-  // the compression leaves its own kept elements pending
-  const bool averaging = period > 0 && (t + 1) % period == 0;
-  const bool pend_in = t > 0 && !averaging;
-  if (plan->pipe.size() >= 2 && plan->side.stream != nullptr) {
-    // pipelined over the plan's parts: one timed span (kind 1) from the
-    // first Delta pass to the last kernel on the caller's stream
-    int rc = topk_compress_check(plan, K, lr, mu, g, m, e, sel, rank, vals);
-    if (rc == SAEF_OK)
-      rc = topk_aggregate_check(plan, K, mode, sel, rank, vals, nullptr, e_srv, srv_sel,
-                                srv_rank, srv_vals, x);
-    if (rc != SAEF_OK) return rc;
-    return hip_rc(timed(layout, 1, [&](const saef::LaunchEvents& ev) {
-      return saef::launch_topk_round_end(layout->dev, plan->dev, plan->pipe.data(),
-                                         (int)plan->pipe.size(), K, lr, mu, mode, g, m, e, sel,
-                                         rank, vals, pend_in, e_srv, srv_sel, srv_rank, srv_vals,
-                                         x, stream, plan->side, ev);
-    }));
-  }
-  int rc = topk_compress(plan, K, lr, mu, g, m, e, sel, rank, vals, pend_in, true, stream);
-  if (rc != SAEF_OK) return rc;
-  return saef_topk_aggregate(plan, K, mode, sel, rank, vals, nullptr, e_srv, srv_sel, srv_rank,
-                             srv_vals, x, stream);
+  return topk_round_end(plan, t, period, K, lr, mu, mode, g, m, e, e_srv, x, sel, rank, vals,
+                        srv_sel, srv_rank, srv_vals, saef::TkStep(), stream);
 }
 
 int saef_topk_round(const saef_topk* plan, int64_t t, int64_t period, int32_t K, float lr,
@@ -1098,6 +1142,22 @@ int saef_topk_round(const saef_topk* plan, int64_t t, int64_t period, int32_t K,
   if (!f32_ok(xh) || !f32_ok(g)) return SAEF_EINVAL;
   const size_t vb = (size_t)K * layout->d_pad * sizeof(float);
   if (overlap(xh, vb, g, vb)) return SAEF_EINVAL;
+  // The gradient is in place: off the averaging iterations the Delta pass
+  // takes the step ahead along, unless xh shares memory with something that
+  // the rest of the iteration writes (then the step ahead goes first).
+  const size_t W = layout->d_pad / 64;
+  const bool apart =
+      !overlap_any(xh, vb, {{m, vb}, {sel, K * W * 8}, {rank, K * W * 4},
+                            {vals, (size_t)K * plan->total_keep * sizeof(float)},
+                            {srv_sel, W * 8}, {srv_rank, W * 4},
+                            {srv_vals, (size_t)plan->total_keep * sizeof(float)}});
+  if (apart && (period <= 0 || (t + 1) % period != 0)) {
+    rc = topk_begin_check(plan, t, period, K, mode, SAEF_VARIANT_SAEF, e, sel, e_srv, x, xh,
+                          nullptr);
+    if (rc != SAEF_OK) return rc;
+    return topk_round_end(plan, t, period, K, lr, mu, mode, g, m, e, e_srv, x, sel, rank, vals,
+                          srv_sel, srv_rank, srv_vals, saef::TkStep{x, xh}, stream);
+  }
   rc = saef_topk_round_begin(plan, t, period, K, mode, SAEF_VARIANT_SAEF, e, sel, e_srv, x, xh,
                              nullptr, stream);
   if (rc != SAEF_OK) return rc;

@@ -43,7 +43,8 @@ constexpr int kTkSpecMaxShare = 8;  // lists when k_l * 8 <= n_l
 // selection kernels of the other rows or tensors, launched on the side
 // stream while a Delta pass streams, find free slots.  At resnet50 K = 8
 // Top-1% per iteration: 1.014 ms against 1.030 ms uncapped, 1.017 ms with
-// only the overlapped pass capped, 1.022 ms at 4 workgroups per CU.
+// only the overlapped pass capped, 1.022 ms at 4 workgroups per CU.  With the
+// step ahead in the pass: 0.876 ms at 5, 0.879 at 4, 0.887 at 6, 0.929 at 3.
 constexpr unsigned kTkDeltaLdsPad = 26624;
 // The Top-K kernels take a tile as 32 sign words (one per lane of a gather
 // wave): they need the layout's tiles to hold 2048 elements.  A library built
@@ -152,11 +153,18 @@ struct TkStreams {
   hipEvent_t fork = nullptr;
   hipEvent_t join = nullptr;
 };
+// The iteration's step ahead xh = x - e taken along by the Delta pass (xh
+// null: not).
+struct TkStep {
+  const float* x = nullptr;
+  float* xh = nullptr;
+};
 // `all`: the part of every tensor.
 hipError_t launch_topk_compress(const DevLayout& lay, const TkDev& tk, const TkPart& all, int K,
                                 float lr, float mu, const float* g, float* m, float* e,
                                 uint64_t* sel, uint32_t* rank, float* vals, bool pend_in,
-                                bool pend_out, hipStream_t s, const TkStreams& side,
+                                bool pend_out, const TkStep& st, hipStream_t s,
+                                const TkStreams& side,
                                 const LaunchEvents& ev = LaunchEvents());
 
 // Sets to 0 the elements of the K rows of e whose selection bit is set.
@@ -186,7 +194,7 @@ hipError_t launch_topk_round_end(const DevLayout& lay, const TkDev& tk, const Tk
                                  const float* g, float* m, float* e, uint64_t* sel,
                                  uint32_t* rank, float* vals, bool pend_in, float* e_srv,
                                  uint64_t* srv_sel, uint32_t* srv_rank, float* srv_vals,
-                                 float* x, hipStream_t s, const TkStreams& side,
-                                 const LaunchEvents& ev = LaunchEvents());
+                                 float* x, const TkStep& st, hipStream_t s,
+                                 const TkStreams& side, const LaunchEvents& ev = LaunchEvents());
 
 }  // namespace saef

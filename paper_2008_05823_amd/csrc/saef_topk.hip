@@ -113,103 +113,126 @@ __device__ __forceinline__ uint32_t spec_floor(const TkSel& st) {
 }
 
 // ------------------------------------------------------------------ pass 1 (workers)
-// kTkU words of one worker's tile: m <- fma(mu, m, g) with kMom, Delta =
-// fma(lr, m or g, e), Delta stored into e, its key counted.
-template <bool kMom, bool kPend, bool kFull>
-__device__ __forceinline__ void delta_words(int w0, int nw, int count, float lr, float mu,
-                                            const float* __restrict__ gk, float* __restrict__ mk,
-                                            float* __restrict__ ek,
-                                            const uint64_t* __restrict__ pk, uint32_t win,
-                                            uint32_t lo, uint32_t* h, uint32_t (&bits)[kTkU],
-                                            u64 (&lm)[kTkU], bool& bad) {
-  const int lane = lane_id();
-  float gv[kTkU], ev[kTkU], mv[kTkU];
-  u64 pw[kTkU];
+// A wave's loads of one worker's tile (kTkU words from w0 on; buffer
+// resources over the tile, so lanes past its end load 0), issued before the
+// histogram is cleared and waited for after it.
+template <bool kMom, bool kPend, bool kXh>
+struct DeltaLoads {
+  float g[kTkU], e[kTkU], m[kTkU], x[kTkU];
+  u64 pend[kTkU];
+
+  __device__ __forceinline__ DeltaLoads(int w0, int nw, Buf rg, Buf re, Buf rm, Buf rx,
+                                        const uint64_t* __restrict__ pk) {
+    const uint32_t off0 = (uint32_t)(w0 * 64 + lane_id()) * 4u;
 #pragma unroll
-  for (int u = 0; u < kTkU; ++u) {
-    const int j = (w0 + u) * 64 + lane;
-    const bool ok = kFull || ((w0 + u < nw) && j < count);
-    gv[u] = ld_nt_or0(gk, j, ok);
-    ev[u] = ld_nt_or0(ek, j, ok);
-    mv[u] = kMom ? ld_nt_or0(mk, j, ok) : 0.0f;
-    pw[u] = (kPend && (kFull || w0 + u < nw)) ? pk[w0 + u] : 0ull;
-  }
-  // the previous call left its kept elements pending: they are 0
-#pragma unroll
-  for (int u = 0; u < kTkU; ++u)
-    if (kPend) ev[u] = sel_by_bit(pw[u], 0.0f, ev[u]);
-#pragma unroll
-  for (int u = 0; u < kTkU; ++u) {
-    const int j = (w0 + u) * 64 + lane;
-    const bool ok = kFull || ((w0 + u < nw) && j < count);
-    float step = gv[u];
-    if (kMom) {
-      step = __builtin_fmaf(mu, mv[u], gv[u]);  // m^(k)_{t+1} = mu m^(k)_t + grad
-      if (ok) st_nt(mk + j, step);
+    for (int u = 0; u < kTkU; ++u) {
+      g[u] = buf_ld(rg, off0 + 256u * u);
+      e[u] = buf_ld(re, off0 + 256u * u);
+      m[u] = kMom ? buf_ld(rm, off0 + 256u * u) : 0.0f;
+      x[u] = kXh ? buf_ld_cached(rx, off0 + 256u * u) : 0.0f;
+      pend[u] = kPend ? ld_word_ro(pk + min(w0 + u, nw - 1)) : 0ull;
     }
-    const float p = __builtin_fmaf(lr, step, ev[u]);  // Delta^(k) = e^(k) + lr m^(k)_{t+1}
+  }
+};
+
+// kTkU words of one worker's tile: m <- fma(mu, m, g) with kMom, Delta =
+// fma(lr, m or g, e), Delta stored into e, its key counted; kXh: xh = x - e
+// from the same read of e.
+template <bool kMom, bool kPend, bool kXh, bool kFull>
+__device__ __forceinline__ void delta_words(const DeltaLoads<kMom, kPend, kXh>& ld, int w0,
+                                            int count, float lr, float mu, Buf rm, Buf re, Buf rh,
+                                            uint32_t win, uint32_t lo, uint32_t* h,
+                                            uint32_t (&bits)[kTkU], u64 (&lm)[kTkU], bool& bad) {
+  const int lane = lane_id();
+  const uint32_t off0 = (uint32_t)(w0 * 64 + lane) * 4u;
+#pragma unroll
+  for (int u = 0; u < kTkU; ++u) {
+    const uint32_t off = off0 + 256u * u;
+    const bool ok = kFull || (w0 + u) * 64 + lane < count;
+    float ev = ld.e[u];
+    if (kPend) ev = sel_by_bit(ld.pend[u], 0.0f, ev);  // kept by the previous call: 0
+    if (kXh) buf_st(rh, off, ld.x[u] - ev);            // x^(k)_{t+1/2} = x_t - e^(k)_t
+    float step = ld.g[u];
+    if (kMom) {
+      step = __builtin_fmaf(mu, ld.m[u], ld.g[u]);  // m^(k)_{t+1} = mu m^(k)_t + grad
+      buf_st(rm, off, step);
+    }
+    const float p = __builtin_fmaf(lr, step, ev);  // Delta^(k) = e^(k) + lr m^(k)_{t+1}
     const uint32_t key = key_of(p);
     bits[u] = __float_as_uint(p);
     lm[u] = __ballot(ok && key >= lo);
+    buf_st(re, off, p);
     if (!ok) continue;
-    st_nt(ek + j, p);
     bad |= key >= kFiniteLimit;
     atomicAdd(&h[hist_bin(key, win)], 1u);
   }
 }
 
-// Grid: (p.t1 - p.t0) * R workgroups; workgroup b handles row row0 + b % R of
-// tile p.t0 + b / R.
+// Grid: run_padded_tiles(p.t1 - p.t0) * R workgroups; workgroup b handles one
+// (tile, row) in the XCD-aware order of run_tile_of over the part's tiles (the
+// rows of a run of tiles follow one another on one XCD and share x there).
 // Each wave takes kTkU words of the tile (one pass); the tile's speculative
 // list is written in index order (wave by wave) when it fits.  kPend: e
 // holds the previous call's Delta with its kept elements (selection words
-// psel) still to be set to 0; they are read as 0.
-template <bool kMom, bool kPend>
+// psel) still to be set to 0; they are read as 0.  kXh: also the iteration's
+// step ahead xh = x - e (the gradient is in place before it): 16 bytes per
+// element for 20 in two kernels.
+template <bool kMom, bool kPend, bool kXh>
 __global__ __launch_bounds__(kBlock) void k_tk_delta(DevLayout lay, TkDev tk, TkPart p, int R,
                                                      int row0,
                                                      float lr, float mu,
                                                      const float* __restrict__ g,
                                                      float* __restrict__ m,
                                                      float* __restrict__ e,
-                                                     const uint64_t* __restrict__ psel) {
+                                                     const uint64_t* __restrict__ psel,
+                                                     const float* __restrict__ x,
+                                                     float* __restrict__ xh) {
   static_assert(kWaves * kTkU == kTileWords, "one pass of the four waves covers a tile");
   __shared__ uint32_t h[kTkHistPad];
   __shared__ uint32_t s_cnt[kWaves];
-  const int k = row0 + (int)(blockIdx.x % (unsigned)R);
-  const int64_t ti = p.t0 + (int64_t)(blockIdx.x / (unsigned)R);
+  int r;
+  int64_t tl;
+  run_tile_of(blockIdx.x, R, tile_run_shift(p.t1 - p.t0), r, tl);
+  if (tl >= p.t1 - p.t0) return;
+  const int k = row0 + r;
+  const int64_t ti = p.t0 + tl;
   const Tile tile = lay.tiles[ti];
   const TkSel* st = tk.sel + (int64_t)k * lay.L + tile.l;
-  const uint32_t win = st->win;
-  const uint32_t lo = spec_floor(*st);
-  for (int i = threadIdx.x; i < kTkHistPad; i += kBlock) h[i] = 0;
-  __syncthreads();
   const int64_t row = (int64_t)k * lay.d_pad + tile.start;
-  const float* gk = g + row;
-  float* mk = kMom ? m + row : nullptr;
-  float* ek = e + row;
+  const uint32_t nbytes = (uint32_t)tile.count * 4u;
+  const Buf rg = buf_of(g + row, nbytes);
+  const Buf re = buf_of(e + row, nbytes);
+  const Buf rm = buf_of(kMom ? m + row : e + row, nbytes);
+  const Buf rx = buf_of(kXh ? x + tile.start : e + row, nbytes);
+  const Buf rh = buf_of(kXh ? xh + row : e + row, nbytes);
   const int nw = (tile.count + 63) >> 6;
   const int wave = wave_id();
   const int w0 = wave * kTkU;
+  const uint64_t* pk = kPend ? psel + (int64_t)k * (lay.d_pad >> 6) + (tile.start >> 6) : nullptr;
+  const DeltaLoads<kMom, kPend, kXh> ld(w0, nw, rg, re, rm, rx, pk);
+  const uint32_t win = st->win;
+  const uint32_t lo = spec_floor(*st);
+  for (int i = threadIdx.x; i < kTkHistPad; i += kBlock) h[i] = 0;
+  lds_barrier();
   bool bad = false;
   uint32_t bits[kTkU];  // Delta's bit patterns
   u64 lm[kTkU];
 #pragma unroll
   for (int u = 0; u < kTkU; ++u) lm[u] = 0ull;
-  const uint64_t* pk = kPend ? psel + (int64_t)k * (lay.d_pad >> 6) + (tile.start >> 6) : nullptr;
   if (w0 < nw) {
     if ((w0 + kTkU) * 64 <= tile.count)
-      delta_words<kMom, kPend, true>(w0, nw, tile.count, lr, mu, gk, mk, ek, pk, win, lo, h, bits,
-                                     lm, bad);
+      delta_words<kMom, kPend, kXh, true>(ld, w0, tile.count, lr, mu, rm, re, rh, win, lo, h, bits,
+                                          lm, bad);
     else
-      delta_words<kMom, kPend, false>(w0, nw, tile.count, lr, mu, gk, mk, ek, pk, win, lo, h,
-                                      bits, lm, bad);
+      delta_words<kMom, kPend, kXh, false>(ld, w0, tile.count, lr, mu, rm, re, rh, win, lo, h,
+                                           bits, lm, bad);
   }
   if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(lay.status, kStatusRange);
   uint32_t mine = 0;
 #pragma unroll
   for (int u = 0; u < kTkU; ++u) mine += (uint32_t)__popcll(lm[u]);
   if (lane_id() == 0) s_cnt[wave] = mine;
-  __syncthreads();
+  lds_barrier();
   uint32_t before = 0, total = 0;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) {
@@ -1383,20 +1406,27 @@ struct Launcher {
   const TkDev& tk;
   hipStream_t s;
 
-  // The Delta pass of R rows (row0..) over the part's tiles; `start` stamps
-  // the dispatch's start when non-null.
+  // The Delta pass of R rows (row0..) over the part's tiles, with the step
+  // ahead when st.xh is given; `start` stamps the dispatch's start when
+  // non-null.
   hipError_t delta(const TkPart& p, int R, int row0, float lr, float mu, const float* g,
-                   float* m, float* e, const uint64_t* psel, bool pend_in,
+                   float* m, float* e, const uint64_t* psel, bool pend_in, const TkStep& st,
                    hipEvent_t start) const {
-    const dim3 grid((unsigned)((int64_t)(p.t1 - p.t0) * R));
-#define SAEF_TKD(MOM, PEND)                                                                  \
-  hipExtLaunchKernelGGL((k_tk_delta<MOM, PEND>), grid, dim3(kBlock), kTkDeltaLdsPad, s, start, \
-                        nullptr, 0, lay, tk, p, R, row0, lr, mu, g, m, e, psel)
+    const dim3 grid((unsigned)(run_padded_tiles(p.t1 - p.t0) * R));
+#define SAEF_TKD(MOM, PEND, XH)                                                               \
+  hipExtLaunchKernelGGL((k_tk_delta<MOM, PEND, XH>), grid, dim3(kBlock), kTkDeltaLdsPad, s,   \
+                        start, nullptr, 0, lay, tk, p, R, row0, lr, mu, g, m, e, psel, st.x,  \
+                        st.xh)
+#define SAEF_TKD_X(MOM, PEND)                                                         \
+  do {                                                                                \
+    if (st.xh != nullptr) SAEF_TKD(MOM, PEND, true); else SAEF_TKD(MOM, PEND, false); \
+  } while (0)
     if (m != nullptr) {
-      if (pend_in) SAEF_TKD(true, true); else SAEF_TKD(true, false);
+      if (pend_in) SAEF_TKD_X(true, true); else SAEF_TKD_X(true, false);
     } else {
-      if (pend_in) SAEF_TKD(false, true); else SAEF_TKD(false, false);
+      if (pend_in) SAEF_TKD_X(false, true); else SAEF_TKD_X(false, false);
     }
+#undef SAEF_TKD_X
 #undef SAEF_TKD
     return hipGetLastError();
   }
@@ -1506,8 +1536,8 @@ static hipError_t join_side(hipStream_t s, const TkStreams& side, hipError_t err
 hipError_t launch_topk_compress(const DevLayout& lay, const TkDev& tk, const TkPart& all, int K,
                                 float lr, float mu, const float* g, float* m, float* e,
                                 uint64_t* sel, uint32_t* rank, float* vals, bool pend_in,
-                                bool pend_out, hipStream_t s, const TkStreams& side,
-                                const LaunchEvents& ev) {
+                                bool pend_out, const TkStep& st, hipStream_t s,
+                                const TkStreams& side, const LaunchEvents& ev) {
   // The Delta pass of a group of rows is HBM-bound; the selection chain that
   // follows it (sums, pick, offsets, gather, select, scan, emit) is mostly
   // launch- and latency-bound.  With a side stream the workers are taken in
@@ -1519,7 +1549,7 @@ hipError_t launch_topk_compress(const DevLayout& lay, const TkDev& tk, const TkP
   const Launcher main{lay, tk, s};
   const int64_t W = lay.d_pad >> 6;
   // the first Delta pass stamps the start event, the last kernel on s the stop event
-  hipError_t err = main.delta(all, R0, 0, lr, mu, g, m, e, sel, pend_in, ev.start);
+  hipError_t err = main.delta(all, R0, 0, lr, mu, g, m, e, sel, pend_in, st, ev.start);
   if (err != hipSuccess) return err;
   if (!split) return main.select_and_emit(all, K, 0, e, sel, rank, vals, nullptr, pend_out, ev);
   const int R1 = K - R0;
@@ -1527,7 +1557,7 @@ hipError_t launch_topk_compress(const DevLayout& lay, const TkDev& tk, const TkP
   if ((err = hipStreamWaitEvent(side.stream, side.fork, 0)) != hipSuccess) return err;
   const Launcher aside{lay, tk, side.stream};
   err = aside.select_and_emit(all, R0, 0, e, sel, rank, vals, nullptr, pend_out, LaunchEvents());
-  if (err == hipSuccess) err = main.delta(all, R1, R0, lr, mu, g, m, e, sel, pend_in, nullptr);
+  if (err == hipSuccess) err = main.delta(all, R1, R0, lr, mu, g, m, e, sel, pend_in, st, nullptr);
   if (err == hipSuccess)
     err = main.select_and_emit(all, R1, R0, e + (int64_t)R0 * lay.d_pad, sel + (int64_t)R0 * W,
                                rank + (int64_t)R0 * W, vals + (int64_t)R0 * tk.total_keep,
@@ -1540,8 +1570,8 @@ hipError_t launch_topk_round_end(const DevLayout& lay, const TkDev& tk, const Tk
                                  const float* g, float* m, float* e, uint64_t* sel,
                                  uint32_t* rank, float* vals, bool pend_in, float* e_srv,
                                  uint64_t* srv_sel, uint32_t* srv_rank, float* srv_vals,
-                                 float* x, hipStream_t s, const TkStreams& side,
-                                 const LaunchEvents& ev) {
+                                 float* x, const TkStep& st, hipStream_t s,
+                                 const TkStreams& side, const LaunchEvents& ev) {
   // Every step after the Delta pass works tensor by tensor, so the parts are
   // independent once their Delta is formed: the Delta passes of the parts
   // stream one after another on s, and each part but the last, as soon as
@@ -1557,7 +1587,7 @@ hipError_t launch_topk_round_end(const DevLayout& lay, const TkDev& tk, const Tk
   for (int i = 0; i < n_parts && err == hipSuccess; ++i) {
     const TkPart& p = parts[i];
     const bool last = i == n_parts - 1;
-    err = main.delta(p, K, 0, lr, mu, g, m, e, sel, pend_in, i == 0 ? ev.start : nullptr);
+    err = main.delta(p, K, 0, lr, mu, g, m, e, sel, pend_in, st, i == 0 ? ev.start : nullptr);
     if (err == hipSuccess && !last) {
       err = hipEventRecord(side.fork, s);
       if (err == hipSuccess) err = hipStreamWaitEvent(side.stream, side.fork, 0);

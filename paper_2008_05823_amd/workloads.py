@@ -287,7 +287,7 @@ def topk_keep(w: Workload, percent: float) -> np.ndarray:
 
 
 def topk_algorithmic_bytes_per_param(K: int, density: float, mode: int = 1,
-                                     averaging: bool = False) -> dict:
+                                     averaging: bool = False, one_pass: bool = False) -> dict:
     """Bytes the Top-K iteration itself moves per parameter (density = kept
     fraction).  A message is the selection bit (1/8), the rank word share
     (4 B per 64 elements: 1/16) and the kept values (4 density).
@@ -299,13 +299,15 @@ def topk_algorithmic_bytes_per_param(K: int, density: float, mode: int = 1,
                                                            + 4 density + 8 density
     server, single-way: read the K messages, read/write x  K (3/16 + 4 density) + 8
     an error-averaging round also writes e[k] once more     + 4K
+    one_pass (the gradient is in place before the step ahead, no averaging): the
+      step ahead and the worker compression read e[k] once    - 4K in "round"
     """
     msg = 3 / 16 + 4 * density
     step = 4 + 8 * K
     worker = (12 + msg) * K
     server = K * msg + (8 + msg + 8 * density if mode == 1 else 8)
     return {"step": step, "worker": worker, "server": server,
-            "round": step + worker + server + (4 * K if averaging else 0)}
+            "round": step + worker + server + (4 * K if averaging else -4 * K if one_pass else 0)}
 
 
 def algorithmic_bytes_per_param(K: int, mode: int = 1, averaging: bool = False,
