@@ -232,12 +232,12 @@ typedef struct saef_topk saef_topk;
  * elements, written by the worker Delta pass and the server aggregation: 2
  * bytes per element of d_pad for each of the k_max + 1 rows).  The selection state
  * keeps, per worker row and tensor, where the last call found its threshold:
- * the next call's histogram is placed there, so the first call on a plan (or
- * one after the data scale rose by more than about two binades, or fell by
- * more than about nine) takes longer; the results never depend on it.  The
+ * the next call's histogram is fine there, so the first call on a plan (or
+ * one whose threshold rose by more than about a binade, or fell by more than
+ * about one and a half) takes longer; the results never depend on it.  The
  * plan also owns a second HIP stream (default priority) and two events:
- * saef_topk_compress and saef_topk_round_end give part of their work to that
- * stream and make the caller's stream wait for it before they return.
+ * large saef_topk_compress and saef_topk_round_end calls give part of their
+ * work to that stream and make the caller's stream wait for it before they return.
  * Calls using one plan must not run concurrently.  Synchronises the device;
  * the layout must outlive the plan. */
 int saef_topk_create(const saef_layout* layout, const int64_t* keep, saef_topk** out);
@@ -280,7 +280,8 @@ int saef_topk_aggregate(const saef_topk* plan, int32_t K, int32_t mode, const ui
  * NULL, then mu must be 0), leaving the kept elements pending, and
  * saef_topk_aggregate with the gradient g the caller computed at xh; t and
  * period must be those of the begin call (they tell whether e is pending).
- * With two or more tensors the plan's side stream runs part of it: the
+ * With two or more tensors and at least 16384 (tile, worker) pairs (a tile
+ * is up to 2048 elements of a tensor) the plan's side stream runs part of it: the
  * tensor list is cut in two runs of whole tensors, and the first run's
  * selection, messages and server step go to the side stream (after an event
  * recorded on `stream`) while the second run's worker pass streams on

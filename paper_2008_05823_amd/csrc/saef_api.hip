@@ -56,11 +56,14 @@ struct saef_topk {
   void* mem_thist = nullptr;
   void* mem_ghist = nullptr;
   void* mem_sghist = nullptr;
-  void* mem_goff = nullptr;
   void* mem_sel = nullptr;
   void* mem_tile_cnt = nullptr;
   void* mem_cand = nullptr;
-  void* mem_cand_off = nullptr;
+  void* mem_lcnt = nullptr;
+  void* mem_rhist = nullptr;
+  void* mem_tile_cand = nullptr;
+  void* mem_seg = nullptr;
+  void* mem_large = nullptr;
   void* mem_spec = nullptr;
   // the side stream (default priority) and fork/join events of the worker
   // compression's two row groups and of the pipelined iteration end
@@ -107,14 +110,14 @@ void* scratch_of(int dev) {
 // order (SAEF_TK_PARTS of them, fewer when there are fewer tensors; one part
 // means no pipeline), cut where the running element count passes the first
 // part's share of d (SAEF_TK_FIRST_PCT percent), then equal shares of the
-// rest.  At resnet50 K = 8 Top-1% a 45% share (cut at 48.8% by the tensor
-// boundaries) took 1.002-1.004 ms per iteration, 40% 1.005-1.007 ms, 50%
-// (57%) 1.011 ms, 35% 1.053-1.057 ms.
+// rest.  At resnet50 K = 8 a 60% share took 836 us per Top-1% iteration and
+// 1057 at Top-10%, 55% 844 and 1069, 45% 848 and 1064, 70% 854 against 851 (an
+// earlier build); three parts lost (913 against 858).
 #ifndef SAEF_TK_PARTS
 #define SAEF_TK_PARTS 2
 #endif
 #ifndef SAEF_TK_FIRST_PCT
-#define SAEF_TK_FIRST_PCT 45
+#define SAEF_TK_FIRST_PCT 60
 #endif
 std::vector<saef::TkPart> pipeline_parts(const saef_layout* layout,
                                          const std::vector<saef::TkTensor>& tens) {
@@ -145,7 +148,8 @@ std::vector<saef::TkPart> pipeline_parts(const saef_layout* layout,
     out.push_back(saef::TkPart{l0, l1, ta.first_tile, tb.first_tile + tb.ntiles, a.first_group,
                                b.first_group + b.ngroups, a.first_sgroup,
                                b.first_sgroup + b.nsgroups, a.first_chunk,
-                               b.first_chunk + b.nchunks});
+                               b.first_chunk + b.nchunks, a.large,
+                               b.large + (b.ngroups > 0 ? 1 : 0)});
     l0 = l1;
   }
   return out;
@@ -251,8 +255,8 @@ void free_topk(saef_topk* p) {
   if (p->side.fork != nullptr) (void)hipEventDestroy(p->side.fork);
   if (p->side.join != nullptr) (void)hipEventDestroy(p->side.join);
   for (void* q : {p->mem_chunks, p->mem_tens, p->mem_groups, p->mem_sgroups, p->mem_thist,
-                  p->mem_ghist, p->mem_sghist, p->mem_goff, p->mem_sel, p->mem_tile_cnt,
-                  p->mem_cand, p->mem_cand_off, p->mem_spec})
+                  p->mem_ghist, p->mem_sghist, p->mem_sel, p->mem_tile_cnt, p->mem_lcnt,
+                  p->mem_rhist, p->mem_tile_cand, p->mem_seg, p->mem_large, p->mem_cand, p->mem_spec})
     (void)hipFree(q);
   delete p;
 }
@@ -760,21 +764,33 @@ int saef_topk_create(const saef_layout* layout, const int64_t* keep, saef_topk**
   if (p == nullptr) return SAEF_EHIP;
   p->layout = layout;
   p->keep.assign(keep, keep + L);
-  // server chunks (kTkChunk elements), tile groups (kTkGroup tiles) and, for
-  // tensors with more than kTkGroup groups, super-groups (kTkGroup groups)
+  // server chunks (kTkChunk elements); for large tensors
+  // (below) tile groups (kTkGroup tiles), and for those with more than
+  // kTkGroup groups (huge) super-groups (kTkGroup groups)
   std::vector<saef::TkChunk> chunks;
   std::vector<saef::TkTensor> tens(L);
   std::vector<saef::TkGroup> groups, sgroups;
+  std::vector<int32_t> large;
+  // A tensor of up to small_tiles tiles is selected by one workgroup of one
+  // kernel; the others are large.  One workgroup takes up to a group of
+  // tiles; where larger tensors need the other kernels anyway, only a
+  // quarter (beyond, spreading the tiles over workgroups is faster).
+  int32_t small_tiles = saef::kTkGroup;
+  for (int32_t l = 0; l < L; ++l)
+    if (layout->tensors[l].ntiles > saef::kTkGroup) small_tiles = saef::kTkSmall;
   for (int32_t l = 0; l < L; ++l) {
     const int64_t n = layout->n[l];
     const int64_t nc = (n + saef::kTkChunk - 1) / saef::kTkChunk;
     const int32_t first_tile = layout->tensors[l].first_tile, ntiles = layout->tensors[l].ntiles;
-    const int32_t ng = (ntiles + saef::kTkGroup - 1) / saef::kTkGroup;
+    const int32_t ng =
+        ntiles > small_tiles ? (ntiles + saef::kTkGroup - 1) / saef::kTkGroup : 0;
     const int32_t nsg = ng > saef::kTkGroup ? (ng + saef::kTkGroup - 1) / saef::kTkGroup : 0;
     tens[l] = saef::TkTensor{p->total_keep,          keep[l],
                              (int32_t)chunks.size(), (int32_t)nc,
                              (int32_t)groups.size(), ng,
-                             (int32_t)sgroups.size(), nsg};
+                             (int32_t)sgroups.size(), nsg,
+                             (int32_t)large.size(),   0};
+    if (ng > 0) large.push_back(l);
     p->total_keep += keep[l];
     for (int64_t c = 0; c < nc; ++c)
       chunks.push_back(saef::TkChunk{layout->off[l] + c * saef::kTkChunk, l,
@@ -788,10 +804,12 @@ int saef_topk_create(const saef_layout* layout, const int64_t* keep, saef_topk**
                                      std::min(saef::kTkGroup, ntiles - g * saef::kTkGroup), 0});
   }
   p->all = saef::TkPart{0, L, 0, (int32_t)layout->dev.n_tiles, 0, (int32_t)groups.size(),
-                        0, (int32_t)sgroups.size(), 0, (int32_t)chunks.size()};
+                        0, (int32_t)sgroups.size(), 0, (int32_t)chunks.size(),
+                        0, (int32_t)large.size()};
   p->pipe = pipeline_parts(layout, tens);
   const size_t rows = (size_t)layout->k_max + 1;
-  if ((int64_t)std::max(chunks.size(), groups.size()) * (int64_t)rows > kMaxGrid) {
+  if ((int64_t)std::max(chunks.size(), groups.size() * saef::kTkGatherSplit) * (int64_t)rows >
+      kMaxGrid) {
     free_topk(p);
     return SAEF_EINVAL;
   }
@@ -799,28 +817,36 @@ int saef_topk_create(const saef_layout* layout, const int64_t* keep, saef_topk**
   const size_t thist_bytes = rows * n_tiles * saef::kTkHistPad * sizeof(uint16_t);
   const size_t ghist_bytes = rows * groups.size() * saef::kTkHistPad * sizeof(uint32_t);
   const size_t sghist_bytes = rows * sgroups.size() * saef::kTkHistPad * sizeof(uint32_t);
-  const size_t goff_bytes = rows * groups.size() * sizeof(uint32_t);
   const size_t sel_bytes = rows * L * sizeof(saef::TkSel);
   const size_t cnt_bytes = rows * n_tiles * sizeof(uint32_t);
   // candidate slots: at most every element of a tensor (8 B each) per row
   const size_t cand_bytes = rows * (size_t)layout->d_pad * sizeof(unsigned long long);
-  const size_t cand_off_bytes = rows * n_tiles * sizeof(uint32_t);
+  const size_t rhist_bytes = sgroups.empty() ? 0 : rows * large.size() * saef::kTkRefineLevels * saef::kTkBins * sizeof(uint32_t);
   // speculative candidate lists of the worker rows and the server row
   const size_t spec_bytes =
       (size_t)(layout->k_max + 1) * n_tiles * saef::kTkSpecCap * sizeof(unsigned long long);
   hipError_t err = hipMalloc(&p->mem_chunks, chunks.size() * sizeof(saef::TkChunk));
   if (err == hipSuccess) err = hipMalloc(&p->mem_tens, tens.size() * sizeof(saef::TkTensor));
-  if (err == hipSuccess) err = hipMalloc(&p->mem_groups, groups.size() * sizeof(saef::TkGroup));
+  if (err == hipSuccess && !groups.empty())
+    err = hipMalloc(&p->mem_groups, groups.size() * sizeof(saef::TkGroup));
   if (err == hipSuccess && !sgroups.empty())
     err = hipMalloc(&p->mem_sgroups, sgroups.size() * sizeof(saef::TkGroup));
   if (err == hipSuccess) err = hipMalloc(&p->mem_thist, thist_bytes);
-  if (err == hipSuccess) err = hipMalloc(&p->mem_ghist, ghist_bytes);
+  if (err == hipSuccess && ghist_bytes) err = hipMalloc(&p->mem_ghist, ghist_bytes);
   if (err == hipSuccess && sghist_bytes) err = hipMalloc(&p->mem_sghist, sghist_bytes);
-  if (err == hipSuccess) err = hipMalloc(&p->mem_goff, goff_bytes);
   if (err == hipSuccess) err = hipMalloc(&p->mem_sel, sel_bytes);
   if (err == hipSuccess) err = hipMalloc(&p->mem_tile_cnt, cnt_bytes);
   if (err == hipSuccess) err = hipMalloc(&p->mem_cand, cand_bytes);
-  if (err == hipSuccess) err = hipMalloc(&p->mem_cand_off, cand_off_bytes);
+  if (err == hipSuccess) err = hipMalloc(&p->mem_lcnt, cnt_bytes);
+  if (err == hipSuccess && rhist_bytes) err = hipMalloc(&p->mem_rhist, rhist_bytes);
+  if (err == hipSuccess && rhist_bytes) err = hipMalloc(&p->mem_tile_cand, cnt_bytes);
+  if (err == hipSuccess && !large.empty()) {
+    err = hipMalloc(&p->mem_seg, rows * groups.size() * saef::kTkGatherSplit * sizeof(uint32_t));
+    if (err == hipSuccess) err = hipMalloc(&p->mem_large, large.size() * sizeof(int32_t));
+    if (err == hipSuccess)
+      err = hipMemcpy(p->mem_large, large.data(), large.size() * sizeof(int32_t),
+                      hipMemcpyHostToDevice);
+  }
   if (err == hipSuccess) err = hipMalloc(&p->mem_spec, spec_bytes);
   if (err == hipSuccess)
     err = hipMemcpy(p->mem_chunks, chunks.data(), chunks.size() * sizeof(saef::TkChunk),
@@ -828,7 +854,7 @@ int saef_topk_create(const saef_layout* layout, const int64_t* keep, saef_topk**
   if (err == hipSuccess)
     err = hipMemcpy(p->mem_tens, tens.data(), tens.size() * sizeof(saef::TkTensor),
                     hipMemcpyHostToDevice);
-  if (err == hipSuccess)
+  if (err == hipSuccess && !groups.empty())
     err = hipMemcpy(p->mem_groups, groups.data(), groups.size() * sizeof(saef::TkGroup),
                     hipMemcpyHostToDevice);
   if (err == hipSuccess && !sgroups.empty())
@@ -862,19 +888,21 @@ int saef_topk_create(const saef_layout* layout, const int64_t* keep, saef_topk**
   d.thist = static_cast<uint16_t*>(p->mem_thist);
   d.ghist = static_cast<uint32_t*>(p->mem_ghist);
   d.sghist = static_cast<uint32_t*>(p->mem_sghist);
-  d.goff = static_cast<uint32_t*>(p->mem_goff);
   d.sel = static_cast<saef::TkSel*>(p->mem_sel);
   d.tile_cnt = static_cast<uint32_t*>(p->mem_tile_cnt);
   d.cand = static_cast<unsigned long long*>(p->mem_cand);
-  d.cand_off = static_cast<uint32_t*>(p->mem_cand_off);
+  d.lcnt = static_cast<uint32_t*>(p->mem_lcnt);
+  d.rhist = static_cast<uint32_t*>(p->mem_rhist);
   d.spec = static_cast<unsigned long long*>(p->mem_spec);
   d.n_chunks = (int64_t)chunks.size();
   d.n_groups = (int64_t)groups.size();
   d.n_sgroups = (int64_t)sgroups.size();
+  d.tile_cand = static_cast<uint32_t*>(p->mem_tile_cand);
+  d.seg = static_cast<uint32_t*>(p->mem_seg);
+  d.large = static_cast<const int32_t*>(p->mem_large);
+  d.n_large = (int64_t)large.size();
+  d.refine = sgroups.empty() ? 0 : 1;
   d.total_keep = p->total_keep;
-  d.lists = 0;
-  for (int32_t l = 0; l < L; ++l)
-    if (p->keep[l] * saef::kTkSpecMaxShare <= layout->n[l]) d.lists = 1;
   *out = p;
   return SAEF_OK;
 }
@@ -928,7 +956,11 @@ int topk_compress(const saef_topk* plan, int32_t K, float lr, float mu, const fl
   const saef_layout* layout = plan->layout;
   return hip_rc(timed(layout, 1, [&](const saef::LaunchEvents& ev) {
     return saef::launch_topk_compress(layout->dev, plan->dev, plan->all, K, lr, mu, g, m, e, sel,
-                                      rank, vals, pend_in, pend_out, st, stream, plan->side, ev);
+                                      rank, vals, pend_in, pend_out, st, stream,
+                                      layout->dev.n_tiles * K >= saef::kTkSplitTiles
+                                          ? plan->side
+                                          : saef::TkStreams(),
+                                      ev);
   }));
 }
 
@@ -1060,7 +1092,7 @@ int topk_round_end(const saef_topk* plan, int64_t t, int64_t period, int32_t K, 
   // the compression leaves its own kept elements pending
   const bool averaging = period > 0 && (t + 1) % period == 0;
   const bool pend_in = t > 0 && !averaging;
-  if (plan->pipe.size() >= 2 && plan->side.stream != nullptr) {
+  if (plan->pipe.size() >= 2 && layout->dev.n_tiles * K >= saef::kTkSplitTiles) {
     // pipelined over the plan's parts: one timed span (kind 1) from the
     // first Delta pass to the last kernel on the caller's stream
     int rc = topk_compress_check(plan, K, lr, mu, g, m, e, sel, rank, vals);

@@ -6,37 +6,60 @@
 
 namespace saef {
 
-// Pass-1 histogram of the key |v| over a window of four binades (exponents)
-// of a (row, tensor), placed around the previous call's threshold: 64 bins
-// per binade (key bits 22..17) inside the window; below it one bin per binade
-// for the kTkLo - 1 binades under the window and one bin for all lower keys;
-// one bin above it.  The window only decides how many elements become
-// candidates; the kept set is exact wherever the threshold falls.  (With one
-// bin below, a threshold that fell more than two binades made every element
-// under the window a candidate: at bert_base Top-1% the selection of the word
-// embedding then took 10-23 ms.  Above the window there are few elements.)
-constexpr int kTkSubShift = 17;                // in-window bin width: 2^17 keys
-constexpr int kTkWin = 256;                    // in-window bins (4 binades)
-constexpr int kTkLo = 8;                       // bins below the window
-constexpr int kTkHist = kTkLo + kTkWin + 1;    // + one above
-constexpr int kTkHistPad = 268;                // 16-bit counts per tile (even, 8-byte rows)
+// Pass-1 histogram of the key |v| around the threshold tau of the previous
+// call: a near range of kTkNear bins of 1/512 binade from kTkSpecMargin (1/32
+// binade) under tau to 0.19 binades above it; below it kTkMidB bins of 1/64
+// binade, above it kTkMidA of 1/16, then on each side kTkFar bins of a binade,
+// the last one open.  The bins only decide how many elements become
+// candidates; the kept set is exact wherever the threshold falls.  Under error
+// feedback the residual piles up at tau; tau rises by 0.01-0.2 binades a call
+// (resnet50) and falls by 0.5-1.1 when the errors are averaged.  A bin of 1/64
+// binade at tau (64 in each of four binades before) held 5000-7000 of the
+// 2.36 M elements of the largest tensors at Top-1% and 17000-29000 at
+// Top-10%, and selecting among them was most of the selection's time; 160 bins
+// of 1/2048 binade, or 224 of 1/512 with coarse ones below, miss the moves
+// (Top-10% 1195 and 1154 against 1110 us).
+constexpr int kTkSubShift = 14;                // near bin width: 2^14 keys
+constexpr int kTkNear = 112;                   // near bins
+constexpr int kTkMidShiftB = 17;               // mid bin width below: 2^17 keys
+constexpr int kTkMidB = 96;                    // 1.5 binades
+constexpr int kTkMidShiftA = 19;               // mid bin width above: 2^19 keys
+constexpr int kTkMidA = 16;                    // one binade
+constexpr int kTkFar = 8;                      // bins of a binade beyond, on each side
+constexpr int kTkBelow = kTkMidB + kTkFar;     // bins below the near range
+constexpr int kTkHist = kTkBelow + kTkNear + kTkMidA + kTkFar;
+constexpr int kTkHistPad = 256;                // 16-bit counts per tile
 constexpr int kTkGroup = 64;      // tile histograms (or group sums) one sum workgroup adds
+constexpr int kTkSmall = 16;      // most tiles of a small tensor in a plan with more than a group
+// Fewest (tile, worker) pairs of a call that is split over the side stream: a
+// smaller one streams its Delta in a few microseconds, and a second chain of
+// kernels costs more than it hides (resnet56 K = 8, 4160 pairs: 120 us per
+// Top-5% iteration whole, 131 split; ragged K = 3, 7400 pairs: 262 against
+// 284 us; resnet50 K = 8 has 100,000).
+constexpr int64_t kTkSplitTiles = 16384;
+constexpr int kTkRefineLevels = 2;  // histograms of 11 key bits a refined bin gets
+constexpr int kTkGatherSplit = 4;  // gather workgroups per group of tiles
 constexpr int kTkBins = 2048;     // bins of an 11-bit radix digit
-constexpr int kTkChunk = 65536;   // elements per server-aggregation workgroup
+// Elements per server-aggregation workgroup: four tiles, one per wave.  Its 17
+// KB of LDS let it run beside a Delta pass, and a small layout still fills
+// the chip (resnet56 Top-5%: 120 us per iteration, 123 at 8 tiles, 136 at 16;
+// with 32 tiles in 1024 threads the kernel took 39 us there against 19).
+constexpr int kTkChunk = 8192;
 // Speculative candidate lists: for a tensor that keeps at most 1/8 of its
 // elements, the worker Delta pass also writes, per (row, tile), the elements
 // whose key is at least the previous call's threshold key minus
-// kTkSpecMargin (1/32 binade), in index order, up to kTkSpecCap of them; their
-// count goes to slot kTkSpecSlot of the tile histogram (kTkSpecNone when the
-// tile had more, or for the server row).  When the bin b1 that this call's
+// kTkSpecMargin (1/32 binade), in index order, up to kTkSpecCap of them, and
+// their count (kTkSpecNone when the tile had more); the server aggregation
+// does the same for the server row.  When the bin b1 that this call's
 // histogram picks lies at or above that bound, the list holds every element
-// the gather needs and the tile's Delta is not read again.  (Under error
+// the selection needs and the tile's Delta is not read again.  (Under error
 // feedback the threshold mostly rises from call to call, and the elements
 // just below it pile up: at 1% kept the lists hold about 3% of the elements.)
 constexpr int kTkSpecCap = 512;
-constexpr int kTkSpecSlot = (kTkHist + 1) & ~1;  // the first even slot past the bins
 constexpr uint32_t kTkSpecNone = 0xFFFFu;
 constexpr uint32_t kTkSpecMargin = 1u << 18;
+static_assert((kTkMidA << kTkMidShiftA) == 1 << 23, "the mid bins above cover a binade");
+static_assert((kTkMidB << kTkMidShiftB) == 3 << 22, "the mid bins below cover 1.5 binades");
 constexpr int kTkSpecMaxShare = 8;  // lists when k_l * 8 <= n_l
 // Dynamic LDS the Delta pass requests and does not use: with its own 1 KB
 // it keeps at most 5 of its workgroups on a CU (160 KB of LDS), so the
@@ -52,10 +75,9 @@ constexpr unsigned kTkDeltaLdsPad = 26624;
 // plans (saef_topk_create returns SAEF_EINVAL).
 constexpr int kTkTileElems = 2048;
 constexpr bool kTkUsable = kTileElems == kTkTileElems;
-static_assert(kTkHistPad >= kTkSpecSlot + 2 && kTkHistPad % 4 == 0, "padded tile histogram");
+static_assert(kTkHistPad >= kTkHist && kTkHistPad % 4 == 0, "padded tile histogram");
 static_assert(kTkTileElems < 65536, "a tile's bin counts fit 16 bits");
 static_assert(kTkChunk % kTkTileElems == 0, "a server chunk holds whole tiles");
-static_assert(kTkSpecSlot < kTkHistPad && kTkSpecSlot % 2 == 0, "a spare, even histogram slot");
 static_assert(kTkSpecCap < (int)kTkSpecNone, "list counts fit the slot below the marker");
 static_assert((int64_t)kTileElems * kMaxTilesPerTensor >= kMaxTensor,
               "every tensor is cut into tiles of kTileElems elements");
@@ -81,24 +103,29 @@ struct TkTensor {
   int64_t keep;         // k_l
   int32_t first_chunk;  // server chunks
   int32_t nchunks;
-  int32_t first_group;  // tile groups
-  int32_t ngroups;
-  int32_t first_sgroup;  // super-groups, when ngroups > kTkGroup
+  int32_t first_group;  // tile groups, for a tensor of more than kTkGroup tiles
+  int32_t ngroups;      // 0 otherwise
+  int32_t first_sgroup;  // super-groups, when ngroups > kTkGroup (a huge tensor)
   int32_t nsgroups;      // 0 otherwise
+  int32_t large;         // number among the large tensors
+  int32_t pad;
 };
 
-// Selection state of one (row, tensor): the histogram window (kept from one
-// call to the next); after the pick, the bin b1 that holds the k-th largest
-// key, how many elements to take from it and how many it holds (the
-// candidates); after the select, the threshold key tau and the last kept
-// index iota (in the tensor) of the elements equal to tau.
+// Selection state of one (row, tensor).  Kept from one call to the next:
+// the threshold key tau, the last kept index iota (in the tensor) of the
+// elements equal to tau, and the histogram's near range placed at tau.  Set by
+// the pick: the lists' bound of this call, and for a large tensor the key
+// range [lo, up) of the candidates (the bin that holds the k-th largest key),
+// how many of them to take, and whether the refine narrows the range first.
 struct TkSel {
   uint32_t tau;
-  uint32_t win;     // window base key (a multiple of 2^23)
-  uint32_t bin;     // b1
-  uint32_t lists;   // 1: worker rows of this tensor keep speculative lists (set at creation)
+  uint32_t win;     // first key of the histogram's near range
+  uint32_t floor;   // the lists hold every element with a key >= floor (2^31: no lists)
+  uint32_t lists;   // 1: the rows of this tensor keep speculative lists (set at creation)
+  uint32_t lo, up;
+  uint32_t coarse;  // 1: the refine's histogram narrows [lo, up)
+  uint32_t pad;
   int64_t need;
-  int64_t cand;
   int64_t iota;     // elements equal to tau with index <= iota are kept
 };
 
@@ -112,6 +139,7 @@ struct TkPart {
   int32_t g0, g1;  // tile groups
   int32_t s0, s1;  // super-groups
   int32_t c0, c1;  // server chunks
+  int32_t b0, b1;  // large tensors
 };
 
 struct TkDev {
@@ -122,17 +150,23 @@ struct TkDev {
   uint16_t* thist;     // [rows][n_tiles][kTkHistPad] tile histograms
   uint32_t* ghist;     // [rows][n_groups][kTkHistPad] group sums
   uint32_t* sghist;    // [rows][n_sgroups][kTkHistPad] super-group sums
-  uint32_t* goff;      // [rows][n_groups] first candidate slot of the group in its tensor
   TkSel* sel;          // [rows][L]
   uint32_t* tile_cnt;  // [rows][n_tiles] kept per tile, then the exclusive prefix
-  uint32_t* cand_off;  // [rows][n_tiles] first candidate slot of the tile in its tensor
-  unsigned long long* cand;  // [rows][d_pad] candidate slots: (row, tensor) at the tensor's offset
-  unsigned long long* spec;  // [k_max][n_tiles][kTkSpecCap] key | (index in the tile) << 32
+  uint32_t* lcnt;      // [rows][n_tiles] entries in the tile's speculative list, or kTkSpecNone
+  uint32_t* rhist;     // [rows][n_large][kTkRefineLevels][kTkBins] histograms of the refine
+  uint32_t* tile_cand;  // [rows][n_tiles] candidates of the tile (plans that refine)
+  uint32_t* seg;       // [rows][n_groups * kTkGatherSplit] candidates of each gather workgroup
+  const int32_t* large;  // [n_large] the large tensors, in order
+  // [rows][d_pad] candidate slots: (row, tensor) at the tensor's offset, those
+  // of a gather workgroup at its first tile
+  unsigned long long* cand;
+  unsigned long long* spec;  // [rows][n_tiles][kTkSpecCap] Delta's bits | (index in the tile) << 32
   int64_t n_chunks;
   int64_t n_groups;
   int64_t n_sgroups;
+  int64_t n_large;     // large tensors (more than kTkGroup tiles)
   int64_t total_keep;
-  int32_t lists;  // 1: some tensor keeps speculative lists
+  int32_t refine;      // 1: some tensor has super-groups; wide candidate bins are narrowed
   int32_t pad;
 };
 

@@ -6,38 +6,34 @@
 // non-negative float orders like its value):
 //   histogram  the pass that forms Delta (one workgroup per tile and row)
 //              also counts the keys into a tile histogram (LDS atomics,
-//              16-bit counts stored): 64 bins per binade over a window of
-//              four binades placed around the (row, tensor)'s previous
-//              threshold, one bin per binade for seven binades below it,
-//              one for the keys further down and one above the window;
-//   sum        tile histograms are added per group of 64 tiles (and groups
-//              per super-group for very large tensors);
+//              16-bit counts stored), fine around the (row, tensor)'s
+//              previous threshold and coarser away from it, and writes the
+//              tile's speculative list (the elements at or above a bound just
+//              below the previous threshold);
+//   sum        tile histograms of large tensors are added per group of 64
+//              tiles (and groups per super-group for very large tensors);
 //   pick       a workgroup per (row, tensor) finds the bin b1 that holds the
-//              k-th largest key and each group's first candidate slot;
-//   offsets    each tile's first candidate slot (a scan inside its group);
-//   gather     one wave per tile: elements above b1 are kept for sure
-//              (their count to the tile's kept count); the elements of b1
-//              (the candidates) go to the tile's slots as (key, index in the
-//              tensor), in index order.  Taken from the tile's speculative
-//              list (written by the Delta pass: the elements at or above a
-//              bound just below the previous threshold) when its bound lies
-//              at or below b1, else from one more read of Delta, which also
-//              gives the selection words of the sure elements;
-//   select     a workgroup per (row, tensor) finds, among the candidates only,
-//              the threshold key tau and the last kept index iota of the
-//              elements equal to tau (radix passes on the key bits below
-//              b1's prefix, then on the index), and places the next call's
-//              window around tau; the same workgroup then counts each
-//              tile's kept elements (its definite ones, from the gather, and
-//              its kept candidates) and turns the counts into each tile's
-//              first rank;
-//   emit       one wave per tile adds its kept candidates to its selection
-//              words, then writes the rank words and the kept values in
-//              index order, and sets the kept elements of the error to 0
-//              (e = Delta - C(Delta) is Delta elsewhere); a tile the gather
-//              took from its list is emitted from the list alone.
+//              k-th largest key.  A small tensor (up to 64 tiles; up to 16 in
+//              a plan that has larger ones) it selects as a whole, so its
+//              selection is this one kernel;
+//   refine     (plans with a tensor of more than 4096 tiles) a bin b1 with
+//              many elements is narrowed to a sub-range of it, 11 key bits
+//              at a time, by the workgroups of all tiles;
+//   gather     the elements of b1 (the candidates) of large tensors, tile by
+//              tile, and each tile's count of elements above b1: from the
+//              tile's list when its bound lies at or below b1, else from one
+//              more read of Delta;
+//   select     a workgroup per (row, large tensor) finds, among the
+//              candidates only, the threshold key tau and the last kept index
+//              iota of the elements equal to tau, and turns the tiles' counts
+//              into each tile's first rank;
+//   emit       one wave per tile writes its selection words, rank words and
+//              kept values in index order, and sets the kept elements of the
+//              error to 0 (e = Delta - C(Delta) is Delta elsewhere), from the
+//              tile's list when it reaches down to tau, else from one more
+//              read of Delta.
 // All of it is integer counting, so the kept set does not depend on the
-// launch geometry.
+// launch geometry, nor on the order in which candidates are collected.
 //
 // The streaming passes (Delta, gather) run one short-lived workgroup or wave
 // per 2048-element tile: on MI355X a 2-read/1-write stream reaches about
@@ -55,15 +51,9 @@ namespace {
 constexpr uint32_t kFiniteLimit = 0x7F800000u;  // keys >= this are Inf or NaN
 constexpr int kTkU = 8;                         // words per wave per pass (Delta pass: one pass)
 constexpr int kTileWords = kTkTileElems / 64;     // 32
-constexpr int kBig = 1024;                      // threads of the per-(row, tensor) kernels
+// Threads of the server aggregation: a wave per tile of a chunk.
+constexpr int kAgg = kTkChunk / kTkTileElems * kWave;
 static_assert(kTileWords <= kWave, "one selection word of a tile per lane");
-// Guarded loads without a branch: the load of p[ok ? j : 0] is always
-// issued (p[0] must exist) and its value replaced by 0 when !ok.  A branch
-// around each load makes the compiler wait for it before the next one.
-__device__ __forceinline__ float ld_nt_or0(const float* p, int64_t j, bool ok) {
-  const float v = __builtin_nontemporal_load(p + (ok ? j : 0));
-  return ok ? v : 0.0f;
-}
 // Word 3 of a raw buffer descriptor on gfx9 parts (32-bit data format, no
 // swizzle, no index stride).  A load through a raw buffer resource of n
 // bytes returns 0 for a byte offset at or past n, without touching memory.
@@ -71,24 +61,25 @@ constexpr int kBufWord3 = 0x00020000;
 
 __device__ __forceinline__ uint32_t key_of(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
 
-// Pass-1 bin of a key for the window [win, win + 4 binades) (win a multiple
-// of 2^23, its binade wb): below it, bin kTkLo - j for binade wb - j (j <
-// kTkLo) and bin 0 for all lower keys; kTkLo .. kTkLo + kTkWin - 1 inside it
-// (key bits 22..17 within each binade); kTkLo + kTkWin above it.  Bins order
-// like the keys.
+// Pass-1 bin of a key for the near range [win, win + kTkNear bins).  Bins
+// order like the keys.
 __device__ __forceinline__ uint32_t hist_bin(uint32_t key, uint32_t win) {
   const int32_t s = (int32_t)(key - win);  // keys and win are below 2^31
+  // below: x keys between key and win; above: x keys past the near range
+  const uint32_t xb = ~(uint32_t)s, xa = (uint32_t)s - ((uint32_t)kTkNear << kTkSubShift);
+  const uint32_t mb = xb >> kTkMidShiftB;
+  const uint32_t gb = mb < (uint32_t)kTkMidB
+                          ? mb : (uint32_t)(kTkMidB - 1) + min(xb >> 23, (uint32_t)kTkFar);
+  const uint32_t ga = min(xa >> kTkMidShiftA,
+                          (uint32_t)(kTkMidA - 1) + min(xa >> 23, (uint32_t)kTkFar));
+  const uint32_t side = s < 0 ? (uint32_t)(kTkBelow - 1) - gb : (uint32_t)(kTkBelow + kTkNear) + ga;
   const uint32_t d = (uint32_t)s >> kTkSubShift;
-  if (d < (uint32_t)kTkWin) return (uint32_t)kTkLo + d;
-  if (s >= 0) return (uint32_t)(kTkLo + kTkWin);
-  const int32_t j = s >> 23;  // -(binades below the window's first): <= -1 (win is 2^23-aligned)
-  return (uint32_t)max(j + kTkLo, 0);
+  return d < (uint32_t)kTkNear ? (uint32_t)kTkBelow + d : side;
 }
 
-// The window for the next call: the binade of tau is the third of four.
+// The near range of the next call: from kTkSpecMargin under tau on.
 __device__ __forceinline__ uint32_t window_for(uint32_t tau) {
-  const uint32_t b = tau >> 23;
-  return (b >= 2u ? b - 2u : 0u) << 23;
+  return tau > kTkSpecMargin ? tau - kTkSpecMargin : 0u;
 }
 
 __device__ __forceinline__ uint16_t* tile_hist(const TkDev& tk, const DevLayout& lay, int row,
@@ -96,12 +87,10 @@ __device__ __forceinline__ uint16_t* tile_hist(const TkDev& tk, const DevLayout&
   return tk.thist + ((int64_t)row * lay.n_tiles + ti) * kTkHistPad;
 }
 
-// Stores an LDS histogram of kTkHistPad bins as 16-bit counts, two per store,
-// with `spec` (the tile's speculative list count) in slot kTkSpecSlot.
-__device__ __forceinline__ void store_hist16(const uint32_t* h, uint16_t* out, uint32_t spec) {
+// Stores an LDS histogram of kTkHistPad bins as 16-bit counts, two per store.
+__device__ __forceinline__ void store_hist16(const uint32_t* h, uint16_t* out) {
   for (int i = threadIdx.x; i < kTkHistPad / 2; i += blockDim.x)
-    reinterpret_cast<uint32_t*>(out)[i] =
-        2 * i == kTkSpecSlot ? spec : (h[2 * i] & 0xFFFFu) | (h[2 * i + 1] << 16);
+    reinterpret_cast<uint32_t*>(out)[i] = (h[2 * i] & 0xFFFFu) | (h[2 * i + 1] << 16);
 }
 
 // Lower key bound of the speculative lists of a (row, tensor): the previous
@@ -242,7 +231,8 @@ __global__ __launch_bounds__(kBlock) void k_tk_delta(DevLayout lay, TkDev tk, Tk
   // no list (kTkSpecNone) before the first threshold, for a tensor without
   // lists, or when the tile has more than kTkSpecCap such elements
   const bool fits = lo != 0x80000000u && total <= (uint32_t)kTkSpecCap;
-  store_hist16(h, tile_hist(tk, lay, k, ti), fits ? total : kTkSpecNone);
+  store_hist16(h, tile_hist(tk, lay, k, ti));
+  if (threadIdx.x == 0) tk.lcnt[(int64_t)k * lay.n_tiles + ti] = fits ? total : kTkSpecNone;
   if (fits && mine != 0u) {
     u64* out = tk.spec + ((int64_t)k * lay.n_tiles + ti) * kTkSpecCap;
     const int lane = lane_id();
@@ -258,30 +248,74 @@ __global__ __launch_bounds__(kBlock) void k_tk_delta(DevLayout lay, TkDev tk, Tk
   }
 }
 
+// The sum of the histograms of n <= kN tiles from `first` on (n <= 0: zeros)
+// as packed pairs of 16-bit counts: lane holds words lane and lane + 64 of the
+// kTkHistPad / 2 of a histogram, every load issued at once.
+template <int kN>
+__device__ __forceinline__ void tile_hist_sum(const TkDev& tk, const DevLayout& lay, int row,
+                                              int64_t first, int n, int lane,
+                                              uint32_t (&v)[2]) {
+  constexpr int kW = kTkHistPad / 2;
+  static_assert(kW == 2 * kWave, "two words per lane");
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(tile_hist(tk, lay, row, n > 0 ? first : 0));
+  uint32_t a[kN][2];
+#pragma unroll
+  for (int i = 0; i < kN; ++i) {
+    const uint32_t* t = src + (i < n ? i : 0) * kW;
+    a[i][0] = t[lane];
+    a[i][1] = t[lane + kWave];
+  }
+  v[0] = v[1] = 0;
+#pragma unroll
+  for (int i = 0; i < kN; ++i)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) v[q] += i < n ? a[i][q] : 0u;
+}
+// Adds a wave's packed sums to the histogram h in LDS.
+__device__ __forceinline__ void tile_hist_add(uint32_t* h, int lane, const uint32_t (&v)[2]) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int w = lane + q * kWave;
+    if ((v[q] & 0xFFFFu) != 0u) atomicAdd(&h[2 * w], v[q] & 0xFFFFu);
+    if ((v[q] >> 16) != 0u) atomicAdd(&h[2 * w + 1], v[q] >> 16);
+  }
+}
+
 // ------------------------------------------------------------------ sums
 // Grid: R * n workgroups, n the part's groups (kSuper: super-groups).
 // Workgroup b adds the tile histograms of the part's group b % n (or the
-// group sums of its super-group b % n) of row row0 + b / n.
+// group sums of its super-group b % n) of row row0 + b / n.  Tile histograms:
+// each wave takes 16 tiles with all its loads in flight at once and adds them
+// as pairs of 16-bit counts (16 tiles of 2048 elements do not overflow one).
 template <bool kSuper>
 __global__ __launch_bounds__(kBlock) void k_tk_sum(DevLayout lay, TkDev tk, TkPart p, int row0) {
   const int64_t n = kSuper ? p.s1 - p.s0 : p.g1 - p.g0;
   const int64_t gi = (kSuper ? p.s0 : p.g0) + (int64_t)(blockIdx.x % n);
   const int row = row0 + (int)(blockIdx.x / n);
   const TkGroup gr = (kSuper ? tk.sgroups : tk.groups)[gi];
-  uint32_t* dst = (kSuper ? tk.sghist + ((int64_t)row * tk.n_sgroups + gi) * kTkHistPad
-                          : tk.ghist + ((int64_t)row * tk.n_groups + gi) * kTkHistPad);
-  for (int b = threadIdx.x; b < kTkHistPad; b += kBlock) {
-    uint32_t acc = 0;
-    if (kSuper) {
+  if constexpr (kSuper) {
+    uint32_t* dst = tk.sghist + ((int64_t)row * tk.n_sgroups + gi) * kTkHistPad;
+    for (int b = threadIdx.x; b < kTkHistPad; b += kBlock) {
+      uint32_t acc = 0;
       const uint32_t* src = tk.ghist + ((int64_t)row * tk.n_groups + gr.first) * kTkHistPad + b;
 #pragma unroll 8
       for (int i = 0; i < gr.n; ++i) acc += src[(int64_t)i * kTkHistPad];
-    } else {
-      const uint16_t* src = tile_hist(tk, lay, row, gr.first) + b;
-#pragma unroll 8
-      for (int i = 0; i < gr.n; ++i) acc += src[(int64_t)i * kTkHistPad];
+      dst[b] = acc;
     }
-    dst[b] = acc;
+  } else {
+    __shared__ uint32_t h[kTkHistPad];
+    constexpr int kPer = kTkGroup / kWaves;  // tiles per wave
+    static_assert(kPer * kTkTileElems < 65536, "packed 16-bit sums");
+    const int lane = lane_id();
+    uint32_t v[2];
+    tile_hist_sum<kPer>(tk, lay, row, gr.first + wave_id() * kPer,
+                        min(kPer, gr.n - wave_id() * kPer), lane, v);
+    for (int i = threadIdx.x; i < kTkHistPad; i += kBlock) h[i] = 0;
+    lds_barrier();
+    tile_hist_add(h, lane, v);
+    lds_barrier();
+    uint32_t* dst = tk.ghist + ((int64_t)row * tk.n_groups + gi) * kTkHistPad;
+    for (int i = threadIdx.x; i < kTkHistPad; i += kBlock) dst[i] = h[i];
   }
 }
 
@@ -352,451 +386,71 @@ __device__ void find_bin(const uint32_t* h, int nb, int64_t need, uint32_t* s_sc
   __syncthreads();
 }
 
-// ------------------------------------------------------------------ pick
-// Grid: R * nl workgroups, nl the part's tensors (workgroup b: tensor
-// p.l0 + b % nl of row row0 + b / nl).  Adds the tensor's group sums (or super-group
-// sums), finds the bin b1 that holds the k-th largest key and how many to
-// take from it, and gives each group of the tensor its first candidate slot:
-// the elements of b1 go to the (row, tensor)'s candidate area (one slot per
-// element of the tensor at most) in tile order.
-__global__ __launch_bounds__(kBlock) void k_tk_pick(DevLayout lay, TkDev tk, TkPart p, int row0) {
-  __shared__ uint32_t s_scan[kWaves];
-  __shared__ uint32_t s_res[3];
-  __shared__ uint32_t h[kTkHistPad];
-  const int nl = p.l1 - p.l0;
-  const int l = p.l0 + (int)(blockIdx.x % (unsigned)nl);
-  const int r = (int)(blockIdx.x / (unsigned)nl);
-  const int row = row0 + r;
-  const TkTensor t = tk.tens[l];
-  const bool super = t.nsgroups > 0;
-  const uint32_t* src = super
-      ? tk.sghist + ((int64_t)row * tk.n_sgroups + t.first_sgroup) * kTkHistPad
-      : tk.ghist + ((int64_t)row * tk.n_groups + t.first_group) * kTkHistPad;
-  const int ns = super ? t.nsgroups : t.ngroups;
-  for (int b = threadIdx.x; b < kTkHistPad; b += kBlock) {
-    uint32_t cnt = 0;
-    for (int i = 0; i < ns; ++i) cnt += src[(int64_t)i * kTkHistPad + b];
-    h[b] = cnt;
-  }
-  __syncthreads();
-  uint32_t b1, n1;
-  int64_t left;
-  find_bin<true>(h, kTkHist, t.keep, s_scan, s_res, b1, left, n1);
-  // first candidate slot of each group, in group order
-  uint32_t carry = 0;
-  const uint32_t* gh = tk.ghist + ((int64_t)row * tk.n_groups + t.first_group) * kTkHistPad + b1;
-  for (int g0 = 0; g0 < t.ngroups; g0 += kBlock) {
-    const int gi = g0 + threadIdx.x;
-    const uint32_t v = gi < t.ngroups ? gh[(int64_t)gi * kTkHistPad] : 0u;
-    uint32_t all;
-    const uint32_t before = block_excl_scan(v, s_scan, &all);
-    if (gi < t.ngroups) tk.goff[(int64_t)row * tk.n_groups + t.first_group + gi] = carry + before;
-    carry += all;
-  }
-  if (threadIdx.x == 0) {
-    TkSel* st = tk.sel + (int64_t)row * lay.L + l;
-    st->bin = b1;
-    st->need = left;
-    st->cand = n1;  // the elements of b1 (the sum of the tile counts)
-  }
-}
+// ------------------------------------------------------------------ selection
+// The selection of a (row, tensor): the bin b1 of the summed histograms that
+// holds the k-th largest key gives the key range [lo, up) of the candidates;
+// elements above it are kept for sure, and among the candidates the `need`
+// first by (key descending, index ascending) are.  The threshold tau and the
+// last kept index iota among the keys equal to it describe the kept set, and
+// each tile's first rank follows from its counts.  The order in which
+// candidates are collected does not matter.
+constexpr int kPick = 256;      // threads of the pick
+constexpr int kSelect = 512;    // threads of the select of large tensors
+constexpr int kPickCand = 512;  // candidates the pick keeps in LDS
+constexpr int kSelKeys = 4096;  // candidates whose keys the select keeps in LDS
+constexpr int kSelTiles = 2048; // tiles whose counts the select's LDS holds (packed 16-bit)
+constexpr int kRefineCand = 4096;  // more candidates than this are narrowed (refine)
+constexpr int kRefineLevels = kTkRefineLevels;
+constexpr int kGatherSplit = kTkGatherSplit;
+constexpr int kGatherTiles = kTkGroup / kGatherSplit;  // tiles per gather workgroup
+static_assert(kTkTileElems < 65536 / 2, "a tile's counts fit 16 bits");
 
-// Grid: R * n workgroups of one wave, n the part's groups: the first
-// candidate slot of each tile of the part's group b % n in row row0 + b / n
-// (the group's slot plus the b1 counts of the group's earlier tiles).
-__global__ __launch_bounds__(kWave) void k_tk_offsets(DevLayout lay, TkDev tk, TkPart p,
-                                                      int row0) {
-  static_assert(kTkGroup == kWave, "one tile of a group per lane");
-  const int64_t n = p.g1 - p.g0;
-  const int64_t gi = p.g0 + (int64_t)(blockIdx.x % n);
-  const int row = row0 + (int)(blockIdx.x / n);
-  const TkGroup gr = tk.groups[gi];
-  const uint32_t b1 = tk.sel[(int64_t)row * lay.L + gr.l].bin;
-  const int lane = lane_id();
-  const uint32_t c = lane < gr.n ? tile_hist(tk, lay, row, gr.first + lane)[b1] : 0u;
-  uint32_t x = c;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off);
-    if (lane >= off) x += y;
-  }
-  if (lane < gr.n)
-    tk.cand_off[(int64_t)row * lay.n_tiles + gr.first + lane] =
-        tk.goff[(int64_t)row * tk.n_groups + gi] + x - c;
-}
-
-// ------------------------------------------------------------------ gather
-// The smallest key of bin b for the window at win (hist_bin's layout; a
-// below bin for a binade under 0 is empty and starts at 0); kTkHist (one
-// past the last bin) gives 2^31, above every key.
+// The smallest key of bin b for the near range at win (hist_bin's layout; a
+// bin below key 0 is empty and starts at 0); kTkHist (one past the last bin)
+// gives 2^31, above every key.
 __device__ __forceinline__ uint32_t bin_floor(uint32_t b, uint32_t win) {
-  const int64_t wb = win >> 23;
-  if (b == 0u) return 0u;
   if (b >= (uint32_t)kTkHist) return 0x80000000u;
   int64_t f;
-  if (b < (uint32_t)kTkLo) {
-    const int64_t kb = wb - (kTkLo - (int64_t)b);  // the bin's binade
-    f = kb > 0 ? kb << 23 : 0;
-  } else if (b < (uint32_t)(kTkLo + kTkWin)) {
-    f = (int64_t)win + ((int64_t)(b - kTkLo) << kTkSubShift);
+  if (b < (uint32_t)kTkBelow) {
+    // bin g of the side: distances up to (below) the first of bin g + 1
+    const int64_t g = kTkBelow - 1 - (int64_t)b;
+    if (g == kTkBelow - 1) return 0u;
+    f = (int64_t)win - (g < kTkMidB ? (g + 1) << kTkMidShiftB : (g - kTkMidB + 2) << 23);
+  } else if (b < (uint32_t)(kTkBelow + kTkNear)) {
+    f = (int64_t)win + ((int64_t)(b - kTkBelow) << kTkSubShift);
   } else {
-    f = (wb + 4) << 23;  // the bin above the window
+    const int64_t g = (int64_t)b - (kTkBelow + kTkNear);
+    f = (int64_t)win + ((int64_t)kTkNear << kTkSubShift) +
+        (g < kTkMidA ? g << kTkMidShiftA : (g - kTkMidA + 1) << 23);
   }
-  return f < 0x80000000ll ? (uint32_t)f : 0x80000000u;
+  return f <= 0 ? 0u : f < 0x80000000ll ? (uint32_t)f : 0x80000000u;
 }
 
-// The key bits bin b fixes: keys of the bin are those with key >> open ==
-// prefix (open = 17 inside the window, 23 for a one-binade bin, 31 for the
-// lowest bin and the one above the window).
-__device__ __forceinline__ void bin_prefix(uint32_t b, uint32_t win, uint32_t& prefix, int& open) {
-  const uint32_t wb = win >> 23;
-  if (b >= (uint32_t)kTkLo && b < (uint32_t)(kTkLo + kTkWin)) {
-    prefix = (win >> kTkSubShift) + (b - kTkLo);
-    open = kTkSubShift;
-  } else if (b >= 1u && b < (uint32_t)kTkLo && wb >= (uint32_t)kTkLo - b) {
-    prefix = wb - ((uint32_t)kTkLo - b);
-    open = 23;
-  } else {
-    prefix = 0u;
-    open = 31;
-  }
+// Bits of the offsets 0 .. up - lo - 1 of the keys in [lo, up).
+__device__ __forceinline__ int range_bits(uint32_t lo, uint32_t up) {
+  const uint32_t last = up - lo - 1u;
+  return up <= lo || last == 0u ? 0 : 32 - __builtin_clz(last);
 }
 
-// The gather's classification of a tile's 32 words (kFull: all 2048
-// elements exist): selection words (lane u gets word u) and candidates to
-// their slots in index order.
-template <bool kFull>
-__device__ __forceinline__ void gather_words(const float (&v)[kTileWords], int count, uint32_t lo,
-                                             uint32_t up, int64_t rel0, uint32_t nslots,
-                                             u64* __restrict__ slots, u64& myw, uint32_t& base) {
-  const int lane = lane_id();
+// A candidate: key | (index in the tensor) << 32.
+__device__ __forceinline__ u64 cand_of(uint32_t key, int64_t idx) {
+  return (u64)key | ((u64)idx << 32);
+}
+
+__device__ __forceinline__ void tile_count_add(uint32_t* t, int tile, uint32_t n) {
+  atomicAdd(&t[tile >> 1], n << (16 * (tile & 1)));
+}
+__device__ __forceinline__ uint32_t tile_count(const uint32_t* t, int tile) {
+  return (t[tile >> 1] >> (16 * (tile & 1))) & 0xFFFFu;
+}
+
+// A tile's 2048 elements of Delta, word by word (lane i: element 64 u + i),
+// all loads in flight at once; past the tile's end 0.
+__device__ __forceinline__ void load_tile(const float* d, int count, float (&v)[kTileWords]) {
+  const Buf r = buf_of(d, (uint32_t)count * 4u);
 #pragma unroll
-  for (int u = 0; u < kTileWords; ++u) {
-    const int j = u * 64 + lane;
-    const bool ok = kFull || j < count;
-    const uint32_t key = key_of(v[u]);
-    const u64 word = __ballot(ok && key >= up);
-    if (lane == u) myw = word;
-    const u64 cm = __ballot(ok && key - lo < up - lo);  // lo <= key < up
-    if (cm != 0ull) {  // wave-uniform: most words have no candidate
-      const uint32_t pos = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(cm >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)cm, 0u));
-      if (((cm >> lane) & 1ull) && pos < nslots)  // pos < nslots always holds
-        slots[pos] = (u64)key | ((u64)(rel0 + j) << 32);
-      base += (uint32_t)__popcll(cm);
-    }
-  }
-}
-
-// The gather from a tile's speculative list (n <= 64 kNC entries: Delta's
-// bits | index in the tile << 32, index order), if the list's bound lies at
-// or below b1 (then every element with a key >= lo is in it): the count of
-// the elements above b1 (per lane, to be added) and the elements of b1 to the
-// candidate slots in index order; returns false, having written nothing,
-// otherwise.  The list loads are issued before the selection state is waited
-// for.  The selection words are left to the emit, which reads the list too.
-template <int kNC>
-__device__ __forceinline__ bool gather_list(const u64* __restrict__ ent, uint32_t n,
-                                            const TkSel* st, const TensorInfo* ten,
-                                            const uint32_t* co, int64_t row_cand, int64_t start,
-                                            int count, const TkDev& tk, uint32_t& ndef) {
-  const int lane = lane_id();
-  u64 e[kNC > 0 ? kNC : 1];
-#pragma unroll
-  for (int c = 0; c < kNC; ++c) {
-    const uint32_t i = (uint32_t)(c * kWave + lane);
-    e[c] = ent[i < n ? i : 0u];
-  }
-  const uint32_t b1 = st->bin, win = st->win;
-  // bin b1 holds the keys [lo, up): above it kept for sure, inside it candidates
-  const uint32_t lo = bin_floor(b1, win), up = bin_floor(b1 + 1u, win);
-  if (spec_floor(*st) > lo) return false;
-  const int64_t off = ten->off;
-  const int64_t rel0 = start - off;  // the tile's first element, index in the tensor
-  u64* slots = tk.cand + row_cand + off + *co;
-  uint32_t base = 0;  // candidates in the earlier entries
-#pragma unroll
-  for (int c = 0; c < kNC; ++c) {
-    const bool ok = (uint32_t)(c * kWave + lane) < n;
-    const uint32_t key = (uint32_t)e[c] & 0x7FFFFFFFu, idx = (uint32_t)(e[c] >> 32);
-    const u64 sure = __ballot(ok && key >= up);
-    ndef += lane == 0 ? (uint32_t)__popcll(sure) : 0u;
-    const u64 cm = __ballot(ok && key - lo < up - lo);  // lo <= key < up
-    if (cm != 0ull) {
-      const uint32_t pos = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(cm >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)cm, 0u));
-      // the tile's slots follow the b1 elements of the earlier tiles of the
-      // tensor, so pos < count keeps the store inside the tensor's area
-      if (((cm >> lane) & 1ull) && pos < (uint32_t)count)
-        slots[pos] = (u64)key | ((u64)(rel0 + idx) << 32);
-      base += (uint32_t)__popcll(cm);
-    }
-  }
-  return true;
-}
-
-// Grid: ceil((p.t1 - p.t0) / 4) * R workgroups; wave w of workgroup b owns
-// tile p.t0 + 4 (b / R) + w of row b % R.  The count of the elements above b1 (kept for
-// sure) and the elements of b1 to the tile's candidate slots as key | (index
-// in the tensor) << 32, in index order: from the tile's speculative list when
-// `spec` is set, the list fits and its bound lies at or below b1 (slot
-// kTkSpecSlot + 1 of the tile histogram then says so to the emit), otherwise
-// from one read of the tile's Delta (all 32 words at once), which also gives
-// the selection words of the elements kept for sure.  At most 64 VGPRs: 8
-// waves per SIMD (the kernel is bound by the latency of its dependent loads).
-// Without lists (kSpec false) every tile takes the Delta read, with its 32
-// loads in flight at once (85 VGPRs: k_tk_gather_full).
-template <bool kSpec>
-__device__ __forceinline__ void gather_tile(const DevLayout& lay, const TkDev& tk,
-                                            const TkPart& p, int R, int row0,
-                                            const float* __restrict__ data,
-                                            uint64_t* __restrict__ sel) {
-  constexpr int spec = kSpec ? 1 : 0;
-  const int r = (int)(blockIdx.x % (unsigned)R);
-  const int64_t ti = p.t0 + (int64_t)(blockIdx.x / (unsigned)R) * kWaves + wave_id();
-  if (ti >= p.t1) return;
-  const int row = row0 + r;
-  uint16_t* th = tile_hist(tk, lay, row, ti);
-  // the list count and the flag slot in one 32-bit word: a scalar load issued
-  // together with the tile's (a 16-bit load would be a vector one, waited for
-  // before anything else)
-  const uint32_t sp = spec ? *reinterpret_cast<const uint32_t*>(th + kTkSpecSlot) : kTkSpecNone;
-  const Tile tile = lay.tiles[ti];
-  const uint32_t n_spec = sp & 0xFFFFu;
-  const TkSel* st = tk.sel + (int64_t)row * lay.L + tile.l;
-  const TensorInfo* ten = lay.tensors + tile.l;
-  const uint32_t* co = tk.cand_off + (int64_t)row * lay.n_tiles + ti;
-  const int64_t row_cand = (int64_t)row * lay.d_pad;
-  const int lane = lane_id();
-  uint32_t ndef = 0;  // kept for sure (lane 0 holds the list path's count)
-  bool listed = false;
-  if (n_spec != kTkSpecNone) {
-    static_assert(kTkSpecCap == 8 * kWave, "lists of up to 8 loads per lane");
-    const u64* ent = tk.spec + ((int64_t)row * lay.n_tiles + ti) * kTkSpecCap;
-#define SAEF_GL(NC) \
-  listed = gather_list<NC>(ent, n_spec, st, ten, co, row_cand, tile.start, tile.count, tk, ndef)
-    switch ((n_spec + kWave - 1) / kWave) {
-      case 0: SAEF_GL(0); break;
-      case 1: SAEF_GL(1); break;
-      case 2: SAEF_GL(2); break;
-      case 3: SAEF_GL(3); break;
-      case 4: SAEF_GL(4); break;
-      case 5: SAEF_GL(5); break;
-      case 6: SAEF_GL(6); break;
-      case 7: SAEF_GL(7); break;
-      default: SAEF_GL(8); break;
-    }
-#undef SAEF_GL
-  }
-  if (!listed) {
-    const uint32_t b1 = st->bin, win = st->win;
-    const uint32_t lo = bin_floor(b1, win), up = bin_floor(b1 + 1u, win);
-    const int64_t rel0 = tile.start - ten->off;
-    u64* slots = tk.cand + row_cand + ten->off + *co;
-    const uint32_t nslots = th[b1];  // elements of b1 in the tile
-    const float* dr = data + (int64_t)r * lay.d_pad + tile.start;
-    float v[kTileWords];
-#pragma unroll
-    for (int u = 0; u < kTileWords; ++u) {
-      const int j = u * 64 + lane;
-      v[u] = ld_nt_or0(dr, j, j < tile.count);
-    }
-    u64 myw = 0;        // lane u < nw: selection word u
-    uint32_t base = 0;  // candidates in the earlier words
-    if (tile.count == kTkTileElems)
-      gather_words<true>(v, tile.count, lo, up, rel0, nslots, slots, myw, base);
-    else
-      gather_words<false>(v, tile.count, lo, up, rel0, nslots, slots, myw, base);
-    const int nw = (tile.count + 63) >> 6;
-    uint64_t* sr = sel + (int64_t)r * (lay.d_pad >> 6) + (tile.start >> 6);
-    if (lane < nw) sr[lane] = myw;
-    ndef = (uint32_t)__popcll(myw);
-  }
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) ndef += __shfl_xor(ndef, off);
-  if (lane == 0) {
-    tk.tile_cnt[(int64_t)row * lay.n_tiles + ti] = ndef;  // kept for sure
-    if (spec) th[kTkSpecSlot + 1] = listed ? 1 : 0;
-  }
-}
-
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8)))
-void k_tk_gather_spec(DevLayout lay, TkDev tk, TkPart p, int R, int row0,
-                      const float* __restrict__ data, uint64_t* __restrict__ sel) {
-  gather_tile<true>(lay, tk, p, R, row0, data, sel);
-}
-
-__global__ __launch_bounds__(kBlock)
-void k_tk_gather_full(DevLayout lay, TkDev tk, TkPart p, int R, int row0,
-                      const float* __restrict__ data, uint64_t* __restrict__ sel) {
-  gather_tile<false>(lay, tk, p, R, row0, data, sel);
-}
-
-// ------------------------------------------------------------------ select
-// One radix pass over the candidates: histogram (LDS) of digit(e) of those
-// with match(e).  Each thread has kIlp candidate loads in flight.
-template <typename Match, typename Dig>
-__device__ void cand_hist(uint32_t* h, int nb, const u64* __restrict__ cand, int64_t C,
-                          Match match, Dig digit) {
-  constexpr int kIlp = 8;
-  for (int i = threadIdx.x; i < nb; i += blockDim.x) h[i] = 0;
-  __syncthreads();
-  const int64_t nt = blockDim.x;
-  for (int64_t i0 = threadIdx.x; i0 < C; i0 += nt * kIlp) {
-    u64 e[kIlp];
-#pragma unroll
-    for (int u = 0; u < kIlp; ++u) {
-      const int64_t i = i0 + u * nt;
-      e[u] = cand[i < C ? i : 0];  // C > 0 here
-    }
-#pragma unroll
-    for (int u = 0; u < kIlp; ++u)
-      if (i0 + u * nt < C && match(e[u])) atomicAdd(&h[digit(e[u])], 1u);
-  }
-  __syncthreads();
-}
-
-// Grid: R * nl workgroups of kBig threads (as k_tk_pick).  Among the candidates of (row,
-// tensor) (the elements of bin b1), takes the `need` largest keys, equal
-// keys by lower index: radix passes of up to 11 bits over the key bits that
-// b1 leaves open (bits 16..0 inside the window, 22..0 for a one-binade bin,
-// all 31 for the lowest bin and the one above) give the threshold key tau and how many of the elements
-// equal to tau are kept; if not all, passes on the index in the tensor
-// (bits 27..17, 16..6, 5..0) give the last kept index iota.  The next
-// call's window is placed around tau.  Then each tile's kept count and first
-// rank (tile_ranks).
-__device__ void tile_ranks(const DevLayout& lay, const TkDev& tk, int row, int l, int64_t C,
-                           const TkSel& st, uint32_t* s_cnt, uint32_t* s_scan);
-__global__ __launch_bounds__(kBig) void k_tk_select(DevLayout lay, TkDev tk, TkPart p,
-                                                     int row0) {
-  __shared__ uint32_t h[kTkBins];
-  __shared__ uint32_t s_scan[kBig / kWave];
-  __shared__ uint32_t s_res[3];
-  const int nl = p.l1 - p.l0;
-  const int l = p.l0 + (int)(blockIdx.x % (unsigned)nl);
-  const int r = (int)(blockIdx.x / (unsigned)nl);
-  const int row = row0 + r;
-  TkSel* st = tk.sel + (int64_t)row * lay.L + l;
-  const u64* cand = tk.cand + (int64_t)row * lay.d_pad + lay.tensors[l].off;
-  const int64_t C = st->cand;
-  const uint32_t b1 = st->bin, win = st->win;
-  int64_t need = st->need;
-  uint32_t prefix;  // key >> open of every candidate
-  int open;
-  bin_prefix(b1, win, prefix, open);
-  uint32_t bin = 0, cnt = 0;
-  int64_t left = need;
-  while (open > 0) {
-    const int d = open > 11 ? 11 : open;
-    const int sh = open - d;
-    const uint32_t mask = (1u << d) - 1u;
-    cand_hist(h, 1 << d, cand, C, [prefix, open](u64 e) { return ((uint32_t)e >> open) == prefix; },
-              [sh, mask](u64 e) { return ((uint32_t)e >> sh) & mask; });
-    find_bin<true>(h, 1 << d, need, s_scan, s_res, bin, left, cnt);
-    prefix = (prefix << d) | bin;
-    open = sh;
-    need = left;
-  }
-  const uint32_t tau = prefix;
-  int64_t iota = INT64_MAX;  // every element equal to tau is kept
-  if (left < (int64_t)cnt) {
-    // the left-th smallest index among the elements equal to tau
-    need = left;
-    cand_hist(h, kTkBins, cand, C, [tau](u64 e) { return (uint32_t)e == tau; },
-              [](u64 e) { return (uint32_t)(e >> 49) & 2047u; });
-    find_bin<false>(h, kTkBins, need, s_scan, s_res, bin, left, cnt);
-    const uint32_t q1 = bin;
-    need = left;
-    cand_hist(h, kTkBins, cand, C,
-              [tau, q1](u64 e) { return (uint32_t)e == tau && (uint32_t)(e >> 49) == q1; },
-              [](u64 e) { return (uint32_t)(e >> 38) & 2047u; });
-    find_bin<false>(h, kTkBins, need, s_scan, s_res, bin, left, cnt);
-    const uint32_t q2 = (q1 << 11) | bin;
-    need = left;
-    cand_hist(h, 64, cand, C,
-              [tau, q2](u64 e) { return (uint32_t)e == tau && (uint32_t)(e >> 38) == q2; },
-              [](u64 e) { return (uint32_t)(e >> 32) & 63u; });
-    find_bin<false>(h, 64, need, s_scan, s_res, bin, left, cnt);
-    iota = ((int64_t)q2 << 6) | bin;
-  }
-  if (threadIdx.x == 0) {
-    st->tau = tau;
-    st->iota = iota;
-    st->win = window_for(tau);
-  }
-  // every thread holds tau and iota; h (free once the last find_bin is done)
-  // holds the per-tile counts
-  static_assert(kTkBins >= kBig, "a count per thread of the workgroup");
-  __syncthreads();
-  TkSel kept{};
-  kept.tau = tau;
-  kept.iota = iota;
-  tile_ranks(lay, tk, row, l, C, kept, h, s_scan);
-}
-
-// ------------------------------------------------------------------ emit
-// A tile's candidates: slots [first, first + n) of its (row, tensor)'s
-// candidate area (the next tile's first slot, or the candidate total after
-// the tensor's last tile).
-struct TileCands {
-  uint32_t first, n;
-};
-__device__ __forceinline__ TileCands tile_cands(const DevLayout& lay, const TkDev& tk, int row,
-                                                int64_t ti, const TensorInfo& ten, int64_t C) {
-  const uint32_t* co = tk.cand_off + (int64_t)row * lay.n_tiles;
-  const uint32_t first = co[ti];
-  const uint32_t end = ti + 1 < ten.first_tile + ten.ntiles ? co[ti + 1] : (uint32_t)C;
-  return TileCands{first, end - first};
-}
-
-__device__ __forceinline__ bool cand_kept(u64 e, const TkSel& st) {
-  const uint32_t key = (uint32_t)e;
-  const int64_t idx = (int64_t)(e >> 32);
-  return key > st.tau || (key == st.tau && idx <= st.iota);
-}
-
-// Each tile's kept count (the gather's count of definite elements plus its
-// kept candidates), then the exclusive prefix over the tensor's tiles in
-// tile order, in place, for (row, tensor l) with threshold st.tau / st.iota
-// and C candidates.  The candidates of a block of blockDim tiles are
-// contiguous: the whole workgroup reads them and counts the kept ones per
-// tile in s_cnt (blockDim entries of LDS).
-__device__ void tile_ranks(const DevLayout& lay, const TkDev& tk, int row, int l, int64_t C,
-                           const TkSel& st, uint32_t* s_cnt, uint32_t* s_scan) {
-  constexpr int kIlp = 4;
-  const int nt = (int)blockDim.x;
-  const TensorInfo ten = lay.tensors[l];
-  const u64* cand = tk.cand + (int64_t)row * lay.d_pad + ten.off;
-  const uint32_t* co = tk.cand_off + (int64_t)row * lay.n_tiles + ten.first_tile;
-  uint32_t* cnt = tk.tile_cnt + (int64_t)row * lay.n_tiles + ten.first_tile;
-  uint32_t carry = 0;
-  for (int b = 0; b < ten.ntiles; b += nt) {
-    s_cnt[threadIdx.x] = 0;
-    __syncthreads();
-    const uint32_t lo = co[b];
-    const uint32_t hi = b + nt < ten.ntiles ? co[b + nt] : (uint32_t)C;
-    for (uint32_t c0 = lo + threadIdx.x; c0 < hi; c0 += (uint32_t)(nt * kIlp)) {
-      u64 e[kIlp];
-#pragma unroll
-      for (int u = 0; u < kIlp; ++u) {
-        const uint32_t c = c0 + (uint32_t)(u * nt);
-        e[u] = cand[c < hi ? c : lo];  // lo < hi here
-      }
-#pragma unroll
-      for (int u = 0; u < kIlp; ++u) {
-        const int64_t t = (int64_t)(e[u] >> 32) / kTkTileElems - b;  // tile of the block
-        if (c0 + (uint32_t)(u * nt) < hi && cand_kept(e[u], st) && t >= 0 && t < nt)
-          atomicAdd(&s_cnt[t], 1u);
-      }
-    }
-    __syncthreads();
-    const int i = b + threadIdx.x;
-    const uint32_t v = i < ten.ntiles ? cnt[i] + s_cnt[threadIdx.x] : 0u;
-    uint32_t all;
-    const uint32_t before = block_excl_scan(v, s_scan, &all);  // ends with a barrier
-    if (i < ten.ntiles) cnt[i] = carry + before;
-    carry += all;
-  }
+  for (int u = 0; u < kTileWords; ++u)
+    v[u] = buf_ld(r, (uint32_t)(u * kWave + lane_id()) * 4u);
 }
 
 // The position of the r-th set bit of w (r counted from 0, r < popcount(w)):
@@ -822,14 +476,813 @@ __device__ __forceinline__ int nth_set_bit(u64 w, uint32_t r) {
   return pos;
 }
 
-// The emit of a tile that the gather took from its speculative list (n <=
-// 64 kNC entries, index order, every kept element among them): an entry is
-// kept iff its key is above tau, or equal to it with an index up to iota;
-// its value (from the entry) goes to the message at the tile's first rank
-// plus the kept entries before it, the error there is set to 0, and the
-// selection words (assembled in LDS) and rank words are written.
+// Where a wave's candidates go: the LDS buffer lds (in_lds), else glb; both
+// filled through the LDS count *fill.
+struct CandSink {
+  uint32_t* fill;
+  u64* lds;
+  u64* glb;
+  uint32_t cap_lds, cap_glb;
+  bool in_lds;
+
+  // Space for `total` candidates of the wave (wave-uniform): the first's place.
+  __device__ __forceinline__ uint32_t take(uint32_t total) const {
+    uint32_t base = 0;
+    if (lane_id() == 0) base = atomicAdd(fill, total);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+  }
+  // The lanes of mask m put theirs from place `base` on.
+  __device__ __forceinline__ void put(u64 m, uint32_t base, uint32_t key, int64_t idx) const {
+    const uint32_t pos =
+        base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    if (((m >> lane_id()) & 1ull) == 0ull) return;
+    if (in_lds) {
+      if (pos < cap_lds) lds[pos] = cand_of(key, idx);  // always holds
+    } else if (pos < cap_glb) {                         // always holds
+      glb[pos] = cand_of(key, idx);
+    }
+  }
+};
+
+// Of a tile: elements with a key at or above up, and those in [lo, up).
+struct TileCounts {
+  uint32_t sure, cand;
+};
+
+// kT tiles (from tile t0 of the tensor on, those below tend) by one wave:
+// the elements in [lo, up) go to the sink; returns in lane j the counts of
+// tile t0 + j.  n: lane j holds the tile's list count (kTkSpecNone: no usable
+// list; 0 past tend).  Taken from the lists (kC chunks of 64 entries of the
+// kT tiles in flight together), else from Delta (kW words' loads in flight).
+template <int kT, int kC, int kW>
+__device__ __forceinline__ TileCounts scan_tiles(const CandSink& sink, const DevLayout& lay,
+                                                 const TkDev& tk, const TensorInfo& ten, int row,
+                                                 int t0, uint32_t n,
+                                                 const float* __restrict__ dr, uint32_t lo,
+                                                 uint32_t up) {
+  static_assert(kTileWords % kW == 0, "whole passes over a tile");
+  const int lane = lane_id();
+  const int64_t tile0 = (int64_t)row * lay.n_tiles + ten.first_tile + t0;
+  const u64 none = __ballot(n == kTkSpecNone);
+  uint32_t most = n == kTkSpecNone ? 0u : n;
+#pragma unroll
+  for (int off = 1; off < kT; off <<= 1) most = max(most, (uint32_t)__shfl_xor((int)most, off));
+  most = (uint32_t)__builtin_amdgcn_readfirstlane((int)most);
+  uint32_t sure = 0, within = 0;
+  const u64* ent = tk.spec + tile0 * kTkSpecCap;
+  for (uint32_t c0 = 0; c0 < most; c0 += kC * kWave) {
+    u64 e[kT][kC], m[kT][kC];
+#pragma unroll
+    for (int j = 0; j < kT; ++j) {
+      const uint32_t nj = (uint32_t)__builtin_amdgcn_readlane((int)n, j);
+#pragma unroll
+      for (int c = 0; c < kC; ++c) {
+        const uint32_t i = c0 + (uint32_t)(c * kWave + lane);
+        // (past the list's end, or without a list, the first tile's first
+        // entry: it exists)
+        e[j][c] = ent[nj != kTkSpecNone && i < nj ? (uint32_t)j * kTkSpecCap + i : 0u];
+      }
+    }
+    uint32_t total = 0;
+#pragma unroll
+    for (int j = 0; j < kT; ++j) {
+      const uint32_t nj = (uint32_t)__builtin_amdgcn_readlane((int)n, j);
+      uint32_t above = 0;
+      const uint32_t before = total;
+#pragma unroll
+      for (int c = 0; c < kC; ++c) {
+        const bool ok = nj != kTkSpecNone && c0 + (uint32_t)(c * kWave + lane) < nj;
+        const uint32_t key = (uint32_t)e[j][c] & 0x7FFFFFFFu;
+        above += (uint32_t)__popcll(__ballot(ok && key >= up));
+        m[j][c] = __ballot(ok && key >= lo && key < up);
+        total += (uint32_t)__popcll(m[j][c]);
+      }
+      sure += lane == j ? above : 0u;
+      within += lane == j ? total - before : 0u;
+    }
+    if (total == 0u) continue;  // wave-uniform
+    uint32_t base = sink.take(total);
+#pragma unroll
+    for (int j = 0; j < kT; ++j)
+#pragma unroll
+      for (int c = 0; c < kC; ++c) {
+        if (m[j][c] == 0ull) continue;  // wave-uniform
+        sink.put(m[j][c], base, (uint32_t)e[j][c] & 0x7FFFFFFFu,
+                 (int64_t)(t0 + j) * kTkTileElems + (int64_t)(e[j][c] >> 32));
+        base += (uint32_t)__popcll(m[j][c]);
+      }
+  }
+  for (u64 todo = none; todo != 0ull; todo &= todo - 1ull) {  // wave-uniform
+    const int j = __builtin_ctzll(todo);
+    const int64_t first = (int64_t)(t0 + j) * kTkTileElems;
+    const int count = (int)min((int64_t)kTkTileElems, ten.n - first);
+    const Buf rd = buf_of(dr + ten.off + first, (uint32_t)count * 4u);
+    uint32_t above = 0, inside = 0;
+    for (int w = 0; w < kTileWords; w += kW) {
+      float v[kW];
+#pragma unroll
+      for (int u = 0; u < kW; ++u) v[u] = buf_ld(rd, (uint32_t)((w + u) * kWave + lane) * 4u);
+      uint32_t total = 0;
+#pragma unroll
+      for (int u = 0; u < kW; ++u) {
+        const bool ok = (w + u) * kWave + lane < count;
+        const uint32_t key = key_of(v[u]);
+        above += (uint32_t)__popcll(__ballot(ok && key >= up));
+        total += (uint32_t)__popcll(__ballot(ok && key >= lo && key < up));
+      }
+      if (total == 0u) continue;  // wave-uniform
+      inside += total;
+      uint32_t base = sink.take(total);
+#pragma unroll
+      for (int u = 0; u < kW; ++u) {
+        const uint32_t key = key_of(v[u]);
+        const u64 m = __ballot((w + u) * kWave + lane < count && key >= lo && key < up);
+        sink.put(m, base, key, first + (w + u) * kWave + lane);
+        base += (uint32_t)__popcll(m);
+      }
+    }
+    sure += lane == j ? above : 0u;
+    within += lane == j ? inside : 0u;
+  }
+  return TileCounts{sure, within};
+}
+
+// The candidates of a (row, tensor): n of them at p (LDS, or slots), or, when
+// segs is not null, in nseg segments of `stride` slots each, segs[i] of them at
+// p + i stride.
+struct Cands {
+  const u64* p;
+  int64_t n;
+  const uint32_t* segs;
+  int nseg;
+  uint32_t stride;
+
+  // f(candidate, whether there is one) over all of them by the workgroup, in
+  // wave-uniform flow.
+  template <typename F>
+  __device__ __forceinline__ void each(F f) const {
+    if (segs == nullptr) {
+      constexpr int kIlp = 4;
+      const int64_t nt = blockDim.x;
+      for (int64_t b0 = wave_id() * kWave; b0 < n; b0 += nt * kIlp) {
+        const int64_t i0 = b0 + lane_id();
+        u64 e[kIlp];
+#pragma unroll
+        for (int u = 0; u < kIlp; ++u) e[u] = p[i0 + u * nt < n ? i0 + u * nt : 0];
+#pragma unroll
+        for (int u = 0; u < kIlp; ++u)
+          if (b0 + u * nt < n) f(e[u], i0 + u * nt < n);
+      }
+      return;
+    }
+    const int nw = (int)blockDim.x / kWave;
+    constexpr int kS = 8;  // segments a wave has in flight
+    for (int s0 = wave_id() * kS; s0 < nseg; s0 += nw * kS) {
+      uint32_t c[kS], most = 0;
+#pragma unroll
+      for (int q = 0; q < kS; ++q) {
+        c[q] = s0 + q < nseg ? segs[s0 + q] : 0u;
+        most = max(most, c[q]);
+      }
+      most = (uint32_t)__builtin_amdgcn_readfirstlane((int)most);
+      for (uint32_t b = 0; b < most; b += kWave) {
+        const uint32_t i = b + (uint32_t)lane_id();
+        u64 e[kS];
+#pragma unroll
+        for (int q = 0; q < kS; ++q)
+          e[q] = p[i < c[q] ? (int64_t)(s0 + q) * stride + i : (int64_t)s0 * stride];
+#pragma unroll
+        for (int q = 0; q < kS; ++q) f(e[q], i < c[q]);
+      }
+    }
+  }
+};
+
+// Counts each ok lane's bin into the LDS histogram h.  The server's errors
+// crowd a few bins (most of them keep last call's residual, and its binade),
+// and one 64-lane LDS atomic into one address is serialized lane by lane: the
+// lanes that share the first lane's bin add their count with one atomic, the
+// others theirs one by one.  At resnet50 K = 8 Top-1% (union gathers) that
+// took the iteration from 0.974-0.977 to 0.965-0.968 ms; repeating it for a
+// second bin gave 0.976, a third 0.987-0.990 ms.
+__device__ __forceinline__ void hist_add(uint32_t* h, uint32_t bin, bool ok) {
+  const int lane = lane_id();
+  const u64 todo = __ballot(ok);
+  if (todo == 0ull) return;  // wave-uniform
+  const int lead = __builtin_ctzll(todo);
+  const uint32_t lb = (uint32_t)__builtin_amdgcn_readlane((int)bin, lead);
+  const u64 same = __ballot(bin == lb) & todo;
+  if (lane == lead)
+    atomicAdd(&h[lb], (uint32_t)__popcll(same));
+  else if (((todo & ~same) >> lane) & 1ull)
+    atomicAdd(&h[bin], 1u);
+}
+
+// One radix pass: histogram of digit(e) of the candidates with match(e).
+template <typename Match, typename Dig>
+__device__ __forceinline__ void cand_hist(uint32_t* h, int nb, const Cands& cand, Match match,
+                                          Dig digit) {
+  for (int i = threadIdx.x; i < nb; i += blockDim.x) h[i] = 0;
+  __syncthreads();
+  cand.each([&](u64 e, bool ok) {
+    const bool take = ok && match(e);
+    hist_add(h, take ? digit(e) : 0u, take);
+  });
+  __syncthreads();
+}
+
+// The next digit of `open` bits taken in as few, and as even, digits of at
+// most `most` bits as possible.
+__device__ __forceinline__ int radix_digit(int open, int most) {
+  const int passes = (open + most - 1) / most;
+  return (open + passes - 1) / passes;
+}
+
+// tau and iota of the `need` first of C candidates, all with keys in [lo,
+// up) (need <= C): up to one per thread in LDS (lds) by counting each one's
+// rank (one pass, no histogram), else radix passes of kDig bits over key -
+// lo, and, when only some of the keys equal to tau are kept, over the index.
+// keys: the candidates' key - lo in LDS, in any order, or null (then every
+// pass reads cand).  Every thread of the workgroup calls it and gets the
+// result.  h: 2^kDig bins.
+template <int kDig>
+__device__ __forceinline__ void cand_select(uint32_t* h, uint32_t* scan, uint32_t* res,
+                                            const u64* lds, const uint32_t* keys,
+                                            const Cands& cand, int64_t C,
+                                            int64_t need, uint32_t lo, uint32_t up, uint32_t& tau,
+                                            int64_t& iota) {
+  if (lds != nullptr && C <= (int64_t)blockDim.x) {
+    if (threadIdx.x == 0) {  // defined result even if need exceeded C
+      res[0] = lo;
+      res[1] = 0xFFFFFFFFu;
+    }
+    __syncthreads();
+    if ((int64_t)threadIdx.x < C) {
+      const u64 me = lds[threadIdx.x];
+      // (key, then the lower index first) as one number
+      const u64 mine = (me << 32) | (uint32_t)~(uint32_t)(me >> 32);
+      int before = 0;  // candidates that come first
+#pragma unroll 8
+      for (int j = 0; j < (int)C; ++j) {
+        const u64 e = lds[j];
+        before += ((e << 32) | (uint32_t)~(uint32_t)(e >> 32)) > mine ? 1 : 0;
+      }
+      if (before == (int)need - 1) {
+        res[0] = (uint32_t)me;
+        res[1] = (uint32_t)(me >> 32);
+      }
+    }
+    __syncthreads();
+    tau = res[0];
+    iota = (int64_t)res[1];
+    __syncthreads();
+    return;
+  }
+  uint32_t prefix = 0, bin = 0, cnt = (uint32_t)C;
+  const int bits = range_bits(lo, up);
+  int open = bits;
+  int64_t left = need;
+  while (open > 0) {
+    const int d = radix_digit(open, kDig);
+    const int sh = open - d;
+    const uint32_t mask = (1u << d) - 1u;
+    const bool first = open == bits;
+    const auto match = [=](uint32_t rel) { return first || (rel >> open) == prefix; };
+    if (keys != nullptr) {
+      for (int i = threadIdx.x; i < 1 << d; i += blockDim.x) h[i] = 0;
+      __syncthreads();
+      for (int b = wave_id() * kWave; b < (int)C; b += (int)blockDim.x) {
+        const int i = b + lane_id();
+        const uint32_t rel = keys[min(i, (int)C - 1)];
+        const bool ok = i < (int)C && match(rel);
+        hist_add(h, ok ? (rel >> sh) & mask : 0u, ok);
+      }
+      __syncthreads();
+    } else {
+      cand_hist(h, 1 << d, cand, [=](u64 e) { return match((uint32_t)e - lo); },
+                [=](u64 e) { return (((uint32_t)e - lo) >> sh) & mask; });
+    }
+    find_bin<true>(h, 1 << d, need, scan, res, bin, left, cnt);
+    prefix = (prefix << d) | bin;
+    open = sh;
+    need = left;
+  }
+  tau = lo + prefix;
+  iota = INT64_MAX;  // every element equal to tau is kept
+  if (left < (int64_t)cnt) {
+    // the left-th smallest index (28 bits) among the elements equal to tau
+    const uint32_t key = tau;
+    uint32_t at = 0;
+    open = 28;
+    need = left;
+    while (open > 0) {
+      const int d = radix_digit(open, kDig);
+      const int sh = open - d;
+      const uint32_t mask = (1u << d) - 1u;
+      cand_hist(h, 1 << d, cand,
+                [=](u64 e) {
+                  return (uint32_t)e == key && ((uint32_t)(e >> 32) >> open) == at;
+                },
+                [=](u64 e) { return ((uint32_t)(e >> 32) >> sh) & mask; });
+      find_bin<false>(h, 1 << d, need, scan, res, bin, left, cnt);
+      at = (at << d) | bin;
+      open = sh;
+      need = left;
+    }
+    iota = (int64_t)at;
+  }
+}
+
+__device__ __forceinline__ bool cand_kept(u64 e, uint32_t tau, int64_t iota) {
+  const uint32_t key = (uint32_t)e;
+  return key > tau || (key == tau && (int64_t)(e >> 32) <= iota);
+}
+
+// Adds the kept candidates to the tile counts t in LDS, then writes each
+// tile's first rank (the exclusive prefix of the counts) to cnt.
+__device__ __forceinline__ void tile_ranks(uint32_t* t, uint32_t* scan, const Cands& cand,
+                                           uint32_t tau, int64_t iota, int ntiles,
+                                           uint32_t* __restrict__ cnt) {
+  cand.each([&](u64 e, bool ok) {
+    const uint32_t i = (uint32_t)(e >> 32) / kTkTileElems;
+    if (ok && cand_kept(e, tau, iota) && i < (uint32_t)ntiles) tile_count_add(t, (int)i, 1u);
+  });
+  __syncthreads();
+  uint32_t carry = 0;
+  for (int b = 0; b < ntiles; b += (int)blockDim.x) {
+    const int i = b + (int)threadIdx.x;
+    uint32_t all;
+    const uint32_t v = i < ntiles ? tile_count(t, i) : 0u;
+    const uint32_t before = block_excl_scan(v, scan, &all);  // ends with a barrier
+    if (i < ntiles) cnt[i] = carry + before;
+    carry += all;
+  }
+}
+
+// Grid: R * nl workgroups, nl the part's tensors (workgroup b: tensor
+// p.l0 + b % nl of row row0 + b / nl).  Adds the tile histograms of a small
+// tensor, or a large one's group sums or super-group sums, and finds b1.  A
+// small tensor is then selected here as a whole, from its tiles' lists or
+// Delta (resnet56 Top-5%: one kernel of 13-24 us for six of 44 us); for a
+// large one the candidate range and the number to take are left to refine,
+// gather and select.  256 threads and 5 KB of LDS: two workgroups fit on a CU
+// beside the five of a Delta pass (a select of 1024 threads waited up to 200
+// us for its wave slots, until the pass drained).
+__global__ __launch_bounds__(kPick) void k_tk_pick(DevLayout lay, TkDev tk, TkPart p, int row0,
+                                                   const float* __restrict__ data) {
+  constexpr int kDig = 8;
+  constexpr int kPW = kPick / kWave;
+  __shared__ uint32_t h[kTkHistPad > (1 << kDig) ? kTkHistPad : (1 << kDig)];
+  __shared__ u64 s_cand[kPickCand];
+  __shared__ uint32_t s_t[kTkGroup / 2];
+  __shared__ uint32_t s_scan[kPW];
+  __shared__ uint32_t s_res[3];
+  __shared__ uint32_t s_fill;
+  const int nl = p.l1 - p.l0;
+  const int l = p.l0 + (int)(blockIdx.x % (unsigned)nl);
+  const int r = (int)(blockIdx.x / (unsigned)nl);
+  const int row = row0 + r;
+  const TkTensor t = tk.tens[l];
+  const TensorInfo ten = lay.tensors[l];
+  TkSel* st = tk.sel + (int64_t)row * lay.L + l;
+  const uint32_t win = st->win;
+  const uint32_t floor = spec_floor(*st);
+  const int lane = lane_id(), wave = wave_id();
+  const bool small = t.ngroups == 0;
+  for (int i = threadIdx.x; i < kTkHistPad; i += kPick) h[i] = 0;
+  if (threadIdx.x < kTkGroup / 2) s_t[threadIdx.x] = 0;
+  if (threadIdx.x == 0) s_fill = 0;
+  constexpr int kPer = 8;  // tiles a wave has in flight
+  const int per = (ten.ntiles + kPW - 1) / kPW;  // a wave's tiles: wave per + 0 .. per - 1
+  const int tw0 = wave * per, tend = min(tw0 + per, ten.ntiles);
+  // lane j: list count of the wave's tile j
+  uint32_t lcnt = 0;
+  if (small && tw0 + lane < tend)
+    lcnt = tk.lcnt[(int64_t)row * lay.n_tiles + ten.first_tile + tw0 + lane];
+  if (small) {
+    lds_barrier();
+    for (int t0 = tw0; t0 < tend; t0 += kPer) {
+      uint32_t v[2];
+      const int n = min(kPer, tend - t0);
+      if (n == 1)
+        tile_hist_sum<1>(tk, lay, row, ten.first_tile + t0, n, lane, v);
+      else
+        tile_hist_sum<kPer>(tk, lay, row, ten.first_tile + t0, n, lane, v);
+      tile_hist_add(h, lane, v);
+    }
+  } else {
+    lds_barrier();
+    const bool super = t.nsgroups > 0;
+    const uint32_t* src = super
+        ? tk.sghist + ((int64_t)row * tk.n_sgroups + t.first_sgroup) * kTkHistPad
+        : tk.ghist + ((int64_t)row * tk.n_groups + t.first_group) * kTkHistPad;
+    const int ns = super ? t.nsgroups : t.ngroups;
+    for (int b = threadIdx.x; b < kTkHistPad; b += kPick) {
+      uint32_t cnt = 0;
+#pragma unroll 8
+      for (int i = 0; i < ns; ++i) cnt += src[(int64_t)i * kTkHistPad + b];
+      h[b] = cnt;
+    }
+  }
+  __syncthreads();
+  uint32_t b1, n1;
+  int64_t need;
+  find_bin<true>(h, kTkHist, t.keep, s_scan, s_res, b1, need, n1);
+  const uint32_t lo = bin_floor(b1, win), up = bin_floor(b1 + 1u, win);
+  if (!small) {
+    const bool coarse = tk.refine != 0 && n1 > (uint32_t)kRefineCand;
+    if (coarse) {
+      uint32_t* rh = tk.rhist + ((int64_t)row * tk.n_large + t.large) * (kRefineLevels * kTkBins);
+      for (int i = threadIdx.x; i < kRefineLevels * kTkBins; i += kPick) rh[i] = 0;
+    }
+    if (threadIdx.x == 0) {
+      st->floor = floor;
+      st->coarse = coarse ? 1u : 0u;
+      st->lo = lo;
+      st->up = up;
+      st->need = need;
+    }
+    return;
+  }
+  u64* slots = tk.cand + (int64_t)row * lay.d_pad + ten.off;
+  const bool in_lds = n1 <= (uint32_t)kPickCand;
+  const CandSink sink{&s_fill, s_cand, slots, kPickCand, (uint32_t)ten.n, in_lds};
+  const float* dr = data + (int64_t)r * lay.d_pad;
+  if (floor > lo && lane < tend - tw0) lcnt = kTkSpecNone;  // the lists end above b1
+  for (int t0 = tw0; t0 < tend; t0 += kPer) {
+    const uint32_t n = (uint32_t)__shfl((int)lcnt, (t0 - tw0 + lane) % kWave);
+    const TileCounts tc =
+        scan_tiles<kPer, 1, 8>(sink, lay, tk, ten, row, t0, lane < kPer ? n : 0u, dr, lo, up);
+    if (lane < kPer && t0 + lane < tend) tile_count_add(s_t, t0 + lane, tc.sure);
+  }
+  __syncthreads();  // candidates in LDS or in the slots, and the tile counts
+  const int64_t C = (int64_t)min(s_fill, n1);
+  const Cands cand{in_lds ? s_cand : slots, C, nullptr, 0, 0};
+  uint32_t tau;
+  int64_t iota;
+  cand_select<kDig>(h, s_scan, s_res, in_lds ? s_cand : nullptr, nullptr, cand, C, need, lo, up,
+                    tau, iota);
+  tile_ranks(s_t, s_scan, cand, tau, iota, ten.ntiles,
+             tk.tile_cnt + (int64_t)row * lay.n_tiles + ten.first_tile);
+  if (threadIdx.x == 0) {
+    st->floor = floor;
+    st->tau = tau;
+    st->iota = iota;
+    st->win = window_for(tau);
+  }
+}
+
+// Grid: R * n * kGatherSplit workgroups, n the part's groups: workgroup b
+// takes kGatherTiles tiles of one group of one row.
+struct GatherUnit {
+  TkGroup gr;
+  int row, part;
+  int t0, n;          // first tile in the tensor, tile count (may be <= 0)
+  const float* data;  // the row's Delta
+};
+__device__ __forceinline__ GatherUnit gather_unit(const DevLayout& lay, const TkDev& tk,
+                                                  const TkPart& p, int row0,
+                                                  const float* __restrict__ data) {
+  const unsigned n = (unsigned)(p.g1 - p.g0) * kGatherSplit;
+  const unsigned u = blockIdx.x % n;
+  const int r = (int)(blockIdx.x / n);
+  GatherUnit g;
+  g.gr = tk.groups[p.g0 + (int)(u / kGatherSplit)];
+  g.row = row0 + r;
+  g.part = p.g0 * kGatherSplit + (int)u;
+  const int first = (int)(u % kGatherSplit) * kGatherTiles;
+  g.t0 = g.gr.first + first - lay.tensors[g.gr.l].first_tile;
+  g.n = min(kGatherTiles, g.gr.n - first);
+  g.data = data + (int64_t)r * lay.d_pad;
+  return g;
+}
+
+// The candidate range of a large (row, tensor) and how many to take from it:
+// the pick's, narrowed by the first kLevels of the refine's histograms when
+// coarse (h: kTkBins entries of LDS).  Every thread of the workgroup calls it.
+template <int kLevels>
+__device__ __forceinline__ void cand_range(const TkDev& tk, const TkSel& st, int row, int large,
+                                           uint32_t* h, uint32_t* scan, uint32_t* res,
+                                           uint32_t& lo, uint32_t& up, int64_t& need) {
+  lo = st.lo;
+  up = st.up;
+  need = st.need;
+  if (st.coarse == 0u) return;  // workgroup-uniform
+  const uint32_t* rh =
+      tk.rhist + ((int64_t)row * tk.n_large + large) * (kRefineLevels * kTkBins);
+#pragma unroll
+  for (int v = 0; v < kLevels; ++v) {
+    if (range_bits(lo, up) == 0) return;  // one key (workgroup-uniform)
+    for (int i = threadIdx.x; i < kTkBins; i += blockDim.x) h[i] = rh[v * kTkBins + i];
+    const int sh = max(range_bits(lo, up) - 11, 0);
+    __syncthreads();
+    uint32_t bin, cnt;
+    const int64_t want = need;
+    find_bin<true>(h, kTkBins, want, scan, res, bin, need, cnt);
+    up = min(up, lo + ((bin + 1u) << sh));
+    lo = lo + (bin << sh);
+  }
+}
+
+// Counts, for the (row, tensor)s whose candidate bin is full, 11 bits of key -
+// lo (level 0: the top 11 of the bin's; level 1: the next 11) over the
+// candidates of their tiles (from the lists where they reach down to lo, else
+// from Delta) in LDS, then adds the bins to rhist; the gather takes the
+// sub-range that holds the threshold, mostly one key.  One workgroup's radix
+// passes over all the candidates of such a bin (a wide one, or one where
+// many values are equal) took up to 3 ms at bert_base Top-1% (K = 16), whose
+// outliers all have one magnitude.  Launched for plans with a tensor of more
+// than 4096 tiles.
+template <int kLevel>
+__global__ __launch_bounds__(kBlock) void k_tk_refine(DevLayout lay, TkDev tk, TkPart p, int row0,
+                                                      const float* __restrict__ data) {
+  __shared__ uint32_t h[kTkBins];
+  __shared__ uint32_t s_scan[kWaves];
+  __shared__ uint32_t s_res[3];
+  const GatherUnit g = gather_unit(lay, tk, p, row0, data);
+  const TkSel& st = tk.sel[(int64_t)g.row * lay.L + g.gr.l];
+  if (st.coarse == 0u || g.n <= 0) return;  // workgroup-uniform
+  const int large = tk.tens[g.gr.l].large;
+  const uint32_t floor = st.floor;
+  uint32_t lo, up;
+  int64_t need;
+  cand_range<kLevel>(tk, st, g.row, large, h, s_scan, s_res, lo, up, need);
+  if (range_bits(lo, up) == 0) return;  // one key already (workgroup-uniform)
+  const int sh = max(range_bits(lo, up) - 11, 0);
+  for (int i = threadIdx.x; i < kTkBins; i += kBlock) h[i] = 0;
+  lds_barrier();
+  const int lane = lane_id();
+  const TensorInfo ten = lay.tensors[g.gr.l];
+  for (int j = wave_id(); j < g.n; j += kWaves) {
+    const int64_t ti = (int64_t)g.row * lay.n_tiles + ten.first_tile + g.t0 + j;
+    const uint32_t n = floor <= lo ? tk.lcnt[ti] : kTkSpecNone;
+    if (n != kTkSpecNone) {
+      const u64* ent = tk.spec + ti * kTkSpecCap;
+      for (uint32_t i0 = 0; i0 < n; i0 += kWave) {
+        const uint32_t i = i0 + (uint32_t)lane;
+        const uint32_t key = (uint32_t)ent[i < n ? i : 0u] & 0x7FFFFFFFu;
+        const bool ok = i < n && key >= lo && key < up;
+        hist_add(h, ok ? (key - lo) >> sh : 0u, ok);
+      }
+      continue;
+    }
+    const int64_t first = (int64_t)(g.t0 + j) * kTkTileElems;
+    const int count = (int)min((int64_t)kTkTileElems, ten.n - first);
+    float v[kTileWords];
+    load_tile(g.data + ten.off + first, count, v);
+#pragma unroll
+    for (int u = 0; u < kTileWords; ++u) {
+      const uint32_t key = key_of(v[u]);
+      const bool ok = u * kWave + lane < count && key >= lo && key < up;
+      hist_add(h, ok ? (key - lo) >> sh : 0u, ok);
+    }
+  }
+  lds_barrier();
+  uint32_t* rh = tk.rhist +
+                 ((int64_t)g.row * tk.n_large + large) * (kRefineLevels * kTkBins) +
+                 kLevel * kTkBins;
+  for (int i = threadIdx.x; i < kTkBins; i += kBlock)
+    if (h[i] != 0u) atomicAdd(&rh[i], h[i]);
+}
+
+// Grid: as k_tk_refine.  Each tile's count of elements with a key at or above
+// up to tile_cnt, and the elements in [lo, up) to the workgroup's segment of
+// the (row, tensor)'s slots (kGatherTiles tiles' slots: they fit), their
+// number to seg.  From the lists where they reach down to lo, else from Delta.
+template <int kC>
+__global__ __launch_bounds__(kBlock) void k_tk_gather(DevLayout lay, TkDev tk, TkPart p, int row0,
+                                                      const float* __restrict__ data) {
+  __shared__ uint32_t h[kTkBins];
+  __shared__ uint32_t s_scan[kWaves];
+  __shared__ uint32_t s_res[3];
+  __shared__ uint32_t s_fill;
+  const GatherUnit g = gather_unit(lay, tk, p, row0, data);
+  const TensorInfo ten = lay.tensors[g.gr.l];
+  uint32_t lo, up;
+  int64_t need;
+  const TkSel& st = tk.sel[(int64_t)g.row * lay.L + g.gr.l];
+  const uint32_t floor = st.floor;
+  constexpr int kPer = kGatherTiles / kWaves;  // tiles per wave
+  const int t0 = g.t0 + wave_id() * kPer, tend = g.t0 + g.n;
+  uint32_t lcnt = 0;
+  if (lane_id() < kPer && t0 + lane_id() < tend)
+    lcnt = tk.lcnt[(int64_t)g.row * lay.n_tiles + ten.first_tile + t0 + lane_id()];
+  if (threadIdx.x == 0) s_fill = 0;
+  cand_range<kRefineLevels>(tk, st, g.row, tk.tens[g.gr.l].large, h, s_scan, s_res, lo, up, need);
+  lds_barrier();
+  u64* slots = tk.cand + (int64_t)g.row * lay.d_pad + ten.off + (int64_t)g.t0 * kTkTileElems;
+  const CandSink sink{&s_fill, nullptr, slots, 0, (uint32_t)kGatherTiles * kTkTileElems, false};
+  if (t0 < tend) {
+    const int lane = lane_id();
+    if (floor > lo && lane < min(kPer, tend - t0)) lcnt = kTkSpecNone;  // they end above lo
+    const TileCounts tc =
+        scan_tiles<kPer, kC, 16>(sink, lay, tk, ten, g.row, t0, lcnt, g.data, lo, up);
+    if (lane < kPer && t0 + lane < tend) {
+      const int64_t ti = (int64_t)g.row * lay.n_tiles + ten.first_tile + t0 + lane;
+      tk.tile_cnt[ti] = tc.sure;
+      if (tk.refine != 0) tk.tile_cand[ti] = tc.cand;
+    }
+  }
+  lds_barrier();
+  if (threadIdx.x == 0)
+    tk.seg[(int64_t)g.row * tk.n_groups * kGatherSplit + g.part] = s_fill;
+}
+
+// The exclusive prefix over the tensor's tiles, in tile order, of f(tile),
+// given to put(tile, first, value); eight consecutive tiles per thread.
+// Every thread of the workgroup calls it.
+template <typename F, typename P>
+__device__ __forceinline__ void tile_prefix(int ntiles, uint32_t* scan, F f, P put) {
+  constexpr int kQ = 8;
+  uint32_t carry = 0;
+  for (int b = 0; b < ntiles; b += (int)blockDim.x * kQ) {
+    const int i0 = b + (int)threadIdx.x * kQ;
+    uint32_t v[kQ], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      v[q] = i0 + q < ntiles ? f(i0 + q) : 0u;
+      sum += v[q];
+    }
+    uint32_t all;
+    uint32_t at = carry + block_excl_scan(sum, scan, &all);  // ends with a barrier
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      if (i0 + q < ntiles) put(i0 + q, at, v[q]);
+      at += v[q];
+    }
+    carry += all;
+  }
+}
+
+// Grid: R * (p.b1 - p.b0) workgroups: large tensor p.b0 + b % n of row row0
+// + b / n.  Its threshold and tile ranks from the gathered candidates and
+// counts.  When the refine left one key, the candidates are equal and the
+// first `need` of them by index are kept: the tile counts give the tile where
+// they end, and only that tile's candidates are looked at.  Else up to
+// kSelTiles tiles are counted in LDS; beyond, in tile_cnt itself with device
+// atomics (read back past the L1).
+__global__ __launch_bounds__(kSelect) void k_tk_select(DevLayout lay, TkDev tk, TkPart p,
+                                                       int row0) {
+  constexpr int kSW = kSelect / kWave;
+  constexpr int kDig = 10;
+  __shared__ uint32_t s_key[kSelKeys];
+  __shared__ uint32_t h[1 << kDig];
+  __shared__ uint32_t s_t[kSelTiles / 2];
+  static_assert(kSelKeys >= kTkBins, "the range's histogram fits in s_key");
+  __shared__ uint32_t s_scan[kSW];
+  __shared__ uint32_t s_res[3];
+  __shared__ uint32_t s_fill;
+  const int nb = p.b1 - p.b0;
+  const int lg = p.b0 + (int)(blockIdx.x % (unsigned)nb);
+  const int row = row0 + (int)(blockIdx.x / (unsigned)nb);
+  const int l = tk.large[lg];
+  const TensorInfo ten = lay.tensors[l];
+  const TkTensor t = tk.tens[l];
+  TkSel* st = tk.sel + (int64_t)row * lay.L + l;
+  const u64* slots = tk.cand + (int64_t)row * lay.d_pad + ten.off;
+  const int64_t tile0 = (int64_t)row * lay.n_tiles + ten.first_tile;
+  uint32_t* cnt = tk.tile_cnt + tile0;
+  const uint32_t* segs = tk.seg + ((int64_t)row * tk.n_groups + t.first_group) * kGatherSplit;
+  const int nseg = t.ngroups * kGatherSplit;
+  constexpr uint32_t kStride = (uint32_t)kGatherTiles * kTkTileElems;
+  uint32_t lo, up;
+  int64_t need;
+  cand_range<kRefineLevels>(tk, *st, row, lg, s_key, s_scan, s_res, lo, up, need);
+  uint32_t tau;
+  int64_t iota;
+  if (st->coarse != 0u && range_bits(lo, up) == 0) {  // workgroup-uniform
+    const uint32_t* within = tk.tile_cand + tile0;
+    if (threadIdx.x == 0) {
+      s_res[0] = 0;
+      s_res[1] = 0;
+      s_res[2] = kTkTileElems - 1;
+    }
+    if (threadIdx.x < kTkTileElems / 32) h[threadIdx.x] = 0;
+    __syncthreads();
+    tile_prefix(ten.ntiles, s_scan, [=](int i) { return within[i]; },
+                [=](int i, uint32_t at, uint32_t v) {
+                  if ((int64_t)at < need && need <= (int64_t)at + v) {
+                    s_res[0] = (uint32_t)i;                 // the tile with the last one kept
+                    s_res[1] = (uint32_t)(need - at);       // how many of it are kept
+                  }
+                });
+    __syncthreads();
+    const int last = (int)s_res[0];
+    const uint32_t take = s_res[1];
+    // the tile's candidates as bits, then the take-th of them
+    const u64* seg = slots + (int64_t)(last / kGatherTiles) * kStride;
+    const uint32_t n = min(segs[last / kGatherTiles], kStride);
+    for (uint32_t i = threadIdx.x; i < n; i += kSelect) {
+      const uint32_t idx = (uint32_t)(seg[i] >> 32);
+      if (idx / kTkTileElems == (uint32_t)last)
+        atomicOr(&h[idx % kTkTileElems / 32], 1u << (idx % 32u));
+    }
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+      const uint32_t w = h[threadIdx.x];
+      const uint32_t c = (uint32_t)__popc(w);
+      uint32_t incl = c;
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off);
+        if (lane_id() >= off) incl += y;
+      }
+      static_assert(kTkTileElems == 32 * kWave, "a lane per word of the tile's bits");
+      if (incl - c < take && take <= incl)
+        s_res[2] = threadIdx.x * 32u + (uint32_t)nth_set_bit((u64)w, take - (incl - c) - 1u);
+    }
+    __syncthreads();
+    tau = lo;
+    iota = (int64_t)last * kTkTileElems + s_res[2];
+    tile_prefix(ten.ntiles, s_scan,
+                [=](int i) { return cnt[i] + (i < last ? within[i] : i == last ? take : 0u); },
+                [=](int i, uint32_t at, uint32_t) { cnt[i] = at; });
+  } else {
+    const bool counted = ten.ntiles <= kSelTiles;
+    if (counted)
+      for (int i = threadIdx.x; 2 * i < ten.ntiles; i += kSelect)
+        s_t[i] = cnt[2 * i] | (2 * i + 1 < ten.ntiles ? cnt[2 * i + 1] << 16 : 0u);
+    if (threadIdx.x == 0) s_fill = 0;
+    // the number of candidates; the keys of up to kSelKeys are brought to LDS
+    uint32_t mine = 0;
+    for (int i = threadIdx.x; i < nseg; i += kSelect) mine += segs[i];
+    uint32_t total;
+    (void)block_excl_scan(mine, s_scan, &total);  // ends with a barrier
+    const bool in_lds = total <= (uint32_t)kSelKeys;
+    const Cands cand{slots, (int64_t)total, segs, nseg, kStride};
+    if (in_lds) {
+      cand.each([&](u64 e, bool ok) {
+        const u64 m = __ballot(ok);
+        if (m == 0ull) return;
+        uint32_t base = 0;
+        if (lane_id() == 0) base = atomicAdd(&s_fill, (uint32_t)__popcll(m));
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        const uint32_t pos =
+            base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (ok && pos < (uint32_t)kSelKeys) s_key[pos] = (uint32_t)e - lo;  // always holds
+      });
+      __syncthreads();
+    }
+    cand_select<kDig>(h, s_scan, s_res, nullptr, in_lds ? s_key : nullptr, cand, (int64_t)total,
+                      need, lo, up, tau, iota);
+    if (counted) {
+      tile_ranks(s_t, s_scan, cand, tau, iota, ten.ntiles, cnt);
+    } else {
+      cand.each([&](u64 e, bool ok) {
+        const uint32_t i = (uint32_t)(e >> 32) / kTkTileElems;
+        if (ok && cand_kept(e, tau, iota) && i < (uint32_t)ten.ntiles) atomicAdd(&cnt[i], 1u);
+      });
+      __threadfence();
+      __syncthreads();
+      tile_prefix(ten.ntiles, s_scan,
+                  [=](int i) {
+                    return __hip_atomic_load(&cnt[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                  },
+                  [=](int i, uint32_t at, uint32_t) { cnt[i] = at; });
+    }
+  }
+  __syncthreads();  // every thread has read st
+  if (threadIdx.x == 0) {
+    st->tau = tau;
+    st->iota = iota;
+    st->win = window_for(tau);
+  }
+}
+
+// ------------------------------------------------------------------ emit
+// A tile's selection words from lane u's word `mine` (u < nw), and its rank
+// words: the tile's first rank and the counts of the words before.  Returns
+// the lane's word's rank in the tile.
+__device__ __forceinline__ uint32_t emit_words(u64 mine, int nw, uint32_t base,
+                                               uint64_t* __restrict__ sr,
+                                               uint32_t* __restrict__ rr) {
+  const int lane = lane_id();
+  const uint32_t cnt = (uint32_t)__popcll(mine);
+  uint32_t incl = cnt;
+#pragma unroll
+  for (int off = 1; off < kTileWords; off <<= 1) {
+    const uint32_t y = __shfl_up(incl, off);
+    if (lane >= off) incl += y;
+  }
+  if (lane < nw) {
+    sr[lane] = mine;
+    rr[lane] = base + incl - cnt;
+  }
+  return incl - cnt;
+}
+
+// The emit of a tile from its speculative list (n <= 64 kNC entries, index
+// order): if the list reaches down to the threshold, an entry is kept iff its
+// key is above tau, or equal to it with an index up to iota; its value (from
+// the entry) goes to the message at the tile's first rank plus the kept
+// entries before it, the error there is set to 0, and the selection words
+// (assembled in LDS) and rank words are written.  Returns false, having
+// written nothing, otherwise.  The list loads are issued before the selection
+// state is waited for.
 template <int kNC, bool kX, bool kPend>
-__device__ __forceinline__ void emit_list(const u64* __restrict__ ent, uint32_t n,
+__device__ __forceinline__ bool emit_list(const u64* __restrict__ ent, uint32_t n,
                                           const TkSel* stp, int64_t rel0, uint32_t base,
                                           uint32_t keep, int count, int nw,
                                           uint64_t* __restrict__ sr, uint32_t* __restrict__ rr,
@@ -844,6 +1297,7 @@ __device__ __forceinline__ void emit_list(const u64* __restrict__ ent, uint32_t 
   }
   const uint32_t tau = stp->tau;
   const int64_t iota = stp->iota;
+  if (stp->floor > tau) return false;
   if (lane < kTileWords) s_w[lane] = 0ull;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -869,36 +1323,24 @@ __device__ __forceinline__ void emit_list(const u64* __restrict__ ent, uint32_t 
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  const u64 mine = lane < nw ? s_w[lane] : 0ull;
-  if (lane < nw) sr[lane] = mine;
-  const uint32_t cnt = (uint32_t)__popcll(mine);
-  uint32_t incl = cnt;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const uint32_t y = __shfl_up(incl, off);
-    if (lane >= off) incl += y;
-  }
-  if (lane < nw) rr[lane] = base + incl - cnt;
+  emit_words(lane < nw ? s_w[lane] : 0ull, nw, base, sr, rr);
+  return true;
 }
 
 // Grid: ceil((p.t1 - p.t0) / 4) * R workgroups; wave w of workgroup b owns
-// tile p.t0 + 4 (b / R) + w of row b % R.  The tile's kept candidates are added to its
-// selection words (LDS), then the rank words, the kept values in index order
-// and the kept elements of data set to 0; kX (server): x <- x - Delta at the
-// kept elements (C(Delta) is zero elsewhere).  Lane j holds selection word j
-// of the tile and a wave scan of the word counts gives every rank word; then
-// lane i takes the tile's kept elements i, i + 64, ...: its word by a binary
-// search over the scan, its bit by nth_set_bit, so the work follows the kept
-// count, not the tile size.
+// tile p.t0 + 4 (b / R) + w of row b % R.  Writes the tile's selection words,
+// rank words and kept values in index order, and sets the kept elements of
+// data to 0 (kPend: left for the next reader); kX (server): x <- x - Delta at
+// the kept elements (C(Delta) is zero elsewhere).  From the tile's list where
+// there is one that reaches down to the threshold, else from Delta (one
+// streaming read, all 32 words in flight at once).
 template <bool kX, bool kPend>
 __global__ __launch_bounds__(kBlock) void k_tk_emit(DevLayout lay, TkDev tk, TkPart p, int R,
-                                                    int row0, int spec,
-                                                    float* __restrict__ data,
+                                                    int row0, float* __restrict__ data,
                                                     uint64_t* __restrict__ sel,
                                                     uint32_t* __restrict__ rank,
                                                     float* __restrict__ vals,
                                                     float* __restrict__ x) {
-  static_assert(kTileWords == 32, "five halving steps find a word of the tile");
   __shared__ u64 words[kWaves][kTileWords];  // one row per wave, used by that wave only
   const int r = (int)(blockIdx.x % (unsigned)R);
   const int64_t ti = p.t0 + (int64_t)(blockIdx.x / (unsigned)R) * kWaves + wave_id();
@@ -906,101 +1348,69 @@ __global__ __launch_bounds__(kBlock) void k_tk_emit(DevLayout lay, TkDev tk, TkP
   const int wave = threadIdx.x / kWave;
   const int lane = lane_id();
   const int row = row0 + r;
-  const int64_t W = lay.d_pad >> 6;
-  // count and flag of the tile's speculative list (read before the tile so
-  // that the two loads overlap)
-  const uint32_t sp =
-      spec ? *reinterpret_cast<const uint32_t*>(tile_hist(tk, lay, row, ti) + kTkSpecSlot) : 0u;
+  const int64_t rt = (int64_t)row * lay.n_tiles + ti;
+  const uint32_t n = tk.lcnt[rt];
+  const uint32_t base = tk.tile_cnt[rt];
   const Tile tile = lay.tiles[ti];
   const int nw = (tile.count + 63) >> 6;
-  uint64_t* sr = sel + (int64_t)r * W + (tile.start >> 6);
-  {
-    // a tile the gather took from its speculative list: emit it from the list
-    if ((sp >> 16) != 0u) {
-      static_assert(kTkSpecSlot % 2 == 0, "count and flag in one 32-bit word");
-      const uint32_t n = sp & 0xFFFFu;
-      const u64* ent = tk.spec + ((int64_t)row * lay.n_tiles + ti) * kTkSpecCap;
-      const uint32_t base = tk.tile_cnt[(int64_t)row * lay.n_tiles + ti];
-      const TkSel* stp = tk.sel + (int64_t)row * lay.L + tile.l;
-      const int64_t rel0 = tile.start - lay.tensors[tile.l].off;
-      const TkTensor* tp = tk.tens + tile.l;
-      uint32_t* rr = rank + (int64_t)r * W + (tile.start >> 6);
-      float* vr = vals + (int64_t)r * tk.total_keep + tp->voff;
-      float* dr = data + (int64_t)r * lay.d_pad + tile.start;
-      const uint32_t keep = (uint32_t)tp->keep;
-      float* xt = kX ? x + tile.start : nullptr;
-#define SAEF_EL(NC)                                                                   \
-  emit_list<NC, kX, kPend>(ent, n, stp, rel0, base, keep, tile.count, nw, sr, rr, vr, dr, xt, \
-                           words[wave])
-      switch ((n + kWave - 1) / kWave) {
-        case 0: SAEF_EL(0); break;
-        case 1: SAEF_EL(1); break;
-        case 2: SAEF_EL(2); break;
-        case 3: SAEF_EL(3); break;
-        case 4: SAEF_EL(4); break;
-        case 5: SAEF_EL(5); break;
-        case 6: SAEF_EL(6); break;
-        case 7: SAEF_EL(7); break;
-        default: SAEF_EL(8); break;
-      }
-#undef SAEF_EL
-      return;
-    }
-  }
-  const TensorInfo ten = lay.tensors[tile.l];
-  const TkSel st = tk.sel[(int64_t)row * lay.L + tile.l];
-  const TkTensor t = tk.tens[tile.l];
-  const TileCands tc = tile_cands(lay, tk, row, ti, ten, st.cand);
-  const uint32_t base = tk.tile_cnt[(int64_t)row * lay.n_tiles + ti];
-  // lane j: word j of the tile (the gather's elements kept for sure)
-  u64 mine = lane < nw ? sr[lane] : 0ull;
-  if (tc.n > 0) {  // wave-uniform: add the kept candidates' bits
-    if (lane < kTileWords) words[wave][lane] = mine;
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    const u64* slots = tk.cand + (int64_t)row * lay.d_pad + ten.off + tc.first;
-    const int64_t rel0 = tile.start - ten.off;
-    for (uint32_t i = lane; i < tc.n; i += kWave) {
-      const u64 e = slots[i];
-      const int64_t q = (int64_t)(e >> 32) - rel0;  // element of the tile
-      if (cand_kept(e, st) && q >= 0 && q < tile.count)
-        atomicOr(&words[wave][q >> 6], 1ull << (q & 63));
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    mine = lane < nw ? words[wave][lane] : 0ull;
-    if (lane < nw) sr[lane] = mine;
-  }
+  const TkSel* stp = tk.sel + (int64_t)row * lay.L + tile.l;
+  const int64_t rel0 = tile.start - lay.tensors[tile.l].off;
+  const TkTensor* tp = tk.tens + tile.l;
+  const int64_t wat = (int64_t)r * (lay.d_pad >> 6) + (tile.start >> 6);
+  uint64_t* sr = sel + wat;
+  uint32_t* rr = rank + wat;
+  float* vr = vals + (int64_t)r * tk.total_keep + tp->voff;
   float* dr = data + (int64_t)r * lay.d_pad + tile.start;
-  uint32_t* rr = rank + (int64_t)r * W + (tile.start >> 6);
-  float* vr = vals + (int64_t)r * tk.total_keep + t.voff;
+  const uint32_t keep = (uint32_t)tp->keep;
   float* xt = kX ? x + tile.start : nullptr;
-  const uint32_t c = (uint32_t)__popcll(mine);
-  uint32_t incl = c;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const uint32_t y = __shfl_up(incl, off);
-    if (lane >= off) incl += y;
+  if (n != kTkSpecNone) {
+    static_assert(kTkSpecCap == 8 * kWave, "lists of up to 8 loads per lane");
+    const u64* ent = tk.spec + rt * kTkSpecCap;
+    bool done;
+#define SAEF_EL(NC)                                                                           \
+  done = emit_list<NC, kX, kPend>(ent, n, stp, rel0, base, keep, tile.count, nw, sr, rr, vr, \
+                                  dr, xt, words[wave])
+    switch ((n + kWave - 1) / kWave) {
+      case 0: SAEF_EL(0); break;
+      case 1: SAEF_EL(1); break;
+      case 2: SAEF_EL(2); break;
+      case 3: SAEF_EL(3); break;
+      case 4: SAEF_EL(4); break;
+      case 5: SAEF_EL(5); break;
+      case 6: SAEF_EL(6); break;
+      case 7: SAEF_EL(7); break;
+      default: SAEF_EL(8); break;
+    }
+#undef SAEF_EL
+    if (done) return;
   }
-  const uint32_t excl = incl - c;
-  if (lane < nw) rr[lane] = base + excl;
-  const uint32_t total = (uint32_t)__shfl(incl, kWave - 1);  // kept in the tile
-  const uint32_t lo = (uint32_t)mine, hi = (uint32_t)(mine >> 32);
-  for (uint32_t i0 = 0; i0 < total; i0 += kWave) {
-    const uint32_t i = i0 + (uint32_t)lane;  // the i-th kept element of the tile
-    // its word: the number of words whose inclusive count is <= i (words past
-    // nw count all of the tile, so the search stays below kTileWords)
-    int u = 0;
+  float v[kTileWords];
+  load_tile(dr, tile.count, v);
+  const uint32_t tau = stp->tau;
+  const int64_t iota = stp->iota;
+  u64 mine = 0;  // lane u: word u
 #pragma unroll
-    for (int step = kTileWords / 2; step >= 1; step >>= 1)
-      if ((uint32_t)__shfl(incl, u + step - 1) <= i) u += step;
-    const uint32_t wlo = (uint32_t)__shfl(lo, u), whi = (uint32_t)__shfl(hi, u);
-    const uint32_t wex = (uint32_t)__shfl(excl, u);
-    const int j = u * 64 + nth_set_bit(((u64)whi << 32) | wlo, i - wex);
-    const uint32_t pos = base + i;
-    if (i < total && j < tile.count && pos < (uint32_t)t.keep) {  // the last two always hold
-      const float v = dr[j];
-      vr[pos] = v;
-      if (!kPend) dr[j] = 0.0f;  // e = Delta - C(Delta) = 0 at a kept element
-      if (kX) xt[j] -= v;
+  for (int u = 0; u < kTileWords; ++u) {
+    const int j = u * kWave + lane;
+    const uint32_t key = key_of(v[u]);
+    const u64 word = __ballot(j < tile.count &&
+                              (key > tau || (key == tau && rel0 + (int64_t)j <= iota)));
+    if (lane == u) mine = word;
+  }
+  const uint32_t excl = emit_words(mine, nw, base, sr, rr);
+#pragma unroll
+  for (int u = 0; u < kTileWords; ++u) {
+    const u64 word = word_of(mine, u);
+    if (word == 0ull) continue;  // wave-uniform
+    const uint32_t pos =
+        base + (uint32_t)__builtin_amdgcn_readlane((int)excl, u) +
+        __builtin_amdgcn_mbcnt_hi((uint32_t)(word >> 32),
+                                  __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0u));
+    const int j = u * kWave + lane;
+    if (((word >> lane) & 1ull) && pos < keep) {  // the last always holds
+      vr[pos] = v[u];
+      if (!kPend) st_nt(dr + j, 0.0f);  // e = Delta - C(Delta) = 0 at a kept element
+      if (kX) xt[j] -= v[u];
     }
   }
 }
@@ -1143,27 +1553,8 @@ __device__ __forceinline__ void union_means(const AggWords& cur, int K, double i
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 }
 
-// Counts each ok lane's bin into the LDS histogram h.  The server's errors
-// crowd a few bins (most of them keep last call's residual, and its binade),
-// and one 64-lane LDS atomic into one address is serialized lane by lane: the
-// lanes that share the first lane's bin add their count with one atomic, the
-// others theirs one by one.  At resnet50 K = 8 Top-1% (union gathers) that
-// took the iteration from 0.974-0.977 to 0.965-0.968 ms; repeating it for a
-// second bin gave 0.976, a third 0.987-0.990 ms.
-__device__ __forceinline__ void agg_hist_add(uint32_t* h, uint32_t bin, bool ok, int lane) {
-  const u64 todo = __ballot(ok);
-  if (todo == 0ull) return;  // wave-uniform
-  const int lead = __builtin_ctzll(todo);
-  const uint32_t lb = (uint32_t)__builtin_amdgcn_readlane((int)bin, lead);
-  const u64 same = __ballot(bin == lb) & todo;
-  if (lane == lead)
-    atomicAdd(&h[lb], (uint32_t)__popcll(same));
-  else if (((todo & ~same) >> lane) & 1ull)
-    atomicAdd(&h[bin], 1u);
-}
-
 template <int kMode, bool kAvg, int U, int kPath>
-__global__ __launch_bounds__(kBig) void k_tk_aggregate(DevLayout lay, TkDev tk, TkPart p,
+__global__ __launch_bounds__(kAgg) void k_tk_aggregate(DevLayout lay, TkDev tk, TkPart p,
                                                        int K, double inv_k,
                                                        const uint64_t* __restrict__ sel,
                                                        const uint32_t* __restrict__ rank,
@@ -1176,9 +1567,9 @@ __global__ __launch_bounds__(kBig) void k_tk_aggregate(DevLayout lay, TkDev tk, 
   static_assert(kTileWords % U == 0, "a pass of U words stays in one tile");
   constexpr int kChunkTiles = kTkChunk / kTkTileElems;
   __shared__ uint32_t h[kMode == 1 ? kChunkTiles * kTkHistPad : 1];  // per tile of the chunk
-  __shared__ float mb[kPath == kTkAggUnion ? (kBig / kWave) * U * kWave : 1];  // a pass's means
-  __shared__ uint4 wt[kPath == kTkAggUnion ? kBig : 1];                 // per wave: its 64 pairs
-  __shared__ uint4 ut[kPath == kTkAggUnion ? (kBig / kWave) * U : 1];   // per wave: union words
+  __shared__ float mb[kPath == kTkAggUnion ? (kAgg / kWave) * U * kWave : 1];  // a pass's means
+  __shared__ uint4 wt[kPath == kTkAggUnion ? kAgg : 1];                 // per wave: its 64 pairs
+  __shared__ uint4 ut[kPath == kTkAggUnion ? (kAgg / kWave) * U : 1];   // per wave: union words
   static_assert(kPath != kTkAggUnion || U * kWave <= (int)(sizeof(mb) / sizeof(float)),
                 "a wave's means");
   const int64_t ci = p.c0 + (int64_t)blockIdx.x;
@@ -1193,7 +1584,7 @@ __global__ __launch_bounds__(kBig) void k_tk_aggregate(DevLayout lay, TkDev tk, 
   const TensorInfo ten = lay.tensors[c.l];
   const int64_t tile0 = ten.first_tile + (c.start - ten.off) / kTkTileElems;
   if (kMode == 1) {
-    for (int i = threadIdx.x; i < kChunkTiles * kTkHistPad; i += kBig) h[i] = 0;
+    for (int i = threadIdx.x; i < kChunkTiles * kTkHistPad; i += kAgg) h[i] = 0;
     __syncthreads();
   }
   const int lane = lane_id();
@@ -1210,7 +1601,7 @@ __global__ __launch_bounds__(kBig) void k_tk_aggregate(DevLayout lay, TkDev tk, 
   // Wave w takes the chunk's tiles w, w + kBW, ... one at a time, U words per
   // pass in word order, so that a tile's passes, and its list, are one
   // wave's.
-  constexpr int kBW = kBig / kWave;
+  constexpr int kBW = kAgg / kWave;
   const auto next_w0 = [](int w) {
     return (w + U) % kTileWords != 0 ? w + U : w + U + (kBW - 1) * kTileWords;
   };
@@ -1372,7 +1763,7 @@ __global__ __launch_bounds__(kBig) void k_tk_aggregate(DevLayout lay, TkDev tk, 
         // (the dense gathers lost with the leader: Top-5% 1.122-1.125 against
         // 1.111 ms, Top-10% 1.257 against 1.247-1.249 ms)
         if (kPath == kTkAggUnion)
-          agg_hist_add(h, hb, ok, lane);
+          hist_add(h, hb, ok);
         else
           atomicAdd(&h[hb], ok ? 1u : 0u);
       } else {
@@ -1383,7 +1774,7 @@ __global__ __launch_bounds__(kBig) void k_tk_aggregate(DevLayout lay, TkDev tk, 
       // the tile's last pass: its list count (none before the first
       // threshold, for a tensor without lists, or past kTkSpecCap entries)
       if (lane == 0)
-        h[tl * kTkHistPad + kTkSpecSlot] =
+        tk.lcnt[(int64_t)lay.k_max * lay.n_tiles + tile0 + tl] =
             lo_spec != 0x80000000u && lc <= (uint32_t)kTkSpecCap ? lc : kTkSpecNone;
       lc = 0;
     }
@@ -1392,10 +1783,9 @@ __global__ __launch_bounds__(kBig) void k_tk_aggregate(DevLayout lay, TkDev tk, 
     if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(lay.status, kStatusRange);
     __syncthreads();
     // the tile histograms of the chunk, 16-bit counts, two bins per store
-    // (the list count in slot kTkSpecSlot, 0 in the flag slot after it)
     const int ntile = (c.count + kTkTileElems - 1) / kTkTileElems;
     uint32_t* out = reinterpret_cast<uint32_t*>(tile_hist(tk, lay, lay.k_max, tile0));
-    for (int i = threadIdx.x; i < ntile * (kTkHistPad / 2); i += kBig)
+    for (int i = threadIdx.x; i < ntile * (kTkHistPad / 2); i += kAgg)
       out[i] = (h[2 * i] & 0xFFFFu) | (h[2 * i + 1] << 16);
   }
 }
@@ -1432,47 +1822,60 @@ struct Launcher {
   }
 
   // everything after the first pass for R rows of `data` (rows row0..) over
-  // the part's tensors: sums, pick, offsets, gather, select (with the tile
-  // ranks), emit.
-  // The last kernel stamps the caller's stop event.
+  // the part's tensors: the selection (pick; for a part with large tensors
+  // the sums before it and gather and select, for the (row, tensor)s that the
+  // pick left to them, after it), then the emit.  The last kernel stamps the
+  // caller's stop event.
   hipError_t select_and_emit(const TkPart& p, int R, int row0, float* data, uint64_t* sel,
                              uint32_t* rank, float* vals, float* x, bool pend_out,
                              const LaunchEvents& last) const {
     const LaunchEvents ev;
     hipError_t err;
+    const bool large = p.g1 > p.g0;
     const dim3 groups((unsigned)((int64_t)R * (p.g1 - p.g0)));
-    SAEF_LAUNCH(k_tk_sum<false>, groups, dim3(kBlock), 0, s, lay, tk, p, row0);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
+    const dim3 quarters((unsigned)((int64_t)R * (p.g1 - p.g0) * kGatherSplit));
+    const dim3 pairs((unsigned)((int64_t)R * (p.l1 - p.l0)));
+    const dim3 tiles((unsigned)((int64_t)(p.t1 - p.t0 + kWaves - 1) / kWaves * R));
+    if (large) {
+      SAEF_LAUNCH(k_tk_sum<false>, groups, dim3(kBlock), 0, s, lay, tk, p, row0);
+      if ((err = hipGetLastError()) != hipSuccess) return err;
+    }
     if (p.s1 > p.s0) {
       SAEF_LAUNCH(k_tk_sum<true>, dim3((unsigned)((int64_t)R * (p.s1 - p.s0))), dim3(kBlock), 0,
                   s, lay, tk, p, row0);
       if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    const dim3 pairs((unsigned)((int64_t)R * (p.l1 - p.l0)));
-    const dim3 tiles((unsigned)((int64_t)(p.t1 - p.t0 + kWaves - 1) / kWaves * R));
-    SAEF_LAUNCH(k_tk_pick, pairs, dim3(kBlock), 0, s, lay, tk, p, row0);
+    SAEF_LAUNCH(k_tk_pick, pairs, dim3(kPick), 0, s, lay, tk, p, row0, data);
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    SAEF_LAUNCH(k_tk_offsets, groups, dim3(kWave), 0, s, lay, tk, p, row0);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    // speculative lists (written by the worker Delta pass, and for the
-    // server row by the aggregation), if some tensor keeps them
-    const int spec = tk.lists != 0 ? 1 : 0;
-    if (spec)
-      SAEF_LAUNCH(k_tk_gather_spec, tiles, dim3(kBlock), 0, s, lay, tk, p, R, row0, data, sel);
-    else
-      SAEF_LAUNCH(k_tk_gather_full, tiles, dim3(kBlock), 0, s, lay, tk, p, R, row0, data, sel);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    SAEF_LAUNCH(k_tk_select, pairs, dim3(kBig), 0, s, lay, tk, p, row0);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
+    if (large) {
+      if (tk.refine != 0) {
+        SAEF_LAUNCH(k_tk_refine<0>, quarters, dim3(kBlock), 0, s, lay, tk, p, row0, data);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+        SAEF_LAUNCH(k_tk_refine<1>, quarters, dim3(kBlock), 0, s, lay, tk, p, row0, data);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+      }
+      // Up to 1.7 times the kept elements are listed: a chunk of 64 entries
+      // holds the list of a tile of a sparse plan (up to 1/64 kept), else two
+      // chunks of each tile are in flight together (Top-10%: 1064 us per
+      // iteration with two, 1067 with four, 1101 against 1093 with one).
+      if (tk.total_keep * 64 <= lay.d_pad)
+        SAEF_LAUNCH(k_tk_gather<1>, quarters, dim3(kBlock), 0, s, lay, tk, p, row0, data);
+      else
+        SAEF_LAUNCH(k_tk_gather<2>, quarters, dim3(kBlock), 0, s, lay, tk, p, row0, data);
+      if ((err = hipGetLastError()) != hipSuccess) return err;
+      SAEF_LAUNCH(k_tk_select, dim3((unsigned)((int64_t)R * (p.b1 - p.b0))), dim3(kSelect), 0, s,
+                  lay, tk, p, row0);
+      if ((err = hipGetLastError()) != hipSuccess) return err;
+    }
     if (x != nullptr)
       hipExtLaunchKernelGGL((k_tk_emit<true, false>), tiles, dim3(kBlock), 0, s, nullptr,
-                            last.stop, 0, lay, tk, p, R, row0, spec, data, sel, rank, vals, x);
+                            last.stop, 0, lay, tk, p, R, row0, data, sel, rank, vals, x);
     else if (pend_out)
       hipExtLaunchKernelGGL((k_tk_emit<false, true>), tiles, dim3(kBlock), 0, s, nullptr,
-                            last.stop, 0, lay, tk, p, R, row0, spec, data, sel, rank, vals, x);
+                            last.stop, 0, lay, tk, p, R, row0, data, sel, rank, vals, x);
     else
       hipExtLaunchKernelGGL((k_tk_emit<false, false>), tiles, dim3(kBlock), 0, s, nullptr,
-                            last.stop, 0, lay, tk, p, R, row0, spec, data, sel, rank, vals, x);
+                            last.stop, 0, lay, tk, p, R, row0, data, sel, rank, vals, x);
     return hipGetLastError();
   }
 
@@ -1495,7 +1898,7 @@ struct Launcher {
     // path (Top-5% 1.12 against 1.11 ms, Top-10% 1.29 against 1.25 ms).
     const bool co = tk.total_keep * 32 >= lay.d_pad;
 #define SAEF_TKA(M, A, U, C)                                                                 \
-  hipExtLaunchKernelGGL((k_tk_aggregate<M, A, U, C>), grid, dim3(kBig), 0, s, ev.start, stop0, \
+  hipExtLaunchKernelGGL((k_tk_aggregate<M, A, U, C>), grid, dim3(kAgg), 0, s, ev.start, stop0, \
                         0, lay, tk, p, K, ik, sel, rank, vals, avg, e_srv, x)
 #define SAEF_TKA_U(M, A)                                                    \
   do {                                                                      \
@@ -1539,9 +1942,8 @@ hipError_t launch_topk_compress(const DevLayout& lay, const TkDev& tk, const TkP
                                 bool pend_out, const TkStep& st, hipStream_t s,
                                 const TkStreams& side, const LaunchEvents& ev) {
   // The Delta pass of a group of rows is HBM-bound; the selection chain that
-  // follows it (sums, pick, offsets, gather, select, scan, emit) is mostly
-  // launch- and latency-bound.  With a side stream the workers are taken in
-  // two groups: the first group's chain runs on the side stream while the
+  // follows it (sums, pick, gather, select, emit) is mostly launch- and
+  // latency-bound.  With a side stream the workers are taken in two groups: the first group's chain runs on the side stream while the
   // second group's Delta pass streams on s; s waits for the side stream at
   // the end.  The groups' scratch rows are disjoint.
   const bool split = side.stream != nullptr && K >= 2;
