@@ -8,9 +8,9 @@ namespace saef {
 
 // Pass-1 histogram of the key |v| around the threshold tau of the previous
 // call: a near range of kTkNear bins of 1/512 binade from kTkSpecMargin (1/32
-// binade) under tau to 0.19 binades above it; below it kTkMidB bins of 1/64
-// binade, above it kTkMidA of 1/16, then on each side kTkFar bins of a binade,
-// the last one open.  The bins only decide how many elements become
+// binade) under tau to 0.19 binades above it; below it kTkMidB and above it
+// kTkMidA bins of 1/64 binade, then on each side kTkFar bins of a binade, the
+// last one open.  The bins only decide how many elements become
 // candidates; the kept set is exact wherever the threshold falls.  Under error
 // feedback the residual piles up at tau; tau rises by 0.01-0.2 binades a call
 // (resnet50) and falls by 0.5-1.1 when the errors are averaged.  A bin of 1/64
@@ -21,10 +21,9 @@ namespace saef {
 // (Top-10% 1195 and 1154 against 1110 us).
 constexpr int kTkSubShift = 14;                // near bin width: 2^14 keys
 constexpr int kTkNear = 112;                   // near bins
-constexpr int kTkMidShiftB = 17;               // mid bin width below: 2^17 keys
-constexpr int kTkMidB = 96;                    // 1.5 binades
-constexpr int kTkMidShiftA = 19;               // mid bin width above: 2^19 keys
-constexpr int kTkMidA = 16;                    // one binade
+constexpr int kTkMidShift = 17;                // mid bin width: 2^17 keys
+constexpr int kTkMidB = 72;                    // below: 1.125 binades
+constexpr int kTkMidA = 40;                    // above: 0.625 binades
 constexpr int kTkFar = 8;                      // bins of a binade beyond, on each side
 constexpr int kTkBelow = kTkMidB + kTkFar;     // bins below the near range
 constexpr int kTkHist = kTkBelow + kTkNear + kTkMidA + kTkFar;
@@ -38,7 +37,10 @@ constexpr int kTkSmall = 16;      // most tiles of a small tensor in a plan with
 // 284 us; resnet50 K = 8 has 100,000).
 constexpr int64_t kTkSplitTiles = 16384;
 constexpr int kTkRefineLevels = 2;  // histograms of 11 key bits a refined bin gets
-constexpr int kTkGatherSplit = 4;  // gather workgroups per group of tiles
+// Gather workgroups per group of tiles (a wave then takes 4 tiles; 8 groups of
+// 2: resnet50 Top-1% 872 against 850 us, bert_base 7.48 against 7.13 ms; 16 of
+// one: 929 us and 8.69 ms).
+constexpr int kTkGatherSplit = 4;
 constexpr int kTkBins = 2048;     // bins of an 11-bit radix digit
 // Elements per server-aggregation workgroup: four tiles, one per wave.  Its 17
 // KB of LDS let it run beside a Delta pass, and a small layout still fills
@@ -58,8 +60,9 @@ constexpr int kTkChunk = 8192;
 constexpr int kTkSpecCap = 512;
 constexpr uint32_t kTkSpecNone = 0xFFFFu;
 constexpr uint32_t kTkSpecMargin = 1u << 18;
-static_assert((kTkMidA << kTkMidShiftA) == 1 << 23, "the mid bins above cover a binade");
-static_assert((kTkMidB << kTkMidShiftB) == 3 << 22, "the mid bins below cover 1.5 binades");
+static_assert(kTkMidB >= 1 << (23 - kTkMidShift) && kTkMidB < 2 << (23 - kTkMidShift) &&
+                  kTkMidA < 1 << (23 - kTkMidShift),
+              "the far bins start in the second binade below and the first above");
 constexpr int kTkSpecMaxShare = 8;  // lists when k_l * 8 <= n_l
 // Dynamic LDS the Delta pass requests and does not use: with its own 1 KB
 // it keeps at most 5 of its workgroups on a CU (160 KB of LDS), so the
@@ -154,7 +157,7 @@ struct TkDev {
   uint32_t* tile_cnt;  // [rows][n_tiles] kept per tile, then the exclusive prefix
   uint32_t* lcnt;      // [rows][n_tiles] entries in the tile's speculative list, or kTkSpecNone
   uint32_t* rhist;     // [rows][n_large][kTkRefineLevels][kTkBins] histograms of the refine
-  uint32_t* tile_cand;  // [rows][n_tiles] candidates of the tile (plans that refine)
+  uint32_t* tile_cand;  // [rows][n_tiles] candidates of the tile (calls that refine)
   uint32_t* seg;       // [rows][n_groups * kTkGatherSplit] candidates of each gather workgroup
   const int32_t* large;  // [n_large] the large tensors, in order
   // [rows][d_pad] candidate slots: (row, tensor) at the tensor's offset, those
@@ -166,7 +169,8 @@ struct TkDev {
   int64_t n_sgroups;
   int64_t n_large;     // large tensors (more than kTkGroup tiles)
   int64_t total_keep;
-  int32_t refine;      // 1: some tensor has super-groups; wide candidate bins are narrowed
+  int32_t refine;      // 1: full candidate bins are narrowed (some tensor has super-groups, or
+                       // one of the plan's first calls)
   int32_t pad;
 };
 

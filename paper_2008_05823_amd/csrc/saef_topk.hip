@@ -16,9 +16,10 @@
 //              k-th largest key.  A small tensor (up to 64 tiles; up to 16 in
 //              a plan that has larger ones) it selects as a whole, so its
 //              selection is this one kernel;
-//   refine     (plans with a tensor of more than 4096 tiles) a bin b1 with
-//              many elements is narrowed to a sub-range of it, 11 key bits
-//              at a time, by the workgroups of all tiles;
+//   refine     (plans with a tensor of more than 4096 tiles, and a plan's
+//              first calls) a bin b1 with many elements is narrowed to a
+//              sub-range of it, 11 key bits at a time, by the workgroups of
+//              all tiles;
 //   gather     the elements of b1 (the candidates) of large tensors, tile by
 //              tile, and each tile's count of elements above b1: from the
 //              tile's list when its bound lies at or below b1, else from one
@@ -67,11 +68,11 @@ __device__ __forceinline__ uint32_t hist_bin(uint32_t key, uint32_t win) {
   const int32_t s = (int32_t)(key - win);  // keys and win are below 2^31
   // below: x keys between key and win; above: x keys past the near range
   const uint32_t xb = ~(uint32_t)s, xa = (uint32_t)s - ((uint32_t)kTkNear << kTkSubShift);
-  const uint32_t mb = xb >> kTkMidShiftB;
+  const uint32_t mb = xb >> kTkMidShift, ma = xa >> kTkMidShift;
   const uint32_t gb = mb < (uint32_t)kTkMidB
                           ? mb : (uint32_t)(kTkMidB - 1) + min(xb >> 23, (uint32_t)kTkFar);
-  const uint32_t ga = min(xa >> kTkMidShiftA,
-                          (uint32_t)(kTkMidA - 1) + min(xa >> 23, (uint32_t)kTkFar));
+  const uint32_t ga = ma < (uint32_t)kTkMidA
+                          ? ma : (uint32_t)kTkMidA + min(xa >> 23, (uint32_t)(kTkFar - 1));
   const uint32_t side = s < 0 ? (uint32_t)(kTkBelow - 1) - gb : (uint32_t)(kTkBelow + kTkNear) + ga;
   const uint32_t d = (uint32_t)s >> kTkSubShift;
   return d < (uint32_t)kTkNear ? (uint32_t)kTkBelow + d : side;
@@ -396,7 +397,7 @@ __device__ void find_bin(const uint32_t* h, int nb, int64_t need, uint32_t* s_sc
 // candidates are collected does not matter.
 constexpr int kPick = 256;      // threads of the pick
 constexpr int kSelect = 512;    // threads of the select of large tensors
-constexpr int kPickCand = 512;  // candidates the pick keeps in LDS
+constexpr int kPickCand = 1024;  // candidates the pick keeps in LDS
 constexpr int kSelKeys = 4096;  // candidates whose keys the select keeps in LDS
 constexpr int kSelTiles = 2048; // tiles whose counts the select's LDS holds (packed 16-bit)
 constexpr int kRefineCand = 4096;  // more candidates than this are narrowed (refine)
@@ -415,13 +416,13 @@ __device__ __forceinline__ uint32_t bin_floor(uint32_t b, uint32_t win) {
     // bin g of the side: distances up to (below) the first of bin g + 1
     const int64_t g = kTkBelow - 1 - (int64_t)b;
     if (g == kTkBelow - 1) return 0u;
-    f = (int64_t)win - (g < kTkMidB ? (g + 1) << kTkMidShiftB : (g - kTkMidB + 2) << 23);
+    f = (int64_t)win - (g < kTkMidB ? (g + 1) << kTkMidShift : (g - kTkMidB + 2) << 23);
   } else if (b < (uint32_t)(kTkBelow + kTkNear)) {
     f = (int64_t)win + ((int64_t)(b - kTkBelow) << kTkSubShift);
   } else {
     const int64_t g = (int64_t)b - (kTkBelow + kTkNear);
     f = (int64_t)win + ((int64_t)kTkNear << kTkSubShift) +
-        (g < kTkMidA ? g << kTkMidShiftA : (g - kTkMidA + 1) << 23);
+        (g <= kTkMidA ? g << kTkMidShift : (g - kTkMidA) << 23);
   }
   return f <= 0 ? 0u : f < 0x80000000ll ? (uint32_t)f : 0x80000000u;
 }
@@ -579,27 +580,32 @@ __device__ __forceinline__ TileCounts scan_tiles(const CandSink& sink, const Dev
     const int count = (int)min((int64_t)kTkTileElems, ten.n - first);
     const Buf rd = buf_of(dr + ten.off + first, (uint32_t)count * 4u);
     uint32_t above = 0, inside = 0;
+    const bool whole = count == kTkTileElems;  // wave-uniform
     for (int w = 0; w < kTileWords; w += kW) {
       float v[kW];
+      u64 m[kW];
 #pragma unroll
       for (int u = 0; u < kW; ++u) v[u] = buf_ld(rd, (uint32_t)((w + u) * kWave + lane) * 4u);
       uint32_t total = 0;
 #pragma unroll
       for (int u = 0; u < kW; ++u) {
-        const bool ok = (w + u) * kWave + lane < count;
         const uint32_t key = key_of(v[u]);
-        above += (uint32_t)__popcll(__ballot(ok && key >= up));
-        total += (uint32_t)__popcll(__ballot(ok && key >= lo && key < up));
+        u64 gl = __ballot(key >= lo);
+        const u64 gu = __ballot(key >= up);
+        // past the tile's end the keys are 0: below up, but not below a lo of 0
+        if (!whole) gl &= __ballot((w + u) * kWave + lane < count);
+        m[u] = gl & ~gu;
+        above += (uint32_t)__popcll(gu);
+        total += (uint32_t)__popcll(m[u]);
       }
       if (total == 0u) continue;  // wave-uniform
       inside += total;
       uint32_t base = sink.take(total);
 #pragma unroll
       for (int u = 0; u < kW; ++u) {
-        const uint32_t key = key_of(v[u]);
-        const u64 m = __ballot((w + u) * kWave + lane < count && key >= lo && key < up);
-        sink.put(m, base, key, first + (w + u) * kWave + lane);
-        base += (uint32_t)__popcll(m);
+        if (m[u] == 0ull) continue;  // wave-uniform
+        sink.put(m[u], base, key_of(v[u]), first + (w + u) * kWave + lane);
+        base += (uint32_t)__popcll(m[u]);
       }
     }
     sure += lane == j ? above : 0u;
@@ -637,7 +643,7 @@ struct Cands {
       return;
     }
     const int nw = (int)blockDim.x / kWave;
-    constexpr int kS = 8;  // segments a wave has in flight
+    constexpr int kS = 4, kC = 4;  // segments, and chunks of each, in flight
     for (int s0 = wave_id() * kS; s0 < nseg; s0 += nw * kS) {
       uint32_t c[kS], most = 0;
 #pragma unroll
@@ -646,14 +652,22 @@ struct Cands {
         most = max(most, c[q]);
       }
       most = (uint32_t)__builtin_amdgcn_readfirstlane((int)most);
-      for (uint32_t b = 0; b < most; b += kWave) {
-        const uint32_t i = b + (uint32_t)lane_id();
-        u64 e[kS];
+      for (uint32_t b = 0; b < most; b += kC * kWave) {
+        u64 e[kC][kS];
 #pragma unroll
-        for (int q = 0; q < kS; ++q)
-          e[q] = p[i < c[q] ? (int64_t)(s0 + q) * stride + i : (int64_t)s0 * stride];
+        for (int a = 0; a < kC; ++a) {
+          const uint32_t i = b + (uint32_t)(a * kWave + lane_id());
 #pragma unroll
-        for (int q = 0; q < kS; ++q) f(e[q], i < c[q]);
+          for (int q = 0; q < kS; ++q)
+            e[a][q] = p[i < c[q] ? (int64_t)(s0 + q) * stride + i : (int64_t)s0 * stride];
+        }
+#pragma unroll
+        for (int a = 0; a < kC; ++a) {
+          const uint32_t i = b + (uint32_t)(a * kWave + lane_id());
+          if (b + (uint32_t)(a * kWave) >= most) break;  // wave-uniform
+#pragma unroll
+          for (int q = 0; q < kS; ++q) f(e[a][q], i < c[q]);
+        }
       }
     }
   }
@@ -993,7 +1007,7 @@ __device__ __forceinline__ void cand_range(const TkDev& tk, const TkSel& st, int
 // passes over all the candidates of such a bin (a wide one, or one where
 // many values are equal) took up to 3 ms at bert_base Top-1% (K = 16), whose
 // outliers all have one magnitude.  Launched for plans with a tensor of more
-// than 4096 tiles.
+// than 4096 tiles, and for a plan's first calls, whose bins are not placed yet.
 template <int kLevel>
 __global__ __launch_bounds__(kBlock) void k_tk_refine(DevLayout lay, TkDev tk, TkPart p, int row0,
                                                       const float* __restrict__ data) {
@@ -1388,13 +1402,14 @@ __global__ __launch_bounds__(kBlock) void k_tk_emit(DevLayout lay, TkDev tk, TkP
   load_tile(dr, tile.count, v);
   const uint32_t tau = stp->tau;
   const int64_t iota = stp->iota;
+  // the last kept element equal to tau, in the tile (none: -1; past the tile's
+  // end the keys are 0, and kept ones end before it)
+  const int last = (int)max((int64_t)-1, min(iota - rel0, (int64_t)tile.count - 1));
   u64 mine = 0;  // lane u: word u
 #pragma unroll
   for (int u = 0; u < kTileWords; ++u) {
-    const int j = u * kWave + lane;
     const uint32_t key = key_of(v[u]);
-    const u64 word = __ballot(j < tile.count &&
-                              (key > tau || (key == tau && rel0 + (int64_t)j <= iota)));
+    const u64 word = __ballot(key > tau || (key == tau && u * kWave + lane <= last));
     if (lane == u) mine = word;
   }
   const uint32_t excl = emit_words(mine, nw, base, sr, rr);
