@@ -326,7 +326,9 @@ int saef_status(const saef_layout* layout, hipStream_t stream);
  * error averaging (with step ahead in the SAEF variant), 6 = mismatch
  * bounds), until the pairs run out (saef_round, saef_round_noalloc and
  * saef_round_momentum take the step ahead and the worker compression of an
- * iteration without averaging as one kernel, timed as kind 1); with every > 1 only the 1st, (every+1)-th,
+ * iteration without averaging as one kernel, timed as kind 1, and iterations of at
+ * most 16 workers on a layout of at most 2048 tiles, 64 in any tensor, add the worker
+ * scales up in the aggregation and launch no kind 2); with every > 1 only the 1st, (every+1)-th,
  * ... dispatch of each timed kind since the call is stamped (a sample spread
  * over the run; every < 1 is SAEF_EINVAL).  saef_profile_read waits for the
  * recorded events and returns, per kind, the number of launches timed

@@ -356,6 +356,7 @@ int saef_layout_create(const int64_t* off, const int64_t* n, int32_t L, int64_t 
   d.tensors = static_cast<const TensorInfo*>(lay->mem_tensors);
   d.part = static_cast<unsigned long long*>(lay->mem_part);
   d.part2 = static_cast<unsigned long long*>(lay->mem_part2);
+  d.max_tiles = max_tiles;
   d.fin_split = fin_split;
   d.status = static_cast<int*>(lay->mem_status);
   d.n_tiles = (int64_t)tiles.size();
@@ -435,8 +436,8 @@ int saef_aggregate(const saef_layout* layout, int32_t K, int32_t mode, const uin
   if (avg != nullptr && !aligned(avg, 4)) return SAEF_EINVAL;
   if (mode == SAEF_MODE_DC && (!f32_ok(e_srv) || !u64_ok(srv_signs) || !f32_ok(srv_scales)))
     return SAEF_EINVAL;
-  rc = hip_rc(saef::launch_aggregate(layout->dev, K, mode, signs, scales, avg, e_srv, srv_signs,
-                                     srv_scales, x, false, stream));
+  rc = hip_rc(saef::launch_aggregate(layout->dev, K, mode, signs, const_cast<float*>(scales),
+                                     false, avg, e_srv, srv_signs, srv_scales, x, false, stream));
   if (rc != SAEF_OK || mode == SAEF_MODE_SC) return rc;
   rc = hip_rc(saef::launch_finalize(layout->dev, K, true, srv_scales, stream));
   if (rc != SAEF_OK) return rc;
@@ -576,13 +577,17 @@ int round_end_impl(const saef_layout* layout, int64_t t, int64_t period, int32_t
                                  stream, ev);
   }));
   if (rc != SAEF_OK) return rc;
-  rc = hip_rc(timed(layout, 2, [&](const saef::LaunchEvents& ev) {
-    return saef::launch_finalize(d, K, false, scales, stream, ev);
-  }));
+  // Small layouts: the aggregation adds up the worker partials itself, one
+  // dependent launch less.
+  const bool fold = saef::folds_scales(d, K);
+  if (!fold)
+    rc = hip_rc(timed(layout, 2, [&](const saef::LaunchEvents& ev) {
+      return saef::launch_finalize(d, K, false, scales, stream, ev);
+    }));
   if (rc != SAEF_OK) return rc;
   // server aggregation, server compression; x keeps its correction pending
   rc = hip_rc(timed(layout, 3, [&](const saef::LaunchEvents& ev) {
-    return saef::launch_aggregate(d, K, mode, signs, scales, nullptr, e_srv, srv_signs,
+    return saef::launch_aggregate(d, K, mode, signs, scales, fold, nullptr, e_srv, srv_signs,
                                   srv_scales, x, pending && dc, stream, ev);
   }));
   if (rc != SAEF_OK || !dc) return rc;

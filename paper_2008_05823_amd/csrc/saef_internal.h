@@ -63,6 +63,7 @@ struct DevLayout {
   unsigned long long* part;  // [(k_max + 1) * n_tiles * 2] exact partial sums (lo, hi) of
                              // each tile; row k_max belongs to the server
   unsigned long long* part2; // [(k_max + 1) * L * fin_split * 2] second-level sums
+  int32_t max_tiles;         // tiles of the tensor with the most of them
   int32_t fin_split;         // finalize workgroups per (row, tensor): ceil(max tiles / kFinChunk)
   int* status;               // sticky error flag
   int64_t n_tiles;
@@ -112,15 +113,28 @@ hipError_t launch_finalize(const DevLayout& lay, int K, bool server, float* scal
                            hipStream_t s,
                            const LaunchEvents& ev = LaunchEvents());
 
+// Whether the aggregation adds up the worker partials itself: a lane per tile
+// and kFoldRows workers at most, and no more tiles than run at once (8
+// workgroups on each of 256 CUs), where the launch of a finalize kernel takes
+// longer than its work in every workgroup: resnet56 K = 8 39.3 us per
+// iteration against 41.4 with the kernel, one tensor of 65536 K = 4 18.8
+// against 21.0.
+constexpr int kFoldRows = 16;
+constexpr int64_t kFoldTiles = 2048;
+bool folds_scales(const DevLayout& lay, int K);
+
 // Server aggregation.  mode 1: reads/writes e_srv (Delta before correction),
 // writes srv_signs and the server tile partial sums (launch_finalize then
 // writes srv_scales); decode applies the pending server correction (old
 // srv_signs/srv_scales) to e_srv on read and materializes it into x.
-// mode 0: x <- x - mean.  avg written when non-null.
+// mode 0: x <- x - mean.  avg written when non-null.  fold (only where
+// folds_scales says so, and without avg): the worker scales come from the
+// tile partials and are written here, instead of by launch_finalize before;
+// otherwise scales is only read.
 hipError_t launch_aggregate(const DevLayout& lay, int K, int mode, const uint64_t* signs,
-                            const float* scales, float* avg, float* e_srv, uint64_t* srv_signs,
-                            const float* srv_scales, float* x, bool decode, hipStream_t s,
-                           const LaunchEvents& ev = LaunchEvents());
+                            float* scales, bool fold, float* avg, float* e_srv,
+                            uint64_t* srv_signs, const float* srv_scales, float* x, bool decode,
+                            hipStream_t s, const LaunchEvents& ev = LaunchEvents());
 
 // How the worker errors are read: as stored; with the pending scaled-sign
 // correction (e - (bit ? s : -s), sign words and scales); or with the

@@ -619,19 +619,74 @@ struct AggGroup {
   u64 words;
   float sc;
 };
-template <bool kFull>
+// The scales of the workgroup's tensor in LDS, where the aggregation adds up
+// the tile partials itself.
+struct FoldedScales {
+  float sc[kFoldRows];
+};
+__device__ __forceinline__ u64 readlane64(u64 v, int lane) {
+  return ((u64)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(v >> 32), lane) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((uint32_t)v, lane);
+}
+template <bool kFold, bool kFull>
 __device__ __forceinline__ AggGroup agg_group_load(int k0, int K, int L, int l, int64_t W,
                                                    int w0, int count,
                                                    const uint64_t* __restrict__ sw,
-                                                   const float* __restrict__ scales) {
+                                                   const float* __restrict__ scales,
+                                                   const FoldedScales& fold) {
   const int lane = lane_id();
   const int kl = k0 + lane / kU, ul = lane % kU;
   AggGroup g;
   g.words = 0ull;
   if (kl < K && (kFull || (w0 + ul) * 64 < count)) g.words = sw[(int64_t)kl * W + w0 + ul];
   g.sc = 0.0f;
-  if (lane < kAggGroup && k0 + lane < K) g.sc = scales[(int64_t)(k0 + lane) * L + l];
+  if (lane < kAggGroup && k0 + lane < K)
+    g.sc = kFold ? fold.sc[k0 + lane] : scales[(int64_t)(k0 + lane) * L + l];
   return g;
+}
+
+// The K worker scales of tile ti's tensor from its tile partials (at most one
+// per lane), for the whole workgroup; the workgroup of the tensor's first
+// tile also stores them.  Wave w takes workers w, w + kSWaves, ...: all their
+// partials are loaded at once, added as three 64-bit integers each, and lane
+// i turns worker i's sum into its scale.
+__device__ __forceinline__ void fold_scales(const DevLayout& lay, int K, int l, int64_t ti,
+                                            float* __restrict__ scales, FoldedScales& fold) {
+  constexpr int kR = kFoldRows / kSWaves;
+  const TensorInfo t = lay.tensors[l];
+  const int lane = lane_id(), wave = wave_id();
+  const bool ok = lane < t.ntiles;
+  u64 lo[kR], hi[kR];
+#pragma unroll
+  for (int i = 0; i < kR; ++i) {
+    const int k = min(wave + i * kSWaves, K - 1);
+    const u64* v = lay.part + ((int64_t)k * lay.n_tiles + t.first_tile + (ok ? lane : 0)) * 2;
+    lo[i] = v[0];
+    hi[i] = v[1];
+  }
+  u64 my_lo = 0, my_hi = 0;
+#pragma unroll
+  for (int i = 0; i < kR; ++i) {
+    if (wave + i * kSWaves >= K) break;  // wave-uniform
+    const u64 a = (u64)wave_sum_i64(ok ? (int64_t)(lo[i] & 0xffffffffull) : 0);
+    const u64 b = (u64)wave_sum_i64(ok ? (int64_t)(lo[i] >> 32) : 0);
+    const u64 c = (u64)wave_sum_i64(ok ? (int64_t)hi[i] : 0);
+    u64 slo = a, shi = c;
+    add128(slo, shi, b << 32, b >> 32);
+    slo = readlane64(slo, kWave - 1);
+    shi = readlane64(shi, kWave - 1);
+    if (lane == i) {
+      my_lo = slo;
+      my_hi = shi;
+    }
+  }
+  const int k = wave + lane * kSWaves;
+  if (lane < kR && k < K) {
+    const float sc = scale_from_sum(my_hi, my_lo, t.n);
+    fold.sc[k] = sc;
+    if (ti == t.first_tile) scales[(int64_t)k * lay.L + l] = sc;
+  }
+  lds_barrier();
 }
 // One pass of a wave over the kU words starting at word w0 of a tile (offsets
 // relative to the tile; buffer resources over the tile's elements and server
@@ -639,12 +694,13 @@ __device__ __forceinline__ AggGroup agg_group_load(int k0, int K, int L, int l, 
 // in binary64, k order) / K.  Worker words come from sw (the tile's first
 // word of worker 0; worker k at sw + k W).  kFull: all kU words lie inside
 // the tile (no lane masks).
-template <int kMode, bool kDecode, bool kAvg, bool kFull>
+template <int kMode, bool kDecode, bool kAvg, bool kFold, bool kFull>
 __device__ __forceinline__ void aggregate_pass(int K, double inv_k, int L, int l, int64_t W,
                                                int w0, int count,
                                                const uint64_t* __restrict__ sw,
-                                               const float* __restrict__ scales, Buf ravg,
-                                               Buf res, Buf rss, const Corr& c_old, Buf rx,
+                                               const float* __restrict__ scales,
+                                               const FoldedScales& fold, Buf ravg, Buf res,
+                                               Buf rss, const Corr& c_old, Buf rx,
                                                ExactSum& acc) {
   const int lane = lane_id();
   const uint32_t off0 = (uint32_t)(w0 * 64 + lane) * 4u;
@@ -652,7 +708,7 @@ __device__ __forceinline__ void aggregate_pass(int K, double inv_k, int L, int l
   // the first group's words and scales go out before the element loads, so
   // that waiting for them (vector loads complete in order) does not wait for
   // the elements
-  AggGroup grp = agg_group_load<kFull>(0, K, L, l, W, w0, count, sw, scales);
+  AggGroup grp = agg_group_load<kFold, kFull>(0, K, L, l, W, w0, count, sw, scales, fold);
   __builtin_amdgcn_sched_barrier(0);
   float ev[kU], xv[kU];
   const u64 mo = (kMode == 1 && kDecode) ? buf_ld_words(rss, w0, kU) : 0ull;  // old words
@@ -665,7 +721,8 @@ __device__ __forceinline__ void aggregate_pass(int K, double inv_k, int L, int l
 #pragma unroll
   for (int u = 0; u < kU; ++u) acc_m[u] = 0.0;
   for (int k0 = 0; k0 < K; k0 += kAggGroup) {
-    if (k0 > 0) grp = agg_group_load<kFull>(k0, K, L, l, W, w0, count, sw, scales);
+    if (k0 > 0)
+      grp = agg_group_load<kFold, kFull>(k0, K, L, l, W, w0, count, sw, scales, fold);
 #pragma unroll
     for (int c = 0; c < kAggGroup; ++c) {
       if (k0 + c >= K) break;  // wave-uniform
@@ -711,10 +768,12 @@ __device__ __forceinline__ void aggregate_pass(int K, double inv_k, int L, int l
 // tile order of run_tile_of (neighbouring tiles, whose sign words share cache
 // lines, run on one XCD).  Wave w takes words w*kU .. w*kU+kU-1 of the tile
 // (one pass over a whole tile), then strides by 4*kU words.
-template <int kMode, bool kDecode, bool kAvg>
+// kFold: the worker scales come from the tile partials instead of a finalize
+// kernel before (folds_scales), and are written here.
+template <int kMode, bool kDecode, bool kAvg, bool kFold>
 __global__ __launch_bounds__(kSBlock) void k_aggregate(DevLayout lay, int K, double inv_k,
                                                       const uint64_t* __restrict__ signs,
-                                                      const float* __restrict__ scales,
+                                                      float* __restrict__ scales,
                                                       float* __restrict__ avg,
                                                       float* __restrict__ es,
                                                       uint64_t* __restrict__ ss,
@@ -734,16 +793,18 @@ __global__ __launch_bounds__(kSBlock) void k_aggregate(DevLayout lay, int K, dou
   const Buf rx = buf_of(x + tile.start, nbytes);
   const Corr c_old((kMode == 1 && kDecode) ? sscales[tile.l] : 0.0f);
   const int64_t W = lay.d_pad >> 6;
+  __shared__ FoldedScales fold;
+  if (kFold) fold_scales(lay, K, tile.l, ti, scales, fold);
   ExactSum acc;
   for (int w0 = wave_id() * kU; w0 < nw; w0 += kSWaves * kU) {
     if ((w0 + kU) * 64 <= tile.count) {
-      aggregate_pass<kMode, kDecode, kAvg, true>(K, inv_k, lay.L, tile.l, W, w0, tile.count,
-                                                 signs + gw0, scales, ravg, res, rss, c_old, rx,
-                                                 acc);
+      aggregate_pass<kMode, kDecode, kAvg, kFold, true>(
+          K, inv_k, lay.L, tile.l, W, w0, tile.count, signs + gw0, scales, fold, ravg, res, rss,
+          c_old, rx, acc);
     } else {
-      aggregate_pass<kMode, kDecode, kAvg, false>(K, inv_k, lay.L, tile.l, W, w0, tile.count,
-                                                  signs + gw0, scales, ravg, res, rss, c_old, rx,
-                                                  acc);
+      aggregate_pass<kMode, kDecode, kAvg, kFold, false>(
+          K, inv_k, lay.L, tile.l, W, w0, tile.count, signs + gw0, scales, fold, ravg, res, rss,
+          c_old, rx, acc);
     }
     if (kMode == 1) acc.added(kU);
   }
@@ -1178,23 +1239,35 @@ hipError_t launch_finalize(const DevLayout& lay, int K, bool server, float* scal
   return hipGetLastError();
 }
 
+bool folds_scales(const DevLayout& lay, int K) {
+  return K <= kFoldRows && lay.max_tiles <= kWave && lay.n_tiles <= kFoldTiles;
+}
+
 hipError_t launch_aggregate(const DevLayout& lay, int K, int mode, const uint64_t* signs,
-                            const float* scales, float* avg, float* e_srv, uint64_t* srv_signs,
-                            const float* srv_scales, float* x, bool decode, hipStream_t s, const LaunchEvents& ev) {
+                            float* scales, bool fold, float* avg, float* e_srv,
+                            uint64_t* srv_signs, const float* srv_scales, float* x, bool decode,
+                            hipStream_t s, const LaunchEvents& ev) {
   const dim3 grid((unsigned)run_padded_tiles(lay.n_tiles));
   const double ik = inv_pow2(K);
-#define SAEF_AGG(M, D, A)                                                                  \
-  SAEF_LAUNCH((k_aggregate<M, D, A>), grid, dim3(kSBlock), 0, s, lay, K, ik, signs, \
+#define SAEF_AGG(M, D, A, F)                                                                  \
+  SAEF_LAUNCH((k_aggregate<M, D, A, F>), grid, dim3(kSBlock), 0, s, lay, K, ik, signs, \
                      scales, avg, e_srv, srv_signs, srv_scales, x)
   const bool a = avg != nullptr;
-  if (mode == 1) {
-    if (decode) {
-      if (a) SAEF_AGG(1, true, true); else SAEF_AGG(1, true, false);
+  if (fold) {
+    if (a || !folds_scales(lay, K)) return hipErrorInvalidValue;  // never requested
+    if (mode == 1) {
+      if (decode) SAEF_AGG(1, true, false, true); else SAEF_AGG(1, false, false, true);
     } else {
-      if (a) SAEF_AGG(1, false, true); else SAEF_AGG(1, false, false);
+      SAEF_AGG(0, false, false, true);
+    }
+  } else if (mode == 1) {
+    if (decode) {
+      if (a) SAEF_AGG(1, true, true, false); else SAEF_AGG(1, true, false, false);
+    } else {
+      if (a) SAEF_AGG(1, false, true, false); else SAEF_AGG(1, false, false, false);
     }
   } else {
-    if (a) SAEF_AGG(0, false, true); else SAEF_AGG(0, false, false);
+    if (a) SAEF_AGG(0, false, true, false); else SAEF_AGG(0, false, false, false);
   }
 #undef SAEF_AGG
   return hipGetLastError();
