@@ -401,11 +401,13 @@ int compress_impl(const saef_layout* layout, int32_t K, float lr, float mu, cons
   rc = hip_rc(
       saef::launch_compress(layout->dev, K, lr, mu, g, m, e, signs, scales, false, stream));
   if (rc != SAEF_OK) return rc;
-  rc = hip_rc(saef::launch_finalize(layout->dev, K, false, scales, stream));
+  // e <- Delta - C(Delta); small layouts: the scales as well
+  const bool fold = saef::folds_scales(layout->dev, K);
+  if (!fold) rc = hip_rc(saef::launch_finalize(layout->dev, K, false, scales, stream));
   if (rc != SAEF_OK) return rc;
-  return hip_rc(saef::launch_materialize(layout->dev, K, SAEF_MODE_SC, e, signs, scales, e,
+  return hip_rc(saef::launch_materialize(layout->dev, K, SAEF_MODE_DC, e, signs, scales, e,
                                          nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                         stream));
+                                         fold, stream));
 }
 
 bool mu_ok(float mu) { return mu >= 0.0f && mu < 1.0f; }
@@ -439,12 +441,13 @@ int saef_aggregate(const saef_layout* layout, int32_t K, int32_t mode, const uin
   rc = hip_rc(saef::launch_aggregate(layout->dev, K, mode, signs, const_cast<float*>(scales),
                                      false, avg, e_srv, srv_signs, srv_scales, x, false, stream));
   if (rc != SAEF_OK || mode == SAEF_MODE_SC) return rc;
-  rc = hip_rc(saef::launch_finalize(layout->dev, K, true, srv_scales, stream));
+  // e_srv <- Delta - C(Delta), x <- x - C(Delta); small layouts: the scales as well
+  const bool fold = saef::folds_scales(layout->dev, 1);
+  if (!fold) rc = hip_rc(saef::launch_finalize(layout->dev, K, true, srv_scales, stream));
   if (rc != SAEF_OK) return rc;
-  // e_srv <- Delta - C(Delta), x <- x - C(Delta)
   return hip_rc(saef::launch_materialize(layout->dev, 0, SAEF_MODE_DC, nullptr, nullptr,
                                          nullptr, nullptr, e_srv, x, srv_signs, srv_scales,
-                                         e_srv, x, stream));
+                                         e_srv, x, fold, stream));
 }
 
 int saef_step_ahead(const saef_layout* layout, int32_t K, const float* x, const float* e,
@@ -714,9 +717,10 @@ int saef_materialize(const saef_layout* layout, int32_t K, int32_t mode, const f
       (!u64_ok(srv_signs) || !f32_ok(srv_scales)))
     return SAEF_EINVAL;
   if (mode == SAEF_MODE_DC && e_srv_out != nullptr && !f32_ok(e_srv)) return SAEF_EINVAL;
-  return hip_rc(saef::launch_materialize(layout->dev, K, mode, e, signs, scales,
-                                         e_out, e_srv, x, srv_signs, srv_scales, e_srv_out,
-                                         x_out, stream));
+  return hip_rc(saef::launch_materialize(layout->dev, K, mode, e, signs,
+                                         const_cast<float*>(scales), e_out, e_srv, x, srv_signs,
+                                         const_cast<float*>(srv_scales), e_srv_out, x_out, false,
+                                         stream));
 }
 
 int saef_profile_enable(saef_layout* layout, int32_t capacity, uint32_t kind_mask,

@@ -113,12 +113,13 @@ hipError_t launch_finalize(const DevLayout& lay, int K, bool server, float* scal
                            hipStream_t s,
                            const LaunchEvents& ev = LaunchEvents());
 
-// Whether the aggregation adds up the worker partials itself: a lane per tile
-// and kFoldRows workers at most, and no more tiles than run at once (8
-// workgroups on each of 256 CUs), where the launch of a finalize kernel takes
-// longer than its work in every workgroup: resnet56 K = 8 39.3 us per
-// iteration against 41.4 with the kernel, one tensor of 65536 K = 4 18.8
-// against 21.0.
+// Whether the aggregation and the in-place corrections of the single calls
+// add up the tile partials themselves: a lane per tile and kFoldRows workers
+// at most, and no more tiles than run at once (8 workgroups on each of 256
+// CUs), where the launch of a finalize kernel takes longer than its work in
+// every workgroup: resnet56 K = 8 39.3 us per iteration against 41.4 with the
+// kernel, one tensor of 65536 K = 4 18.8 against 21.0, the single calls of one
+// of 12 workers on 91 tensors of 72071 elements 32.7 against 40.6.
 constexpr int kFoldRows = 16;
 constexpr int64_t kFoldTiles = 2048;
 bool folds_scales(const DevLayout& lay, int K);
@@ -165,12 +166,14 @@ hipError_t launch_weights(const DevLayout& lay, const float* x, const uint64_t* 
 // Apply pending corrections: e_out[k] = e[k] - c_k for k < K (when e_out),
 // and, when e_srv_out or x_out is given, e_srv_out = e_srv - c and
 // x_out = x - c (mode 1) or plain copies (mode 0; e_srv_out then receives 0).
+// fold (mode 1, where folds_scales says so): the scales of the rows asked for
+// come from the tile partials and are written, instead of by launch_finalize
+// before; otherwise they are only read.
 hipError_t launch_materialize(const DevLayout& lay, int K, int mode, const float* e,
-                              const uint64_t* signs, const float* scales, float* e_out,
+                              const uint64_t* signs, float* scales, float* e_out,
                               const float* e_srv, const float* x, const uint64_t* srv_signs,
-                              const float* srv_scales, float* e_srv_out, float* x_out,
-                              hipStream_t s,
-                           const LaunchEvents& ev = LaunchEvents());
+                              float* srv_scales, float* e_srv_out, float* x_out, bool fold,
+                              hipStream_t s, const LaunchEvents& ev = LaunchEvents());
 
 // Gradient-mismatch bounds of the state (a diagnostic): out[l] = sum over
 // tensor l of (e_srv + ebar)^2 and out[L + l] = (1/K) sum_k sum (e_srv + ebar

@@ -122,6 +122,22 @@ __device__ __forceinline__ void wave_sum128(u64& lo, u64& hi) {
   }
 }
 
+__device__ __forceinline__ u64 readlane64(u64 v, int lane) {
+  return ((u64)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(v >> 32), lane) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((uint32_t)v, lane);
+}
+// The sum of the lanes' 128-bit values (below 2^127 in all) in every lane, as
+// three sums of 64-bit integers over DPP operands.
+__device__ __forceinline__ void lane_sum128(u64 lo, u64 hi, u64& slo, u64& shi) {
+  const u64 a = (u64)wave_sum_i64((int64_t)(lo & 0xffffffffull));
+  const u64 b = (u64)wave_sum_i64((int64_t)(lo >> 32));
+  slo = a;
+  shi = (u64)wave_sum_i64((int64_t)hi);
+  add128(slo, shi, b << 32, b >> 32);
+  slo = readlane64(slo, kWave - 1);
+  shi = readlane64(shi, kWave - 1);
+}
+
 // Nearest binary64 to the 128-bit integer (hi, lo), ties to even.
 __device__ double u128_to_f64(u64 hi, u64 lo) {
   if (hi == 0) return (double)lo;
@@ -624,10 +640,6 @@ struct AggGroup {
 struct FoldedScales {
   float sc[kFoldRows];
 };
-__device__ __forceinline__ u64 readlane64(u64 v, int lane) {
-  return ((u64)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(v >> 32), lane) << 32) |
-         (uint32_t)__builtin_amdgcn_readlane((uint32_t)v, lane);
-}
 template <bool kFold, bool kFull>
 __device__ __forceinline__ AggGroup agg_group_load(int k0, int K, int L, int l, int64_t W,
                                                    int w0, int count,
@@ -648,8 +660,7 @@ __device__ __forceinline__ AggGroup agg_group_load(int k0, int K, int L, int l, 
 // The K worker scales of tile ti's tensor from its tile partials (at most one
 // per lane), for the whole workgroup; the workgroup of the tensor's first
 // tile also stores them.  Wave w takes workers w, w + kSWaves, ...: all their
-// partials are loaded at once, added as three 64-bit integers each, and lane
-// i turns worker i's sum into its scale.
+// partials are loaded at once, and lane i turns worker i's sum into its scale.
 __device__ __forceinline__ void fold_scales(const DevLayout& lay, int K, int l, int64_t ti,
                                             float* __restrict__ scales, FoldedScales& fold) {
   constexpr int kR = kFoldRows / kSWaves;
@@ -668,13 +679,8 @@ __device__ __forceinline__ void fold_scales(const DevLayout& lay, int K, int l, 
 #pragma unroll
   for (int i = 0; i < kR; ++i) {
     if (wave + i * kSWaves >= K) break;  // wave-uniform
-    const u64 a = (u64)wave_sum_i64(ok ? (int64_t)(lo[i] & 0xffffffffull) : 0);
-    const u64 b = (u64)wave_sum_i64(ok ? (int64_t)(lo[i] >> 32) : 0);
-    const u64 c = (u64)wave_sum_i64(ok ? (int64_t)hi[i] : 0);
-    u64 slo = a, shi = c;
-    add128(slo, shi, b << 32, b >> 32);
-    slo = readlane64(slo, kWave - 1);
-    shi = readlane64(shi, kWave - 1);
+    u64 slo, shi;
+    lane_sum128(ok ? lo[i] : 0ull, ok ? hi[i] : 0ull, slo, shi);
     if (lane == i) {
       my_lo = slo;
       my_hi = shi;
@@ -812,52 +818,87 @@ __global__ __launch_bounds__(kSBlock) void k_aggregate(DevLayout lay, int K, dou
 }
 
 // ------------------------------------------------------------------ materialize
+// The scale of (row, tensor l) from the tensor's tile partials (at most one
+// per lane), in every lane.
+__device__ __forceinline__ float fold_scale(const DevLayout& lay, int row, const TensorInfo& t) {
+  const bool ok = lane_id() < t.ntiles;
+  const u64* v = lay.part + ((int64_t)row * lay.n_tiles + t.first_tile + (ok ? lane_id() : 0)) * 2;
+  u64 lo, hi;
+  lane_sum128(ok ? v[0] : 0ull, ok ? v[1] : 0ull, lo, hi);
+  return scale_from_sum(hi, lo, t.n);
+}
+
+// kU words of a tile from word w0: out <- in - (bit ? s : -s) for one or two
+// arrays with the same words (kCopy: the second copied, the first set to 0).
+// A resource of size 0 stands for an array that is not asked for.
+template <bool kTwo, bool kCopy>
+__device__ __forceinline__ void correct_words(int w0, Buf rw, const Corr& c, Buf ra, Buf oa,
+                                              Buf rb, Buf ob) {
+  const uint32_t off0 = (uint32_t)(w0 * 64 + lane_id()) * 4u;
+  const u64 words = kCopy ? 0ull : buf_ld_words(rw, w0, kU);
+  __builtin_amdgcn_sched_barrier(0);
+  float av[kU], bv[kU];
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
+    av[u] = kCopy ? 0.0f : buf_ld(ra, off0 + 256u * u);
+    bv[u] = kTwo ? buf_ld(rb, off0 + 256u * u) : 0.0f;
+  }
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
+    const float q = kCopy ? 0.0f : c(word_of(words, u));
+    buf_st(oa, off0 + 256u * u, kCopy ? 0.0f : av[u] - q);
+    if (kTwo) buf_st(ob, off0 + 256u * u, kCopy ? bv[u] : bv[u] - q);
+  }
+}
+
 // Grid: n_tiles * rows, rows = K (+1 when the server row is requested); row K
-// is the server error and the weights.
+// is the server error and the weights.  Bound by HBM: a tile in one pass of 8
+// words per wave, all loads before the first use (resnet50, one worker row:
+// 32 us, 6.4 TB/s; the server row, e_srv and x: 60 us, 6.8 TB/s; a word per
+// wave at a time before, 356 against 287 us per iteration of one of 8 workers
+// by the single calls).  The tiles in reverse order, or the stores of Delta
+// cached, find no more of it in the last-level cache (287 and 294 us).
 // e_out may be e, es_out es and x_out x (in place): every element is read and
-// then written by the same lane, so those pairs are not restrict-qualified.
-__global__ __launch_bounds__(kBlock) void k_materialize(
-    DevLayout lay, int K, int rows, int mode, const float* e,
-    const uint64_t* __restrict__ signs, const float* __restrict__ scales, float* e_out,
-    const float* es, const float* x, const uint64_t* __restrict__ ss,
-    const float* __restrict__ sscales, float* es_out, float* x_out) {
-  const int64_t b = blockIdx.x;
-  const int row = (int)(b % rows);
-  const Tile tile = lay.tiles[b / rows];
-  const int l = tile.l;
-  const int lane = lane_id();
-  const int wave = wave_id();
-  const int64_t d_pad = lay.d_pad;
-  const int64_t gw0 = tile.start >> 6;
+// then written by the same lane.  kFold: the scales of the rows come from the
+// tile partials (folds_scales) and are written here.
+template <int kMode, bool kFold>
+__global__ __launch_bounds__(kSBlock) void k_materialize(
+    DevLayout lay, int K, int rows, const float* e, const uint64_t* __restrict__ signs,
+    float* __restrict__ scales, float* e_out, const float* es, const float* x,
+    const uint64_t* __restrict__ ss, float* __restrict__ sscales, float* es_out, float* x_out) {
+  const unsigned b = blockIdx.x;
+  const int row = (int)(b % (unsigned)rows);
+  const int64_t ti = b / (unsigned)rows;
+  const Tile tile = lay.tiles[ti];
   const int nw = (tile.count + 63) >> 6;
-  if (row < K) {
-    const float s = scales[(int64_t)row * lay.L + l];
-    const uint64_t* sk = signs + (int64_t)row * (d_pad >> 6) + gw0;
-    for (int w = wave; w < nw; w += kWaves) {
-      const u64 m = sk[w];
-      const int j = w * 64 + lane;
-      if (j < tile.count) {
-        const int64_t i = (int64_t)row * d_pad + tile.start + j;
-        e_out[i] = e[i] - corr(m, s);
-      }
-    }
+  const uint32_t nbytes = (uint32_t)tile.count * 4u, wbytes = (uint32_t)nw * 8u;
+  const int64_t gw0 = tile.start >> 6;
+  const bool server = row == K;  // workgroup-uniform
+  float* sc = server ? sscales + tile.l : scales + (int64_t)row * lay.L + tile.l;
+  float s = 0.0f;
+  if (kFold) {
+    const TensorInfo t = lay.tensors[tile.l];
+    s = fold_scale(lay, server ? lay.k_max : row, t);
+    if (ti == t.first_tile && threadIdx.x == 0) *sc = s;
+  } else if (!server || kMode == 1) {
+    s = *sc;
+  }
+  const Corr c(s);
+  if (!server) {
+    const int64_t at = (int64_t)row * lay.d_pad + tile.start;
+    const Buf rw = buf_of(signs + (int64_t)row * (lay.d_pad >> 6) + gw0, wbytes);
+    const Buf re = buf_of(e + at, nbytes), oe = buf_of(e_out + at, nbytes);
+    for (int w0 = wave_id() * kU; w0 < nw; w0 += kSWaves * kU)
+      correct_words<false, false>(w0, rw, c, re, oe, re, oe);
     return;
   }
-  const float s = (mode == 1) ? sscales[l] : 0.0f;
-  for (int w = wave; w < nw; w += kWaves) {
-    const u64 m = (mode == 1) ? ss[gw0 + w] : 0ull;
-    const int j = w * 64 + lane;
-    if (j >= tile.count) continue;
-    const int64_t i = tile.start + j;
-    if (mode == 1) {
-      const float c = corr(m, s);
-      if (es_out) es_out[i] = es[i] - c;
-      if (x_out) x_out[i] = x[i] - c;
-    } else {
-      if (es_out) es_out[i] = 0.0f;
-      if (x_out) x_out[i] = x[i];
-    }
-  }
+  const Buf rw = buf_of(kMode == 1 ? (const void*)(ss + gw0) : lay.tiles, kMode == 1 ? wbytes : 0u);
+  const Buf re = buf_of(es_out ? es + tile.start : nullptr, es_out && kMode == 1 ? nbytes : 0u);
+  const Buf oe = buf_of(es_out ? es_out + tile.start : nullptr, es_out ? nbytes : 0u);
+  const Buf rx = buf_of(x_out ? x + tile.start : nullptr, x_out ? nbytes : 0u);
+  const Buf ox = buf_of(x_out ? x_out + tile.start : nullptr, x_out ? nbytes : 0u);
+  for (int w0 = wave_id() * kU; w0 < nw; w0 += kSWaves * kU)
+    correct_words<true, kMode == 0>(w0, rw, c, re, oe, rx, ox);
 }
 
 // ------------------------------------------------------------------ mismatch
@@ -1335,16 +1376,26 @@ hipError_t launch_weights(const DevLayout& lay, const float* x, const uint64_t* 
 }
 
 hipError_t launch_materialize(const DevLayout& lay, int K, int mode, const float* e,
-                              const uint64_t* signs, const float* scales, float* e_out,
+                              const uint64_t* signs, float* scales, float* e_out,
                               const float* e_srv, const float* x, const uint64_t* srv_signs,
-                              const float* srv_scales, float* e_srv_out, float* x_out,
+                              float* srv_scales, float* e_srv_out, float* x_out, bool fold,
                               hipStream_t s, const LaunchEvents& ev) {
   const int k_rows = e_out != nullptr ? K : 0;
   const int rows = k_rows + ((e_srv_out != nullptr || x_out != nullptr) ? 1 : 0);
   if (rows == 0) return hipSuccess;
   const dim3 grid((unsigned)(lay.n_tiles * rows));
-  SAEF_LAUNCH(k_materialize, grid, dim3(kBlock), 0, s, lay, k_rows, rows, mode, e, signs,
-                     scales, e_out, e_srv, x, srv_signs, srv_scales, e_srv_out, x_out);
+#define SAEF_MAT(M, F)                                                                       \
+  SAEF_LAUNCH((k_materialize<M, F>), grid, dim3(kSBlock), 0, s, lay, k_rows, rows, e, signs, \
+              scales, e_out, e_srv, x, srv_signs, srv_scales, e_srv_out, x_out)
+  if (fold) {
+    if (mode != 1 || !folds_scales(lay, K)) return hipErrorInvalidValue;  // never requested
+    SAEF_MAT(1, true);
+  } else if (mode == 1) {
+    SAEF_MAT(1, false);
+  } else {
+    SAEF_MAT(0, false);
+  }
+#undef SAEF_MAT
   return hipGetLastError();
 }
 

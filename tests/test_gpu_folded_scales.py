@@ -1,7 +1,8 @@
-"""The iteration whose aggregation adds up the worker partials itself (small
-layouts) against the single calls, which finalize the scales in a kernel of
-their own: messages and server state to the bit, at the edges of the rule (64
-and 65 tiles in a tensor, 2048 and 2049 tiles, 16 and 17 workers)."""
+"""Small layouts, where the aggregation and the in-place corrections add up
+the tile partials themselves, against the same tensors in a layout with one
+more tensor of 65 tiles, where kernels of their own write the scales: messages
+and states to the bit, at the edges of the rule (64 and 65 tiles in a tensor,
+2048 and 2049 tiles, 16 and 17 workers)."""
 import pytest
 import torch
 
@@ -19,31 +20,47 @@ SIZES = {
 }
 
 
-@pytest.mark.parametrize("sizes", SIZES)
-@pytest.mark.parametrize("K,mode", [(1, 1), (5, 0), (16, 1), (17, 1)])
-def test_round_equals_single_calls(sizes, K, mode):
-    print(f"[case] {sizes} K={K} mode={mode}", flush=True)
+def _run(call, sizes, K, mode, x0, g0, pad):
+    """State after two iterations of `sizes`, its layout longer by `pad`."""
     from paper_2008_05823_amd import saef as S
-    w = W.custom(SIZES[sizes], K=K, mode=mode, scale_range=(1e-3, 1.0), seed=K + 3)
+    w = W.custom(sizes + [pad] if pad else sizes, K=K, mode=mode)
     off, n, d_pad = w.layout()
     lay = S.Layout(off, n, d_pad, K)
-    rows = lambda r: torch.zeros((r, d_pad), device="cuda")
-    x = torch.from_numpy(W.initial_x(w)).cuda()
-    g = torch.from_numpy(W.gradients(w, 0)).cuda()
-    words = lambda r: torch.zeros((r, d_pad // 64), dtype=torch.int64, device="cuda")
+    d0, L0 = x0.numel(), len(sizes)
 
-    def state():
-        return {"e": rows(K), "e_srv": rows(1)[0], "x": x.clone(), "signs": words(K),
-                "scales": torch.full((K, w.L), -1.0, device="cuda"), "srv_signs": words(1)[0],
-                "srv_scales": torch.full((w.L,), -1.0, device="cuda")}
-    a, b = state(), state()
-    S.saef_round(lay, 0, 0, K, w.lr, mode, g, a["e"], a["e_srv"], a["x"], rows(K), a["signs"],
-                 a["scales"], a["srv_signs"], a["srv_scales"])
-    S.saef_compress(lay, K, w.lr, g, b["e"], b["signs"], b["scales"])
-    S.saef_aggregate(lay, K, mode, b["signs"], b["scales"], b["x"], b["e_srv"], b["srv_signs"],
-                     b["srv_scales"])
-    keys = ["signs", "scales"] + (["srv_signs", "srv_scales"] if mode else ["x"])
-    for k in keys:
-        assert torch.equal(a[k], b[k]), k
-    assert (a["scales"] >= 0).all()
+    def zeros(r, cols=d_pad, dtype=torch.float32):
+        return torch.zeros((r, cols), dtype=dtype, device="cuda")
+    s = {"e": zeros(K), "e_srv": zeros(1)[0], "x": zeros(1)[0], "xh": zeros(K),
+         "signs": zeros(K, d_pad // 64, torch.int64), "scales": zeros(K, w.L),
+         "srv_signs": zeros(1, d_pad // 64, torch.int64)[0], "srv_scales": zeros(1, w.L)[0]}
+    g = zeros(K)
+    s["x"][:d0], g[:, :d0] = x0, g0
+    msg = (s["signs"], s["scales"])
+    srv = (s["srv_signs"], s["srv_scales"])
+    for t in range(2):
+        if call == "round":
+            S.saef_round(lay, t, 0, K, w.lr, mode, g, s["e"], s["e_srv"], s["x"], s["xh"], *msg,
+                         *srv)
+        else:
+            S.saef_step_ahead(lay, K, s["x"], s["e"], s["xh"])
+            S.saef_compress(lay, K, w.lr, g, s["e"], *msg)
+            S.saef_aggregate(lay, K, mode, *msg, s["x"], s["e_srv"], *srv)
     assert S.saef_status(lay) == S.OK
+    cut = {"signs": d0 // 64, "srv_signs": d0 // 64, "scales": L0, "srv_scales": L0}
+    return {k: v[..., :cut.get(k, d0)].clone() for k, v in s.items()}
+
+
+@pytest.mark.parametrize("sizes", SIZES)
+@pytest.mark.parametrize("call,K,mode", [("round", 1, 1), ("round", 5, 0), ("round", 16, 1),
+                                         ("round", 17, 1), ("single", 3, 1), ("single", 16, 0),
+                                         ("single", 17, 1)])
+def test_folded_equals_finalized(sizes, call, K, mode):
+    print(f"[case] {sizes} {call} K={K} mode={mode}", flush=True)
+    w = W.custom(SIZES[sizes], K=K, mode=mode, scale_range=(1e-3, 1.0), seed=K + 3)
+    x0 = torch.from_numpy(W.initial_x(w)).cuda()
+    g0 = torch.from_numpy(W.gradients(w, 0)).cuda()
+    a = _run(call, SIZES[sizes], K, mode, x0, g0, 0)
+    b = _run(call, SIZES[sizes], K, mode, x0, g0, 65 * TILE)
+    for k in a:
+        assert torch.equal(a[k], b[k]), k
+    assert (a["scales"] > 0).all()
