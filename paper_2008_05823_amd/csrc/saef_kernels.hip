@@ -306,22 +306,21 @@ __device__ __forceinline__ void compress_tile(const DevLayout& lay, int k, int64
 
 // Grid: n_tiles * K workgroups; workgroup b handles worker b % K of tile
 // b / K.
+// At most 4 waves per SIMD: 12 workers of 15.2 M elements 358 us, 360 at 5,
+// 366 at 6, 374 uncapped (more streams in flight at once lose).
 template <bool kDecode>
-__global__ __launch_bounds__(kSBlock) void k_compress(DevLayout lay, int K, float lr, float mu,
-                                                     const float* __restrict__ g,
-                                                     float* __restrict__ m,
-                                                     float* __restrict__ e,
-                                                     uint64_t* __restrict__ signs,
-                                                     const float* __restrict__ scales) {
+__global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) void
+k_compress(DevLayout lay, int K, float lr, float mu, const float* __restrict__ g,
+           float* __restrict__ m, float* __restrict__ e, uint64_t* __restrict__ signs,
+           const float* __restrict__ scales) {
   const unsigned b = blockIdx.x;
   compress_tile<kDecode, false, kXhNone, kSWaves, kU>(lay, (int)(b % (unsigned)K),
                                                       b / (unsigned)K, lr, mu, g, m, e, signs,
                                                       scales, nullptr, nullptr, nullptr, nullptr);
 }
 
-// With momentum (three streams in, two out) at most 4 waves per SIMD: 665
-// against 674 us at 5 and 690 at 8 (resnet50, K = 8); the sign kernel is as
-// fast at 5 and 8 (400 us, 395 at 5).
+// With momentum (three streams in, two out): 665 us at 4 waves per SIMD, 674
+// at 5 and 690 at 8 (resnet50, K = 8).
 template <bool kDecode>
 __global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) void
 k_compress_mom(DevLayout lay, int K, float lr, float mu, const float* __restrict__ g,
