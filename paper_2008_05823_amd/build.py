@@ -14,10 +14,18 @@ ROOT = os.path.dirname(HERE)
 SOURCES = [os.path.join(HERE, "csrc", f) for f in ("saef_kernels.hip", "saef_topk.hip",
                                                           "saef_api.hip")]
 LIB = os.path.join(HERE, "libsaef.so")
-# the same library with 4096-element work tiles: the tile-size determinism
-# test runs the sign path with both builds and compares the bytes
+# the same library with larger work tiles: the tile-size determinism tests run
+# the sign path with each build and compare the bytes (16384: a tile whose exact
+# sums need more than 64 bits)
 TILE_VARIANT_ELEMS = 4096
-LIB_TILE_VARIANT = os.path.join(HERE, f"libsaef_tile{TILE_VARIANT_ELEMS}.so")
+TILE_VARIANT_LARGE = 16384
+
+
+def tile_variant_lib(elems: int) -> str:
+    return os.path.join(HERE, f"libsaef_tile{elems}.so")
+
+
+LIB_TILE_VARIANT = tile_variant_lib(TILE_VARIANT_ELEMS)
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -74,14 +82,15 @@ def build_client(out: str = CLIENT, lib: str = LIB) -> str:
     return out
 
 
-def build_tile_variant(verbose: bool = False) -> str:
-    """The library with SAEF_TILE_ELEMS = TILE_VARIANT_ELEMS (Top-K plans are
-    refused by that build; the sign path is complete)."""
-    return build(out=LIB_TILE_VARIANT, verbose=verbose,
-                 defines=(f"SAEF_TILE_ELEMS={TILE_VARIANT_ELEMS}",))
+def build_tile_variant(verbose: bool = False, elems: int = TILE_VARIANT_ELEMS) -> str:
+    """The library with SAEF_TILE_ELEMS = elems (Top-K plans are refused by
+    that build; the sign path is complete)."""
+    return build(out=tile_variant_lib(elems), verbose=verbose,
+                 defines=(f"SAEF_TILE_ELEMS={elems}",))
 
 
 if __name__ == "__main__":
     print(build(verbose=True))
     print(build_tile_variant())
+    print(build_tile_variant(elems=TILE_VARIANT_LARGE))
     print(build_client())

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "saef_internal.h"
 
 namespace saef {
@@ -116,16 +118,17 @@ __device__ __forceinline__ float in_vgpr(float v) {
 //   definition says (H = 0 there, a - H = a >= 0).
 // With at most 16 values per lane between flushes, -sum H 2^30 <= 2^53 and
 // |sum trunc((a - H) 2^80)| <= 16 2^49 = 2^53: both fp64 sums are exact.
-// They are then 64-bit integers h and q, S = h 2^50 + q, and a tile of at
-// most 2^13 elements keeps |h|, |q| <= 2^62, so lanes and waves are added as
-// two plain 64-bit sums; one thread per tile forms the 128-bit integer.
-static_assert(kTileElems <= 8192, "a tile's sums h and q fit 64-bit integers");
+// They are then integers h and q, S = h 2^50 + q, and a tile of at most 2^13
+// elements keeps |h|, |q| <= 2^62, so lanes and waves are added as two plain
+// 64-bit sums; one thread per tile forms the 128-bit integer.  In a build with
+// larger tiles h and q are 128-bit.
+using TileSum = std::conditional_t<(kTileElems <= 8192), int64_t, __int128>;
 struct ExactSum {
   double nh = 0.0;   // -sum of H
   double lq = 0.0;   // sum of trunc((a - H) 2^80)
   float mx = 0.0f;   // largest |v| seen (range check; NaN shows in nh)
   int terms = 0;     // values since the last flush (wave-uniform)
-  int64_t h = 0, q = 0;  // flushed sums
+  TileSum h = 0, q = 0;  // flushed sums
   bool bad = false;
 
   __device__ __forceinline__ void add(float v) {
@@ -185,6 +188,18 @@ __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
   v = dpp_add<0x118, 0xf>(v);  // row_shr:8: lane 15 of each row holds its sum
   v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
   v = dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+__device__ __forceinline__ int64_t wave_sum_tile(int64_t v) { return wave_sum_i64(v); }
+// The 128-bit form (in every lane).
+__device__ __forceinline__ __int128 wave_sum_tile(__int128 v) {
+#pragma unroll
+  for (int off = kWave / 2; off >= 1; off >>= 1) {
+    const u64 lo = __shfl_xor((unsigned long long)v, off);
+    const u64 hi = __shfl_xor((unsigned long long)((unsigned __int128)v >> 64), off);
+    v += (__int128)(((unsigned __int128)hi << 64) | lo);
+  }
   return v;
 }
 

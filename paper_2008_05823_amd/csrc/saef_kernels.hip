@@ -169,10 +169,10 @@ __device__ float scale_from_sum(u64 hi, u64 lo, int64_t n) {
 template <int kNW>
 __device__ __forceinline__ void block_partial(const DevLayout& lay, int row, int64_t tile,
                                               ExactSum& acc) {
-  __shared__ int64_t s_h[kNW];
-  __shared__ int64_t s_q[kNW];
+  __shared__ TileSum s_h[kNW];
+  __shared__ TileSum s_q[kNW];
   acc.finish();
-  const int64_t h = wave_sum_i64(acc.h), q = wave_sum_i64(acc.q);
+  const TileSum h = wave_sum_tile(acc.h), q = wave_sum_tile(acc.q);
   const int w = threadIdx.x / kWave;
   if (lane_id() == kWave - 1) {
     s_h[w] = h;
@@ -181,15 +181,15 @@ __device__ __forceinline__ void block_partial(const DevLayout& lay, int row, int
   if (__ballot(acc.bad) != 0ull && lane_id() == 0) atomicOr(lay.status, kStatusRange);
   lds_barrier();
   if (threadIdx.x != 0) return;
-  int64_t th = 0, tq = 0;
+  TileSum th = 0, tq = 0;
 #pragma unroll
   for (int i = 0; i < kNW; ++i) {
     th += s_h[i];
     tq += s_q[i];
   }
   // S = th 2^50 + tq (0 <= S < 2^127)
-  u64 lo = (u64)th << 50, hi = (u64)th >> 14;
-  add128(lo, hi, (u64)tq, tq < 0 ? ~0ull : 0ull);
+  u64 lo = (u64)th << 50, hi = (u64)(th >> 14);
+  add128(lo, hi, (u64)tq, sizeof(TileSum) > 8 ? (u64)((__int128)tq >> 64) : tq < 0 ? ~0ull : 0ull);
   u64* p = lay.part + ((int64_t)row * lay.n_tiles + tile) * 2;
   p[0] = lo;
   p[1] = hi;
