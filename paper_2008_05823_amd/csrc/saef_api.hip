@@ -1100,21 +1100,33 @@ int topk_begin_check(const saef_topk* plan, int64_t t, int64_t period, int32_t K
   return SAEF_OK;
 }
 
+// The argument checks of saef_topk_round_end, both halves of it.
+int topk_end_check(const saef_topk* plan, int64_t t, int64_t period, int32_t K, float lr,
+                   float mu, int32_t mode, const float* g, const float* m, const float* e,
+                   const float* e_srv, const float* x, const uint64_t* sel, const uint32_t* rank,
+                   const float* vals, const uint64_t* srv_sel, const uint32_t* srv_rank,
+                   const float* srv_vals) {
+  if (plan == nullptr || t < 0 || period < 0) return SAEF_EINVAL;
+  int rc = topk_compress_check(plan, K, lr, mu, g, m, e, sel, rank, vals);
+  if (rc == SAEF_OK)
+    rc = topk_aggregate_check(plan, K, mode, sel, rank, vals, nullptr, e_srv, srv_sel, srv_rank,
+                              srv_vals, x);
+  if (rc != SAEF_OK) return rc;
+  const size_t vb = (size_t)K * plan->layout->d_pad * sizeof(float);
+  const size_t xb = plan->layout->d_pad * sizeof(float);
+  return overlap(g, vb, x, xb) || overlap(e, vb, x, xb) ? SAEF_EINVAL : SAEF_OK;
+}
+
 // saef_topk_round_end; st: the step ahead taken along by the Delta pass.
 int topk_round_end(const saef_topk* plan, int64_t t, int64_t period, int32_t K, float lr,
                    float mu, int32_t mode, const float* g, float* m, float* e, float* e_srv,
                    float* x, uint64_t* sel, uint32_t* rank, float* vals, uint64_t* srv_sel,
                    uint32_t* srv_rank, float* srv_vals, const saef::TkStep& st,
                    hipStream_t stream) {
-  if (plan == nullptr) return SAEF_EINVAL;
-  if (t < 0 || period < 0) return SAEF_EINVAL;
+  int rc = topk_end_check(plan, t, period, K, lr, mu, mode, g, m, e, e_srv, x, sel, rank, vals,
+                          srv_sel, srv_rank, srv_vals);
+  if (rc != SAEF_OK) return rc;
   const saef_layout* layout = plan->layout;
-  if (layout == nullptr || K < 1 || K > layout->k_max) return SAEF_EINVAL;
-  const size_t vb = (size_t)K * layout->d_pad * sizeof(float);
-  const size_t xb = layout->d_pad * sizeof(float);
-  if (g != nullptr && x != nullptr && e != nullptr &&
-      (overlap(g, vb, x, xb) || overlap(e, vb, x, xb)))
-    return SAEF_EINVAL;
   // e is pending unless t = 0 or this iteration's averaging wrote it plain;
   // the compression leaves its own kept elements pending
   const bool averaging = period > 0 && (t + 1) % period == 0;
@@ -1122,11 +1134,6 @@ int topk_round_end(const saef_topk* plan, int64_t t, int64_t period, int32_t K, 
   if (plan->pipe.size() >= 2 && layout->dev.n_tiles * K >= saef::kTkSplitTiles) {
     // pipelined over the plan's parts: one timed span (kind 1) from the
     // first Delta pass to the last kernel on the caller's stream
-    int rc = topk_compress_check(plan, K, lr, mu, g, m, e, sel, rank, vals);
-    if (rc == SAEF_OK)
-      rc = topk_aggregate_check(plan, K, mode, sel, rank, vals, nullptr, e_srv, srv_sel,
-                                srv_rank, srv_vals, x);
-    if (rc != SAEF_OK) return rc;
     return hip_rc(timed(layout, 1, [&](const saef::LaunchEvents& ev) {
       return saef::launch_topk_round_end(layout->dev, call_dev(plan), plan->pipe.data(),
                                          (int)plan->pipe.size(), K, lr, mu, mode, g, m, e, sel,
@@ -1134,7 +1141,7 @@ int topk_round_end(const saef_topk* plan, int64_t t, int64_t period, int32_t K, 
                                          x, st, stream, plan->side, ev);
     }));
   }
-  int rc = topk_compress(plan, K, lr, mu, g, m, e, sel, rank, vals, pend_in, true, st, stream);
+  rc = topk_compress(plan, K, lr, mu, g, m, e, sel, rank, vals, pend_in, true, st, stream);
   if (rc != SAEF_OK) return rc;
   return saef_topk_aggregate(plan, K, mode, sel, rank, vals, nullptr, e_srv, srv_sel, srv_rank,
                              srv_vals, x, stream);
@@ -1210,13 +1217,16 @@ int saef_topk_round(const saef_topk* plan, int64_t t, int64_t period, int32_t K,
                             {vals, (size_t)K * plan->total_keep * sizeof(float)},
                             {srv_sel, W * 8}, {srv_rank, W * 4},
                             {srv_vals, (size_t)plan->total_keep * sizeof(float)}});
-  if (apart && (period <= 0 || (t + 1) % period != 0)) {
-    rc = topk_begin_check(plan, t, period, K, mode, SAEF_VARIANT_SAEF, e, sel, e_srv, x, xh,
-                          nullptr);
-    if (rc != SAEF_OK) return rc;
+  // both halves' arguments are checked before anything is enqueued
+  rc = topk_begin_check(plan, t, period, K, mode, SAEF_VARIANT_SAEF, e, sel, e_srv, x, xh,
+                        nullptr);
+  if (rc == SAEF_OK)
+    rc = topk_end_check(plan, t, period, K, lr, mu, mode, g, m, e, e_srv, x, sel, rank, vals,
+                        srv_sel, srv_rank, srv_vals);
+  if (rc != SAEF_OK) return rc;
+  if (apart && (period == 0 || (t + 1) % period != 0))
     return topk_round_end(plan, t, period, K, lr, mu, mode, g, m, e, e_srv, x, sel, rank, vals,
                           srv_sel, srv_rank, srv_vals, saef::TkStep{x, xh}, stream);
-  }
   rc = saef_topk_round_begin(plan, t, period, K, mode, SAEF_VARIANT_SAEF, e, sel, e_srv, x, xh,
                              nullptr, stream);
   if (rc != SAEF_OK) return rc;
