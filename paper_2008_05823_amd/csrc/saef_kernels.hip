@@ -221,6 +221,8 @@ __device__ __forceinline__ void compress_words(int w0, int nw, int count, float 
   float gv[kN], ev[kN], mv[kN], xv[kN];
   u64 mx[kN];
   uint32_t nw_lo = 0, nw_hi = 0;  // lane u: new word u
+  // k_compress<true>'s words one by one, as they are formed (measured there)
+  constexpr bool kWordwise = kDecode && !kMom && kXh == kXhNone;
   // the old words first (every element waits for them; the scheduling
   // barrier keeps the compiler from moving the load behind the others)
   const u64 ow = kDecode ? buf_ld_words(rs, w0, kN) : 0ull;
@@ -253,13 +255,17 @@ __device__ __forceinline__ void compress_words(int w0, int nw, int count, float 
     float p = __builtin_fmaf(lr, step, ev2);
     if (!kFull) p = ok ? p : 0.0f;
     const u64 word = __ballot(ok && p >= 0.0f);
-    nw_lo = lane == u ? (uint32_t)word : nw_lo;
-    nw_hi = lane == u ? (uint32_t)(word >> 32) : nw_hi;
+    if (kWordwise) {
+      if (lane == 0) buf_st_word(rs, (uint32_t)(w0 + u) * 8u, word);
+    } else {
+      nw_lo = lane == u ? (uint32_t)word : nw_lo;
+      nw_hi = lane == u ? (uint32_t)(word >> 32) : nw_hi;
+    }
     acc.add(p);
     buf_st(re, off, p);
   }
   // the pass's words in one store (lane u: word u; past the tile: dropped)
-  if (lane < kN) buf_st_lane_word(rs, (uint32_t)(w0 + lane) * 8u, nw_lo, nw_hi);
+  if (!kWordwise && lane < kN) buf_st_lane_word(rs, (uint32_t)(w0 + lane) * 8u, nw_lo, nw_hi);
 }
 
 // Worker k's tile ti by a workgroup of kNW waves of kN words per pass: wave
@@ -306,10 +312,17 @@ __device__ __forceinline__ void compress_tile(const DevLayout& lay, int k, int64
 
 // Grid: n_tiles * K workgroups; workgroup b handles worker b % K of tile
 // b / K.
-// At most 4 waves per SIMD: 12 workers of 15.2 M elements 358 us, 360 at 5,
-// 366 at 6, 374 uncapped (more streams in flight at once lose).
+// Plain errors (kDecode false, the single calls): at most 4 waves per SIMD
+// (more streams in flight at once lose: the call on 12 workers of 15.2 M
+// elements 600-605 us, 606-610 at 5 or 6 and 619 at 8, on 3 of 60 M 577 against
+// 606) and the words of a pass in one store (3 of 60 M: 632 word by word).
+// Pending errors (the halves): uncapped and word by word; the load of the old
+// words, first in a pass, leaves fewer streams in flight by itself.  Per pair
+// of halves, 3 workers of 60 M 508 us, 526 with one store per pass and 519 with
+// that and 4 waves; 4 of 30 M 324, 330 and 329; 5 of 9 M 126.1, 127.5 and
+// 127.7; 5 of 3 M 50.1, 50.4 and 51.3; 8 of 25.6 M (resnet50) 479, 470, 474.
 template <bool kDecode>
-__global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) void
+__global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(1, kDecode ? 8 : 4))) void
 k_compress(DevLayout lay, int K, float lr, float mu, const float* __restrict__ g,
            float* __restrict__ m, float* __restrict__ e, uint64_t* __restrict__ signs,
            const float* __restrict__ scales) {
