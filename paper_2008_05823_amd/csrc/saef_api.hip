@@ -63,15 +63,12 @@ struct saef_topk {
   void* mem_rhist = nullptr;
   void* mem_tile_cand = nullptr;
   void* mem_seg = nullptr;
+  void* mem_arrived = nullptr;
   void* mem_large = nullptr;
   void* mem_spec = nullptr;
   // the side stream (default priority) and fork/join events of the worker
   // compression's two row groups and of the pipelined iteration end
   saef::TkStreams side{};
-  // Calls so far, up to kFreshCalls: on a fresh plan the histograms are not
-  // placed at the thresholds yet and a bin can hold most of a tensor, so the
-  // first calls narrow such bins (calls on one plan do not run concurrently)
-  int calls = 0;
   saef::TkPart all{};               // every tensor
   std::vector<saef::TkPart> pipe;   // the iteration end's parts (empty: not pipelined)
 };
@@ -206,20 +203,6 @@ int check_common(const saef_layout* lay, int32_t K) {
 bool f32_ok(const float* p) { return p != nullptr && aligned(p, 4); }
 bool u64_ok(const uint64_t* p) { return p != nullptr && aligned(p, 8); }
 
-// The device view of the plan for one call: a compression, an aggregation or
-// an iteration end.  At resnet50 K = 8 Top-1% the selection of a first call
-// took 20 ms without the narrowing.
-constexpr int kFreshCalls = 2;
-saef::TkDev call_dev(const saef_topk* plan) {
-  saef_topk* p = const_cast<saef_topk*>(plan);
-  saef::TkDev d = plan->dev;
-  if (p->calls < kFreshCalls) {
-    ++p->calls;
-    if (d.n_large > 0) d.refine = 1;
-  }
-  return d;
-}
-
 int hip_rc(hipError_t e) { return e == hipSuccess ? SAEF_OK : SAEF_EHIP; }
 
 void release_events(saef_layout* l) {
@@ -274,7 +257,8 @@ void free_topk(saef_topk* p) {
   if (p->side.join != nullptr) (void)hipEventDestroy(p->side.join);
   for (void* q : {p->mem_chunks, p->mem_tens, p->mem_groups, p->mem_sgroups, p->mem_thist,
                   p->mem_ghist, p->mem_sghist, p->mem_sel, p->mem_tile_cnt, p->mem_lcnt,
-                  p->mem_rhist, p->mem_tile_cand, p->mem_seg, p->mem_large, p->mem_cand, p->mem_spec})
+                  p->mem_rhist, p->mem_tile_cand, p->mem_seg, p->mem_arrived, p->mem_large,
+                  p->mem_cand, p->mem_spec})
     (void)hipFree(q);
   delete p;
 }
@@ -868,7 +852,12 @@ int saef_topk_create(const saef_layout* layout, const int64_t* keep, saef_topk**
   if (err == hipSuccess && rhist_bytes) err = hipMalloc(&p->mem_rhist, rhist_bytes);
   if (err == hipSuccess && rhist_bytes) err = hipMalloc(&p->mem_tile_cand, cnt_bytes);
   if (err == hipSuccess && !large.empty()) {
-    err = hipMalloc(&p->mem_seg, rows * groups.size() * saef::kTkGatherSplit * sizeof(uint32_t));
+    const size_t seg_bytes = rows * groups.size() * saef::kTkGatherSplit * sizeof(uint32_t);
+    err = hipMalloc(&p->mem_seg, seg_bytes);
+    if (err == hipSuccess) err = hipMemset(p->mem_seg, 0, seg_bytes);
+    const size_t arrived_bytes = rows * large.size() * sizeof(uint32_t);
+    if (err == hipSuccess) err = hipMalloc(&p->mem_arrived, arrived_bytes);
+    if (err == hipSuccess) err = hipMemset(p->mem_arrived, 0, arrived_bytes);
     if (err == hipSuccess) err = hipMalloc(&p->mem_large, large.size() * sizeof(int32_t));
     if (err == hipSuccess)
       err = hipMemcpy(p->mem_large, large.data(), large.size() * sizeof(int32_t),
@@ -926,9 +915,13 @@ int saef_topk_create(const saef_layout* layout, const int64_t* keep, saef_topk**
   d.n_sgroups = (int64_t)sgroups.size();
   d.tile_cand = static_cast<uint32_t*>(p->mem_tile_cand);
   d.seg = static_cast<uint32_t*>(p->mem_seg);
+  d.arrived = static_cast<uint32_t*>(p->mem_arrived);
   d.large = static_cast<const int32_t*>(p->mem_large);
   d.n_large = (int64_t)large.size();
-  d.refine = sgroups.empty() ? 0 : 1;
+  d.levels = sgroups.empty() ? 0 : saef::kTkRefineLevels;
+  for (int32_t l = 0; l < L; ++l)
+    if (tens[l].ngroups == 0 && layout->tensors[l].ntiles > saef::kTkPickTiles) d.pick_wide = 1;
+  d.alone = layout->dev.n_tiles * layout->k_max < saef::kTkSplitTiles ? 1 : 0;
   d.total_keep = p->total_keep;
   *out = p;
   return SAEF_OK;
@@ -982,7 +975,7 @@ int topk_compress(const saef_topk* plan, int32_t K, float lr, float mu, const fl
   if (rc != SAEF_OK) return rc;
   const saef_layout* layout = plan->layout;
   return hip_rc(timed(layout, 1, [&](const saef::LaunchEvents& ev) {
-    return saef::launch_topk_compress(layout->dev, call_dev(plan), plan->all, K, lr, mu, g, m, e, sel,
+    return saef::launch_topk_compress(layout->dev, plan->dev, plan->all, K, lr, mu, g, m, e, sel,
                                       rank, vals, pend_in, pend_out, st, stream,
                                       layout->dev.n_tiles * K >= saef::kTkSplitTiles
                                           ? plan->side
@@ -1054,7 +1047,7 @@ int saef_topk_aggregate(const saef_topk* plan, int32_t K, int32_t mode, const ui
   if (rc != SAEF_OK) return rc;
   const saef_layout* layout = plan->layout;
   return hip_rc(timed(layout, 3, [&](const saef::LaunchEvents& ev) {
-    return saef::launch_topk_aggregate(layout->dev, call_dev(plan), plan->all, K, mode, sel, rank,
+    return saef::launch_topk_aggregate(layout->dev, plan->dev, plan->all, K, mode, sel, rank,
                                        vals, avg, e_srv, srv_sel, srv_rank, srv_vals, x, stream,
                                        ev);
   }));
@@ -1135,7 +1128,7 @@ int topk_round_end(const saef_topk* plan, int64_t t, int64_t period, int32_t K, 
     // pipelined over the plan's parts: one timed span (kind 1) from the
     // first Delta pass to the last kernel on the caller's stream
     return hip_rc(timed(layout, 1, [&](const saef::LaunchEvents& ev) {
-      return saef::launch_topk_round_end(layout->dev, call_dev(plan), plan->pipe.data(),
+      return saef::launch_topk_round_end(layout->dev, plan->dev, plan->pipe.data(),
                                          (int)plan->pipe.size(), K, lr, mu, mode, g, m, e, sel,
                                          rank, vals, pend_in, e_srv, srv_sel, srv_rank, srv_vals,
                                          x, st, stream, plan->side, ev);

@@ -8,28 +8,42 @@ namespace saef {
 
 // Pass-1 histogram of the key |v| around the threshold tau of the previous
 // call: a near range of kTkNear bins of 1/512 binade from kTkSpecMargin (1/32
-// binade) under tau to 0.19 binades above it; below it kTkMidB and above it
-// kTkMidA bins of 1/64 binade, then on each side kTkFar bins of a binade, the
-// last one open.  The bins only decide how many elements become
-// candidates; the kept set is exact wherever the threshold falls.  Under error
-// feedback the residual piles up at tau; tau rises by 0.01-0.2 binades a call
-// (resnet50) and falls by 0.5-1.1 when the errors are averaged.  A bin of 1/64
-// binade at tau (64 in each of four binades before) held 5000-7000 of the
-// 2.36 M elements of the largest tensors at Top-1% and 17000-29000 at
-// Top-10%, and selecting among them was most of the selection's time; 160 bins
-// of 1/2048 binade, or 224 of 1/512 with coarse ones below, miss the moves
+// binade) under tau to 0.19 binades above it; below it kTkMidB bins of 1/64
+// binade (to 1.16 binades under tau), then kTkFarB of 1/8 (to 3.66); above it
+// kTkMidA bins of 1/64 (to 0.81 binades over tau), then kTkFarA of 1/8 (to
+// 2.06); on each side one open bin.  The bins only decide how many elements
+// become candidates; the kept set is exact wherever the threshold falls.  Under
+// error feedback the residual piles up at tau; tau rises by 0.01-0.2 binades a
+// call (resnet50) and falls by 0.5-1.1 when the errors are averaged (up to 2
+// for 16 independent ones).  A bin of 1/64 binade at tau held 5000-7000 of the
+// 2.36 M elements of the largest tensors at Top-1% and 17000-29000 at Top-10%,
+// and selecting among them was most of the selection's time; 160 bins of
+// 1/2048 binade, or 224 of 1/512 with coarse ones below, miss the moves
 // (Top-10% 1195 and 1154 against 1110 us).
 constexpr int kTkSubShift = 14;                // near bin width: 2^14 keys
 constexpr int kTkNear = 112;                   // near bins
 constexpr int kTkMidShift = 17;                // mid bin width: 2^17 keys
 constexpr int kTkMidB = 72;                    // below: 1.125 binades
 constexpr int kTkMidA = 40;                    // above: 0.625 binades
-constexpr int kTkFar = 8;                      // bins of a binade beyond, on each side
-constexpr int kTkBelow = kTkMidB + kTkFar;     // bins below the near range
-constexpr int kTkHist = kTkBelow + kTkNear + kTkMidA + kTkFar;
+constexpr int kTkFarShift = 20;                // far bin width: 2^20 keys
+constexpr int kTkFarB = 20;                    // 2.5 binades
+constexpr int kTkFarA = 10;                    // 1.25 binades
+constexpr int kTkBelow = kTkMidB + kTkFarB + 1;  // bins below the near range
+constexpr int kTkAbove = kTkMidA + kTkFarA + 1;  // bins above it
+constexpr int kTkHist = kTkBelow + kTkNear + kTkAbove;
 constexpr int kTkHistPad = 256;                // 16-bit counts per tile
 constexpr int kTkGroup = 64;      // tile histograms (or group sums) one sum workgroup adds
 constexpr int kTkSmall = 16;      // most tiles of a small tensor in a plan with more than a group
+// The pick has 1024 threads where some small tensor has more than kTkPickTiles
+// tiles (a wave takes them one after another), and in a plan that is never
+// split where at most kTkWidePairs (row, tensor)s are picked, a workgroup for
+// each CU: 30 tensors of 18 tiles, K = 8, Top-20% 134 us per iteration against
+// 157 with 256 threads, one of 16 tiles, K = 2, 75.5 against 96.4, one of 32
+// 90 against 131.  With more pairs their waves are in each other's way
+// (resnet56, 1336 pairs: 128 against 97 us), and beside a Delta pass they wait
+// for slots (resnet50 Top-1%: 851 against 819).
+constexpr int kTkPickTiles = 20;
+constexpr int kTkWidePairs = 256;
 // Fewest (tile, worker) pairs of a call that is split over the side stream: a
 // smaller one streams its Delta in a few microseconds, and a second chain of
 // kernels costs more than it hides (resnet56 K = 8, 4160 pairs: 120 us per
@@ -54,15 +68,17 @@ constexpr int kTkChunk = 8192;
 // their count (kTkSpecNone when the tile had more); the server aggregation
 // does the same for the server row.  When the bin b1 that this call's
 // histogram picks lies at or above that bound, the list holds every element
-// the selection needs and the tile's Delta is not read again.  (Under error
-// feedback the threshold mostly rises from call to call, and the elements
-// just below it pile up: at 1% kept the lists hold about 3% of the elements.)
+// the selection needs and the tile's Delta is not read again; otherwise the
+// selection reads Delta and writes the list again down to that bin, for the emit.
+// (Under error feedback the threshold mostly rises from call to call, and the
+// elements just below it pile up: at 1% kept the lists hold about 3% of the
+// elements.)
 constexpr int kTkSpecCap = 512;
 constexpr uint32_t kTkSpecNone = 0xFFFFu;
 constexpr uint32_t kTkSpecMargin = 1u << 18;
-static_assert(kTkMidB >= 1 << (23 - kTkMidShift) && kTkMidB < 2 << (23 - kTkMidShift) &&
-                  kTkMidA < 1 << (23 - kTkMidShift),
-              "the far bins start in the second binade below and the first above");
+static_assert(kTkMidB % (1 << (kTkFarShift - kTkMidShift)) == 0 &&
+                  kTkMidA % (1 << (kTkFarShift - kTkMidShift)) == 0,
+              "the mid bins of a side are whole far bins");
 constexpr int kTkSpecMaxShare = 8;  // lists when k_l * 8 <= n_l
 // Dynamic LDS the Delta pass requests and does not use: with its own 1 KB
 // it keeps at most 5 of its workgroups on a CU (160 KB of LDS), so the
@@ -106,7 +122,8 @@ struct TkTensor {
   int64_t keep;         // k_l
   int32_t first_chunk;  // server chunks
   int32_t nchunks;
-  int32_t first_group;  // tile groups, for a tensor of more than kTkGroup tiles
+  int32_t first_group;  // tile groups, for a large tensor (more than kTkGroup tiles; more than
+                        // kTkSmall in a plan that has one of more than kTkGroup)
   int32_t ngroups;      // 0 otherwise
   int32_t first_sgroup;  // super-groups, when ngroups > kTkGroup (a huge tensor)
   int32_t nsgroups;      // 0 otherwise
@@ -119,14 +136,15 @@ struct TkTensor {
 // elements equal to tau, and the histogram's near range placed at tau.  Set by
 // the pick: the lists' bound of this call, and for a large tensor the key
 // range [lo, up) of the candidates (the bin that holds the k-th largest key),
-// how many of them to take, and whether the refine narrows the range first.
+// how many of them to take, and whether there are many of them.
 struct TkSel {
   uint32_t tau;
   uint32_t win;     // first key of the histogram's near range
-  uint32_t floor;   // the lists hold every element with a key >= floor (2^31: no lists)
+  uint32_t floor;   // the lists hold every element with a key >= floor (2^31: no lists); once the
+                    // gather has been over them, at most its lo
   uint32_t lists;   // 1: the rows of this tensor keep speculative lists (set at creation)
   uint32_t lo, up;
-  uint32_t coarse;  // 1: the refine's histogram narrows [lo, up)
+  uint32_t coarse;  // 1: [lo, up) is full: its keys are counted into rhist
   uint32_t pad;
   int64_t need;
   int64_t iota;     // elements equal to tau with index <= iota are kept
@@ -156,9 +174,10 @@ struct TkDev {
   TkSel* sel;          // [rows][L]
   uint32_t* tile_cnt;  // [rows][n_tiles] kept per tile, then the exclusive prefix
   uint32_t* lcnt;      // [rows][n_tiles] entries in the tile's speculative list, or kTkSpecNone
-  uint32_t* rhist;     // [rows][n_large][kTkRefineLevels][kTkBins] histograms of the refine
-  uint32_t* tile_cand;  // [rows][n_tiles] candidates of the tile (calls that refine)
+  uint32_t* rhist;     // [rows][n_large][kTkRefineLevels][kTkBins] histograms of full bins
+  uint32_t* tile_cand;  // [rows][n_tiles] candidates of the tile (full bins)
   uint32_t* seg;       // [rows][n_groups * kTkGatherSplit] candidates of each gather workgroup
+  uint32_t* arrived;   // [rows][n_large] workgroups of the select that gathered; 0 between calls
   const int32_t* large;  // [n_large] the large tensors, in order
   // [rows][d_pad] candidate slots: (row, tensor) at the tensor's offset, those
   // of a gather workgroup at its first tile
@@ -167,10 +186,13 @@ struct TkDev {
   int64_t n_chunks;
   int64_t n_groups;
   int64_t n_sgroups;
-  int64_t n_large;     // large tensors (more than kTkGroup tiles)
+  int64_t n_large;     // large tensors (those with tile groups)
   int64_t total_keep;
-  int32_t refine;      // 1: full candidate bins are narrowed (some tensor has super-groups, or
-                       // one of the plan's first calls)
+  int32_t levels;      // times the refine may narrow a full bin: kTkRefineLevels when some
+                       // tensor has super-groups, else 0 (no refine: the gather counts and
+                       // the select's launch gathers)
+  int32_t pick_wide;   // 1: some small tensor has more than kTkPickTiles tiles
+  int32_t alone;       // 1: no call of the plan is split over the side stream
   int32_t pad;
 };
 

@@ -16,14 +16,13 @@
 //              k-th largest key.  A small tensor (up to 64 tiles; up to 16 in
 //              a plan that has larger ones) it selects as a whole, so its
 //              selection is this one kernel;
-//   refine     (plans with a tensor of more than 4096 tiles, and a plan's
-//              first calls) a bin b1 with many elements is narrowed to a
-//              sub-range of it, 11 key bits at a time, by the workgroups of
-//              all tiles;
+//   refine     (plans with a tensor of more than 4096 tiles) a bin b1 with
+//              many elements is narrowed to a sub-range of it, 11 key bits at
+//              a time, by the workgroups of all tiles;
 //   gather     the elements of b1 (the candidates) of large tensors, tile by
 //              tile, and each tile's count of elements above b1: from the
 //              tile's list when its bound lies at or below b1, else from one
-//              more read of Delta;
+//              more read of Delta (a full b1 is narrowed by 11 key bits first);
 //   select     a workgroup per (row, large tensor) finds, among the
 //              candidates only, the threshold key tau and the last kept index
 //              iota of the elements equal to tau, and turns the tiles' counts
@@ -62,6 +61,10 @@ constexpr int kBufWord3 = 0x00020000;
 
 __device__ __forceinline__ uint32_t key_of(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
 
+// The mid bins of a side, in far bins.
+constexpr int kMidFarB = kTkMidB >> (kTkFarShift - kTkMidShift);
+constexpr int kMidFarA = kTkMidA >> (kTkFarShift - kTkMidShift);
+
 // Pass-1 bin of a key for the near range [win, win + kTkNear bins).  Bins
 // order like the keys.
 __device__ __forceinline__ uint32_t hist_bin(uint32_t key, uint32_t win) {
@@ -70,9 +73,11 @@ __device__ __forceinline__ uint32_t hist_bin(uint32_t key, uint32_t win) {
   const uint32_t xb = ~(uint32_t)s, xa = (uint32_t)s - ((uint32_t)kTkNear << kTkSubShift);
   const uint32_t mb = xb >> kTkMidShift, ma = xa >> kTkMidShift;
   const uint32_t gb = mb < (uint32_t)kTkMidB
-                          ? mb : (uint32_t)(kTkMidB - 1) + min(xb >> 23, (uint32_t)kTkFar);
+                          ? mb : min((xb >> kTkFarShift) + (uint32_t)(kTkMidB - kMidFarB),
+                                     (uint32_t)(kTkBelow - 1));
   const uint32_t ga = ma < (uint32_t)kTkMidA
-                          ? ma : (uint32_t)kTkMidA + min(xa >> 23, (uint32_t)(kTkFar - 1));
+                          ? ma : min((xa >> kTkFarShift) + (uint32_t)(kTkMidA - kMidFarA),
+                                     (uint32_t)(kTkAbove - 1));
   const uint32_t side = s < 0 ? (uint32_t)(kTkBelow - 1) - gb : (uint32_t)(kTkBelow + kTkNear) + ga;
   const uint32_t d = (uint32_t)s >> kTkSubShift;
   return d < (uint32_t)kTkNear ? (uint32_t)kTkBelow + d : side;
@@ -135,6 +140,10 @@ __device__ __forceinline__ void delta_words(const DeltaLoads<kMom, kPend, kXh>& 
                                             uint32_t (&bits)[kTkU], u64 (&lm)[kTkU], bool& bad) {
   const int lane = lane_id();
   const uint32_t off0 = (uint32_t)(w0 * 64 + lane) * 4u;
+  // keys in the open low bin, counted without LDS atomics: most of them when the
+  // values fall (resnet50 K = 8 Top-1%, all divided by 16: 1340 us a call before,
+  // 1070 now)
+  uint32_t low = 0;
 #pragma unroll
   for (int u = 0; u < kTkU; ++u) {
     const uint32_t off = off0 + 256u * u;
@@ -152,10 +161,13 @@ __device__ __forceinline__ void delta_words(const DeltaLoads<kMom, kPend, kXh>& 
     bits[u] = __float_as_uint(p);
     lm[u] = __ballot(ok && key >= lo);
     buf_st(re, off, p);
+    const uint32_t bin = hist_bin(key, win);
+    low += (uint32_t)__popcll(__ballot(ok && bin == 0u));
     if (!ok) continue;
     bad |= key >= kFiniteLimit;
-    atomicAdd(&h[hist_bin(key, win)], 1u);
+    if (bin != 0u) atomicAdd(&h[bin], 1u);
   }
+  if (low != 0u && lane == 0) atomicAdd(&h[0], low);
 }
 
 // Grid: run_padded_tiles(p.t1 - p.t0) * R workgroups; workgroup b handles one
@@ -323,7 +335,7 @@ __global__ __launch_bounds__(kBlock) void k_tk_sum(DevLayout lay, TkDev tk, TkPa
 // ------------------------------------------------------------------ block helpers
 // Exclusive prefix sum of v over the workgroup (threads in order); *total
 // receives the sum.  s must hold blockDim.x / 64 entries.
-__device__ uint32_t block_excl_scan(uint32_t v, uint32_t* s, uint32_t* total) {
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* s, uint32_t* total) {
   const int lane = lane_id();
   const int wave = threadIdx.x / kWave;
   const int nwaves = blockDim.x / kWave;
@@ -349,8 +361,9 @@ __device__ uint32_t block_excl_scan(uint32_t v, uint32_t* s, uint32_t* total) {
 // counted from the top (kTop) or from the bottom (1 <= need <= total).
 // Returns to every thread the bin, how many to take inside it and its count.
 template <bool kTop>
-__device__ void find_bin(const uint32_t* h, int nb, int64_t need, uint32_t* s_scan,
-                         uint32_t* s_res, uint32_t& bin, int64_t& left, uint32_t& count) {
+__device__ __forceinline__ void find_bin(const uint32_t* h, int nb, int64_t need,
+                                         uint32_t* s_scan, uint32_t* s_res, uint32_t& bin,
+                                         int64_t& left, uint32_t& count) {
   const int per = (nb + (int)blockDim.x - 1) / (int)blockDim.x;
   if (threadIdx.x == 0) {  // defined result even if need exceeded the total
     s_res[0] = 0;
@@ -396,14 +409,20 @@ __device__ void find_bin(const uint32_t* h, int nb, int64_t need, uint32_t* s_sc
 // each tile's first rank follows from its counts.  The order in which
 // candidates are collected does not matter.
 constexpr int kPick = 256;      // threads of the pick
+constexpr int kPickWide = 1024;  // or this many (kTkPickTiles, kTkWidePairs)
 constexpr int kSelect = 512;    // threads of the select of large tensors
 constexpr int kPickCand = 1024;  // candidates the pick keeps in LDS
 constexpr int kSelKeys = 4096;  // candidates whose keys the select keeps in LDS
 constexpr int kSelTiles = 2048; // tiles whose counts the select's LDS holds (packed 16-bit)
-constexpr int kRefineCand = 4096;  // more candidates than this are narrowed (refine)
+// A bin with more candidates is full and narrowed first: where there is a refine
+// anyway (one tensor of 2^24: 440 us per iteration, 478 at 16384), and else
+// (resnet50 K = 8 Top-10%: 1054 us, 1118 at 4096).
+constexpr int kRefineCand = 4096;
+constexpr int kFullCand = 16384;
 constexpr int kRefineLevels = kTkRefineLevels;
 constexpr int kGatherSplit = kTkGatherSplit;
 constexpr int kGatherTiles = kTkGroup / kGatherSplit;  // tiles per gather workgroup
+constexpr int kGatherWide = kGatherTiles * kWave;      // a wave per tile
 static_assert(kTkTileElems < 65536 / 2, "a tile's counts fit 16 bits");
 
 // The smallest key of bin b for the near range at win (hist_bin's layout; a
@@ -416,15 +435,21 @@ __device__ __forceinline__ uint32_t bin_floor(uint32_t b, uint32_t win) {
     // bin g of the side: distances up to (below) the first of bin g + 1
     const int64_t g = kTkBelow - 1 - (int64_t)b;
     if (g == kTkBelow - 1) return 0u;
-    f = (int64_t)win - (g < kTkMidB ? (g + 1) << kTkMidShift : (g - kTkMidB + 2) << 23);
+    f = (int64_t)win - (g < kTkMidB ? (g + 1) << kTkMidShift
+                                    : (g - kTkMidB + kMidFarB + 1) << kTkFarShift);
   } else if (b < (uint32_t)(kTkBelow + kTkNear)) {
     f = (int64_t)win + ((int64_t)(b - kTkBelow) << kTkSubShift);
   } else {
     const int64_t g = (int64_t)b - (kTkBelow + kTkNear);
     f = (int64_t)win + ((int64_t)kTkNear << kTkSubShift) +
-        (g <= kTkMidA ? g << kTkMidShift : (g - kTkMidA) << 23);
+        (g <= kTkMidA ? g << kTkMidShift : (g - kTkMidA + kMidFarA) << kTkFarShift);
   }
   return f <= 0 ? 0u : f < 0x80000000ll ? (uint32_t)f : 0x80000000u;
+}
+
+// Bits of the indexes 0 .. n - 1 (1 <= n <= 2^28).
+__device__ __forceinline__ int index_bits(int64_t n) {
+  return n > 1 ? 32 - __builtin_clz((uint32_t)(n - 1)) : 0;
 }
 
 // Bits of the offsets 0 .. up - lo - 1 of the keys in [lo, up).
@@ -477,6 +502,26 @@ __device__ __forceinline__ int nth_set_bit(u64 w, uint32_t r) {
   return pos;
 }
 
+// Counts each ok lane's bin into the LDS histogram h.  The server's errors
+// crowd a few bins (most of them keep last call's residual, and its binade),
+// and one 64-lane LDS atomic into one address is serialized lane by lane: the
+// lanes that share the first lane's bin add their count with one atomic, the
+// others theirs one by one.  At resnet50 K = 8 Top-1% (union gathers) that
+// took the iteration from 0.974-0.977 to 0.965-0.968 ms; repeating it for a
+// second bin gave 0.976, a third 0.987-0.990 ms.
+__device__ __forceinline__ void hist_add(uint32_t* h, uint32_t bin, bool ok) {
+  const int lane = lane_id();
+  const u64 todo = __ballot(ok);
+  if (todo == 0ull) return;  // wave-uniform
+  const int lead = __builtin_ctzll(todo);
+  const uint32_t lb = (uint32_t)__builtin_amdgcn_readlane((int)bin, lead);
+  const u64 same = __ballot(bin == lb) & todo;
+  if (lane == lead)
+    atomicAdd(&h[lb], (uint32_t)__popcll(same));
+  else if (((todo & ~same) >> lane) & 1ull)
+    atomicAdd(&h[bin], 1u);
+}
+
 // Where a wave's candidates go: the LDS buffer lds (in_lds), else glb; both
 // filled through the LDS count *fill.
 struct CandSink {
@@ -515,13 +560,15 @@ struct TileCounts {
 // the elements in [lo, up) go to the sink; returns in lane j the counts of
 // tile t0 + j.  n: lane j holds the tile's list count (kTkSpecNone: no usable
 // list; 0 past tend).  Taken from the lists (kC chunks of 64 entries of the
-// kT tiles in flight together), else from Delta (kW words' loads in flight).
+// kT tiles in flight together), else from Delta (kW words' loads in flight),
+// and then, with relist, the tile's list is written again down to lo (in index
+// order, when it fits), for the emit, which would read Delta once more.
 template <int kT, int kC, int kW>
 __device__ __forceinline__ TileCounts scan_tiles(const CandSink& sink, const DevLayout& lay,
                                                  const TkDev& tk, const TensorInfo& ten, int row,
                                                  int t0, uint32_t n,
                                                  const float* __restrict__ dr, uint32_t lo,
-                                                 uint32_t up) {
+                                                 uint32_t up, bool relist) {
   static_assert(kTileWords % kW == 0, "whole passes over a tile");
   const int lane = lane_id();
   const int64_t tile0 = (int64_t)row * lay.n_tiles + ten.first_tile + t0;
@@ -579,8 +626,10 @@ __device__ __forceinline__ TileCounts scan_tiles(const CandSink& sink, const Dev
     const int64_t first = (int64_t)(t0 + j) * kTkTileElems;
     const int count = (int)min((int64_t)kTkTileElems, ten.n - first);
     const Buf rd = buf_of(dr + ten.off + first, (uint32_t)count * 4u);
-    uint32_t above = 0, inside = 0;
+    uint32_t above = 0, inside = 0, listed = 0;
+    u64* list = tk.spec + (tile0 + j) * kTkSpecCap;
     const bool whole = count == kTkTileElems;  // wave-uniform
+#pragma unroll 1
     for (int w = 0; w < kTileWords; w += kW) {
       float v[kW];
       u64 m[kW];
@@ -597,6 +646,14 @@ __device__ __forceinline__ TileCounts scan_tiles(const CandSink& sink, const Dev
         m[u] = gl & ~gu;
         above += (uint32_t)__popcll(gu);
         total += (uint32_t)__popcll(m[u]);
+        if (relist && gl != 0ull) {  // wave-uniform
+          const uint32_t pos =
+              listed + __builtin_amdgcn_mbcnt_hi((uint32_t)(gl >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)gl, 0u));
+          if (((gl >> lane) & 1ull) && pos < (uint32_t)kTkSpecCap)
+            list[pos] = (u64)__float_as_uint(v[u]) | ((u64)((w + u) * kWave + lane) << 32);
+          listed += (uint32_t)__popcll(gl);
+        }
       }
       if (total == 0u) continue;  // wave-uniform
       inside += total;
@@ -608,10 +665,48 @@ __device__ __forceinline__ TileCounts scan_tiles(const CandSink& sink, const Dev
         base += (uint32_t)__popcll(m[u]);
       }
     }
+    if (relist && lane == 0)
+      tk.lcnt[tile0 + j] = listed <= (uint32_t)kTkSpecCap ? listed : kTkSpecNone;
     sure += lane == j ? above : 0u;
     within += lane == j ? inside : 0u;
   }
   return TileCounts{sure, within};
+}
+
+// Counts (key - lo) >> sh of the elements in [lo, up) of one tile (number tile
+// of its tensor, ti in the scratch) into the LDS histogram h, by one wave: from
+// its list of n entries, or (kTkSpecNone) from Delta, kW words in flight.
+template <int kW>
+__device__ __forceinline__ void tile_range_hist(uint32_t* h, const TkDev& tk,
+                                                const TensorInfo& ten, int64_t ti, int tile,
+                                                uint32_t n, const float* __restrict__ dr,
+                                                uint32_t lo, uint32_t up, int sh) {
+  const int lane = lane_id();
+  if (n != kTkSpecNone) {
+    const u64* ent = tk.spec + ti * kTkSpecCap;
+    for (uint32_t i0 = 0; i0 < n; i0 += kWave) {
+      const uint32_t i = i0 + (uint32_t)lane;
+      const uint32_t key = (uint32_t)ent[i < n ? i : 0u] & 0x7FFFFFFFu;
+      const bool ok = i < n && key >= lo && key < up;
+      hist_add(h, ok ? (key - lo) >> sh : 0u, ok);
+    }
+    return;
+  }
+  const int64_t first = (int64_t)tile * kTkTileElems;
+  const int count = (int)min((int64_t)kTkTileElems, ten.n - first);
+  const Buf rd = buf_of(dr + ten.off + first, (uint32_t)count * 4u);
+#pragma unroll 1
+  for (int w = 0; w < kTileWords; w += kW) {
+    float v[kW];
+#pragma unroll
+    for (int u = 0; u < kW; ++u) v[u] = buf_ld(rd, (uint32_t)((w + u) * kWave + lane) * 4u);
+#pragma unroll
+    for (int u = 0; u < kW; ++u) {
+      const uint32_t key = key_of(v[u]);
+      const bool ok = (w + u) * kWave + lane < count && key >= lo && key < up;
+      hist_add(h, ok ? (key - lo) >> sh : 0u, ok);
+    }
+  }
 }
 
 // The candidates of a (row, tensor): n of them at p (LDS, or slots), or, when
@@ -673,26 +768,6 @@ struct Cands {
   }
 };
 
-// Counts each ok lane's bin into the LDS histogram h.  The server's errors
-// crowd a few bins (most of them keep last call's residual, and its binade),
-// and one 64-lane LDS atomic into one address is serialized lane by lane: the
-// lanes that share the first lane's bin add their count with one atomic, the
-// others theirs one by one.  At resnet50 K = 8 Top-1% (union gathers) that
-// took the iteration from 0.974-0.977 to 0.965-0.968 ms; repeating it for a
-// second bin gave 0.976, a third 0.987-0.990 ms.
-__device__ __forceinline__ void hist_add(uint32_t* h, uint32_t bin, bool ok) {
-  const int lane = lane_id();
-  const u64 todo = __ballot(ok);
-  if (todo == 0ull) return;  // wave-uniform
-  const int lead = __builtin_ctzll(todo);
-  const uint32_t lb = (uint32_t)__builtin_amdgcn_readlane((int)bin, lead);
-  const u64 same = __ballot(bin == lb) & todo;
-  if (lane == lead)
-    atomicAdd(&h[lb], (uint32_t)__popcll(same));
-  else if (((todo & ~same) >> lane) & 1ull)
-    atomicAdd(&h[bin], 1u);
-}
-
 // One radix pass: histogram of digit(e) of the candidates with match(e).
 template <typename Match, typename Dig>
 __device__ __forceinline__ void cand_hist(uint32_t* h, int nb, const Cands& cand, Match match,
@@ -713,19 +788,19 @@ __device__ __forceinline__ int radix_digit(int open, int most) {
   return (open + passes - 1) / passes;
 }
 
-// tau and iota of the `need` first of C candidates, all with keys in [lo,
-// up) (need <= C): up to one per thread in LDS (lds) by counting each one's
-// rank (one pass, no histogram), else radix passes of kDig bits over key -
-// lo, and, when only some of the keys equal to tau are kept, over the index.
-// keys: the candidates' key - lo in LDS, in any order, or null (then every
-// pass reads cand).  Every thread of the workgroup calls it and gets the
-// result.  h: 2^kDig bins.
+// tau and iota of the `need` first of C candidates, all with keys below lo +
+// 2^open (need <= C): up to one per thread in LDS (lds) by counting each one's
+// rank (one pass, no histogram), else radix passes of at most kDig bits over
+// key - lo, and, when only some of the keys equal to tau are kept, over the
+// index (idx_bits bits).  keys: the candidates' key - lo in LDS, in any order,
+// or null (then every pass reads cand).  Every thread of the workgroup calls it
+// and gets the result.  h: 2^kDig bins.
 template <int kDig>
 __device__ __forceinline__ void cand_select(uint32_t* h, uint32_t* scan, uint32_t* res,
                                             const u64* lds, const uint32_t* keys,
-                                            const Cands& cand, int64_t C,
-                                            int64_t need, uint32_t lo, uint32_t up, uint32_t& tau,
-                                            int64_t& iota) {
+                                            const Cands& cand, int64_t C, int64_t need,
+                                            uint32_t lo, int open, int idx_bits,
+                                            uint32_t& tau, int64_t& iota) {
   if (lds != nullptr && C <= (int64_t)blockDim.x) {
     if (threadIdx.x == 0) {  // defined result even if need exceeded C
       res[0] = lo;
@@ -754,15 +829,12 @@ __device__ __forceinline__ void cand_select(uint32_t* h, uint32_t* scan, uint32_
     return;
   }
   uint32_t prefix = 0, bin = 0, cnt = (uint32_t)C;
-  const int bits = range_bits(lo, up);
-  int open = bits;
   int64_t left = need;
   while (open > 0) {
     const int d = radix_digit(open, kDig);
     const int sh = open - d;
     const uint32_t mask = (1u << d) - 1u;
-    const bool first = open == bits;
-    const auto match = [=](uint32_t rel) { return first || (rel >> open) == prefix; };
+    const auto match = [=](uint32_t rel) { return (rel >> open) == prefix; };  // open < 32
     if (keys != nullptr) {
       for (int i = threadIdx.x; i < 1 << d; i += blockDim.x) h[i] = 0;
       __syncthreads();
@@ -785,10 +857,10 @@ __device__ __forceinline__ void cand_select(uint32_t* h, uint32_t* scan, uint32_
   tau = lo + prefix;
   iota = INT64_MAX;  // every element equal to tau is kept
   if (left < (int64_t)cnt) {
-    // the left-th smallest index (28 bits) among the elements equal to tau
+    // the left-th smallest index among the elements equal to tau
     const uint32_t key = tau;
     uint32_t at = 0;
-    open = 28;
+    open = idx_bits;
     need = left;
     while (open > 0) {
       const int d = radix_digit(open, kDig);
@@ -840,13 +912,16 @@ __device__ __forceinline__ void tile_ranks(uint32_t* t, uint32_t* scan, const Ca
 // small tensor is then selected here as a whole, from its tiles' lists or
 // Delta (resnet56 Top-5%: one kernel of 13-24 us for six of 44 us); for a
 // large one the candidate range and the number to take are left to refine,
-// gather and select.  256 threads and 5 KB of LDS: two workgroups fit on a CU
-// beside the five of a Delta pass (a select of 1024 threads waited up to 200
-// us for its wave slots, until the pass drained).
-__global__ __launch_bounds__(kPick) void k_tk_pick(DevLayout lay, TkDev tk, TkPart p, int row0,
-                                                   const float* __restrict__ data) {
+// gather and select.  A bin with more candidates than its LDS holds is narrowed
+// first, 11 key bits per pass over the tensor's lists or Delta, until they fit
+// or are all equal.  256 threads, so that its workgroups find wave slots beside
+// a Delta pass (a select of 1024 threads waited up to 200 us for them, until
+// the pass drained), or 1024 (kTkPickTiles, kTkWidePairs).
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_tk_pick(DevLayout lay, TkDev tk, TkPart p,
+                                                      int row0, const float* __restrict__ data) {
   constexpr int kDig = 8;
-  constexpr int kPW = kPick / kWave;
+  constexpr int kPW = kThreads / kWave;
   __shared__ uint32_t h[kTkHistPad > (1 << kDig) ? kTkHistPad : (1 << kDig)];
   __shared__ u64 s_cand[kPickCand];
   __shared__ uint32_t s_t[kTkGroup / 2];
@@ -864,10 +939,10 @@ __global__ __launch_bounds__(kPick) void k_tk_pick(DevLayout lay, TkDev tk, TkPa
   const uint32_t floor = spec_floor(*st);
   const int lane = lane_id(), wave = wave_id();
   const bool small = t.ngroups == 0;
-  for (int i = threadIdx.x; i < kTkHistPad; i += kPick) h[i] = 0;
+  for (int i = threadIdx.x; i < kTkHistPad; i += kThreads) h[i] = 0;
   if (threadIdx.x < kTkGroup / 2) s_t[threadIdx.x] = 0;
   if (threadIdx.x == 0) s_fill = 0;
-  constexpr int kPer = 8;  // tiles a wave has in flight
+  constexpr int kPer = kThreads == kPick ? 8 : 4;  // tiles a wave has in flight
   const int per = (ten.ntiles + kPW - 1) / kPW;  // a wave's tiles: wave per + 0 .. per - 1
   const int tw0 = wave * per, tend = min(tw0 + per, ten.ntiles);
   // lane j: list count of the wave's tile j
@@ -903,12 +978,12 @@ __global__ __launch_bounds__(kPick) void k_tk_pick(DevLayout lay, TkDev tk, TkPa
   uint32_t b1, n1;
   int64_t need;
   find_bin<true>(h, kTkHist, t.keep, s_scan, s_res, b1, need, n1);
-  const uint32_t lo = bin_floor(b1, win), up = bin_floor(b1 + 1u, win);
+  uint32_t lo = bin_floor(b1, win), up = bin_floor(b1 + 1u, win);
   if (!small) {
-    const bool coarse = tk.refine != 0 && n1 > (uint32_t)kRefineCand;
+    const bool coarse = n1 > (uint32_t)(tk.levels != 0 ? kRefineCand : kFullCand);
     if (coarse) {
       uint32_t* rh = tk.rhist + ((int64_t)row * tk.n_large + t.large) * (kRefineLevels * kTkBins);
-      for (int i = threadIdx.x; i < kRefineLevels * kTkBins; i += kPick) rh[i] = 0;
+      for (int i = threadIdx.x; i < max(tk.levels, 1) * kTkBins; i += kThreads) rh[i] = 0;
     }
     if (threadIdx.x == 0) {
       st->floor = floor;
@@ -919,15 +994,35 @@ __global__ __launch_bounds__(kPick) void k_tk_pick(DevLayout lay, TkDev tk, TkPa
     }
     return;
   }
+  const float* dr = data + (int64_t)r * lay.d_pad;
+  static_assert(sizeof(s_cand) >= kTkBins * sizeof(uint32_t), "a narrowing histogram fits");
+  uint32_t* nh = reinterpret_cast<uint32_t*>(s_cand);
+  while (n1 > (uint32_t)kPickCand && range_bits(lo, up) > 0) {  // workgroup-uniform
+    const int sh = max(range_bits(lo, up) - 11, 0);
+    for (int i = threadIdx.x; i < kTkBins; i += kThreads) nh[i] = 0;
+    lds_barrier();
+    for (int q = tw0; q < tend; ++q) {
+      const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)lcnt, q - tw0);
+      tile_range_hist<8>(nh, tk, ten, (int64_t)row * lay.n_tiles + ten.first_tile + q, q,
+                         floor <= lo ? n : kTkSpecNone, dr, lo, up, sh);
+    }
+    lds_barrier();
+    uint32_t bin;
+    const int64_t want = need;
+    find_bin<true>(nh, kTkBins, want, s_scan, s_res, bin, need, n1);  // ends with a barrier
+    up = min(up, lo + ((bin + 1u) << sh));
+    lo = lo + (bin << sh);
+  }
   u64* slots = tk.cand + (int64_t)row * lay.d_pad + ten.off;
   const bool in_lds = n1 <= (uint32_t)kPickCand;
   const CandSink sink{&s_fill, s_cand, slots, kPickCand, (uint32_t)ten.n, in_lds};
-  const float* dr = data + (int64_t)r * lay.d_pad;
+  const bool relist = st->lists != 0u;
   if (floor > lo && lane < tend - tw0) lcnt = kTkSpecNone;  // the lists end above b1
   for (int t0 = tw0; t0 < tend; t0 += kPer) {
     const uint32_t n = (uint32_t)__shfl((int)lcnt, (t0 - tw0 + lane) % kWave);
     const TileCounts tc =
-        scan_tiles<kPer, 1, 8>(sink, lay, tk, ten, row, t0, lane < kPer ? n : 0u, dr, lo, up);
+        scan_tiles<kPer, 1, 8>(sink, lay, tk, ten, row, t0, lane < kPer ? n : 0u, dr, lo, up,
+                               relist);
     if (lane < kPer && t0 + lane < tend) tile_count_add(s_t, t0 + lane, tc.sure);
   }
   __syncthreads();  // candidates in LDS or in the slots, and the tile counts
@@ -935,12 +1030,12 @@ __global__ __launch_bounds__(kPick) void k_tk_pick(DevLayout lay, TkDev tk, TkPa
   const Cands cand{in_lds ? s_cand : slots, C, nullptr, 0, 0};
   uint32_t tau;
   int64_t iota;
-  cand_select<kDig>(h, s_scan, s_res, in_lds ? s_cand : nullptr, nullptr, cand, C, need, lo, up,
-                    tau, iota);
+  cand_select<kDig>(h, s_scan, s_res, in_lds ? s_cand : nullptr, nullptr, cand, C, need, lo,
+                    range_bits(lo, up), index_bits(ten.n), tau, iota);
   tile_ranks(s_t, s_scan, cand, tau, iota, ten.ntiles,
              tk.tile_cnt + (int64_t)row * lay.n_tiles + ten.first_tile);
   if (threadIdx.x == 0) {
-    st->floor = floor;
+    st->floor = relist ? min(floor, lo) : floor;
     st->tau = tau;
     st->iota = iota;
     st->win = window_for(tau);
@@ -973,11 +1068,10 @@ __device__ __forceinline__ GatherUnit gather_unit(const DevLayout& lay, const Tk
 }
 
 // The candidate range of a large (row, tensor) and how many to take from it:
-// the pick's, narrowed by the first kLevels of the refine's histograms when
+// the pick's, narrowed by the first `levels` of the refine's histograms when
 // coarse (h: kTkBins entries of LDS).  Every thread of the workgroup calls it.
-template <int kLevels>
 __device__ __forceinline__ void cand_range(const TkDev& tk, const TkSel& st, int row, int large,
-                                           uint32_t* h, uint32_t* scan, uint32_t* res,
+                                           int levels, uint32_t* h, uint32_t* scan, uint32_t* res,
                                            uint32_t& lo, uint32_t& up, int64_t& need) {
   lo = st.lo;
   up = st.up;
@@ -985,8 +1079,7 @@ __device__ __forceinline__ void cand_range(const TkDev& tk, const TkSel& st, int
   if (st.coarse == 0u) return;  // workgroup-uniform
   const uint32_t* rh =
       tk.rhist + ((int64_t)row * tk.n_large + large) * (kRefineLevels * kTkBins);
-#pragma unroll
-  for (int v = 0; v < kLevels; ++v) {
+  for (int v = 0; v < levels; ++v) {
     if (range_bits(lo, up) == 0) return;  // one key (workgroup-uniform)
     for (int i = threadIdx.x; i < kTkBins; i += blockDim.x) h[i] = rh[v * kTkBins + i];
     const int sh = max(range_bits(lo, up) - 11, 0);
@@ -999,6 +1092,53 @@ __device__ __forceinline__ void cand_range(const TkDev& tk, const TkSel& st, int
   }
 }
 
+// Counts the top 11 bits of key - lo over [lo, up) of the unit's tiles into the
+// LDS histogram h.
+__device__ __forceinline__ void unit_range_hist(uint32_t* h, const DevLayout& lay, const TkDev& tk,
+                                                const GatherUnit& g, uint32_t floor, uint32_t lo,
+                                                uint32_t up) {
+  const TensorInfo ten = lay.tensors[g.gr.l];
+  const int sh = max(range_bits(lo, up) - 11, 0);
+  for (int j = wave_id(); j < g.n; j += (int)blockDim.x / kWave) {
+    const int64_t ti = (int64_t)g.row * lay.n_tiles + ten.first_tile + g.t0 + j;
+    tile_range_hist<8>(h, tk, ten, ti, g.t0 + j, floor <= lo ? tk.lcnt[ti] : kTkSpecNone, g.data,
+                       lo, up, sh);
+  }
+}
+
+// Adds the LDS histogram h to a level of the (row, large tensor)'s in rhist.
+__device__ __forceinline__ void add_range_hist(const uint32_t* h, const TkDev& tk, int row,
+                                               int large, int level) {
+  uint32_t* rh = tk.rhist + ((int64_t)row * tk.n_large + large) * (kRefineLevels * kTkBins) +
+                 level * kTkBins;
+  for (int i = threadIdx.x; i < kTkBins; i += blockDim.x)
+    if (h[i] != 0u) atomicAdd(&rh[i], h[i]);
+}
+
+// A wave's kPer tiles (t0 .. of the tensor, those below tend) to the segment
+// that starts at tile seg0: candidates to its slots (filled through the LDS
+// count *fill), counts to tile_cnt (and tile_cand).  lcnt: lane j holds the
+// list count of tile t0 + j.
+template <int kPer, int kC>
+__device__ __forceinline__ void gather_tiles(uint32_t* fill, const DevLayout& lay,
+                                             const TkDev& tk, const TensorInfo& ten, int row,
+                                             int seg0, int t0, int tend, uint32_t lcnt,
+                                             uint32_t floor, const float* __restrict__ data,
+                                             uint32_t lo, uint32_t up, bool within, bool relist) {
+  if (t0 >= tend) return;  // wave-uniform
+  u64* slots = tk.cand + (int64_t)row * lay.d_pad + ten.off + (int64_t)seg0 * kTkTileElems;
+  const CandSink sink{fill, nullptr, slots, 0, (uint32_t)kGatherTiles * kTkTileElems, false};
+  const int lane = lane_id();
+  if (floor > lo && lane < min(kPer, tend - t0)) lcnt = kTkSpecNone;  // the lists end above lo
+  const TileCounts tc =
+      scan_tiles<kPer, kC, 8>(sink, lay, tk, ten, row, t0, lcnt, data, lo, up, relist);
+  if (lane < kPer && t0 + lane < tend) {
+    const int64_t ti = (int64_t)row * lay.n_tiles + ten.first_tile + t0 + lane;
+    tk.tile_cnt[ti] = tc.sure;
+    if (within) tk.tile_cand[ti] = tc.cand;
+  }
+}
+
 // Counts, for the (row, tensor)s whose candidate bin is full, 11 bits of key -
 // lo (level 0: the top 11 of the bin's; level 1: the next 11) over the
 // candidates of their tiles (from the lists where they reach down to lo, else
@@ -1007,7 +1147,9 @@ __device__ __forceinline__ void cand_range(const TkDev& tk, const TkSel& st, int
 // passes over all the candidates of such a bin (a wide one, or one where
 // many values are equal) took up to 3 ms at bert_base Top-1% (K = 16), whose
 // outliers all have one magnitude.  Launched for plans with a tensor of more
-// than 4096 tiles, and for a plan's first calls, whose bins are not placed yet.
+// than 4096 tiles.  In the others the gather counts and the select's launch
+// gathers: launches that mostly find nothing to narrow took resnet50 K = 8 from
+// 820 to 825 us per Top-1% iteration and from 1059 to 1077 at Top-10%.
 template <int kLevel>
 __global__ __launch_bounds__(kBlock) void k_tk_refine(DevLayout lay, TkDev tk, TkPart p, int row0,
                                                       const float* __restrict__ data) {
@@ -1021,54 +1163,27 @@ __global__ __launch_bounds__(kBlock) void k_tk_refine(DevLayout lay, TkDev tk, T
   const uint32_t floor = st.floor;
   uint32_t lo, up;
   int64_t need;
-  cand_range<kLevel>(tk, st, g.row, large, h, s_scan, s_res, lo, up, need);
+  cand_range(tk, st, g.row, large, kLevel, h, s_scan, s_res, lo, up, need);
   if (range_bits(lo, up) == 0) return;  // one key already (workgroup-uniform)
-  const int sh = max(range_bits(lo, up) - 11, 0);
   for (int i = threadIdx.x; i < kTkBins; i += kBlock) h[i] = 0;
   lds_barrier();
-  const int lane = lane_id();
-  const TensorInfo ten = lay.tensors[g.gr.l];
-  for (int j = wave_id(); j < g.n; j += kWaves) {
-    const int64_t ti = (int64_t)g.row * lay.n_tiles + ten.first_tile + g.t0 + j;
-    const uint32_t n = floor <= lo ? tk.lcnt[ti] : kTkSpecNone;
-    if (n != kTkSpecNone) {
-      const u64* ent = tk.spec + ti * kTkSpecCap;
-      for (uint32_t i0 = 0; i0 < n; i0 += kWave) {
-        const uint32_t i = i0 + (uint32_t)lane;
-        const uint32_t key = (uint32_t)ent[i < n ? i : 0u] & 0x7FFFFFFFu;
-        const bool ok = i < n && key >= lo && key < up;
-        hist_add(h, ok ? (key - lo) >> sh : 0u, ok);
-      }
-      continue;
-    }
-    const int64_t first = (int64_t)(g.t0 + j) * kTkTileElems;
-    const int count = (int)min((int64_t)kTkTileElems, ten.n - first);
-    float v[kTileWords];
-    load_tile(g.data + ten.off + first, count, v);
-#pragma unroll
-    for (int u = 0; u < kTileWords; ++u) {
-      const uint32_t key = key_of(v[u]);
-      const bool ok = u * kWave + lane < count && key >= lo && key < up;
-      hist_add(h, ok ? (key - lo) >> sh : 0u, ok);
-    }
-  }
+  unit_range_hist(h, lay, tk, g, floor, lo, up);
   lds_barrier();
-  uint32_t* rh = tk.rhist +
-                 ((int64_t)g.row * tk.n_large + large) * (kRefineLevels * kTkBins) +
-                 kLevel * kTkBins;
-  for (int i = threadIdx.x; i < kTkBins; i += kBlock)
-    if (h[i] != 0u) atomicAdd(&rh[i], h[i]);
+  add_range_hist(h, tk, g.row, large, kLevel);
 }
 
 // Grid: as k_tk_refine.  Each tile's count of elements with a key at or above
 // up to tile_cnt, and the elements in [lo, up) to the workgroup's segment of
 // the (row, tensor)'s slots (kGatherTiles tiles' slots: they fit), their
 // number to seg.  From the lists where they reach down to lo, else from Delta.
-template <int kC>
-__global__ __launch_bounds__(kBlock) void k_tk_gather(DevLayout lay, TkDev tk, TkPart p, int row0,
-                                                      const float* __restrict__ data) {
+// Of a full bin that no refine narrows (a threshold that moved far) it only
+// counts 11 bits of key - lo into rhist; the select's launch gathers.
+template <int kC, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_tk_gather(DevLayout lay, TkDev tk, TkPart p,
+                                                        int row0,
+                                                        const float* __restrict__ data) {
   __shared__ uint32_t h[kTkBins];
-  __shared__ uint32_t s_scan[kWaves];
+  __shared__ uint32_t s_scan[kThreads / kWave];
   __shared__ uint32_t s_res[3];
   __shared__ uint32_t s_fill;
   const GatherUnit g = gather_unit(lay, tk, p, row0, data);
@@ -1077,27 +1192,26 @@ __global__ __launch_bounds__(kBlock) void k_tk_gather(DevLayout lay, TkDev tk, T
   int64_t need;
   const TkSel& st = tk.sel[(int64_t)g.row * lay.L + g.gr.l];
   const uint32_t floor = st.floor;
-  constexpr int kPer = kGatherTiles / kWaves;  // tiles per wave
+  const int large = tk.tens[g.gr.l].large;
+  if (st.coarse != 0u && tk.levels == 0) {  // workgroup-uniform
+    if (g.n <= 0) return;
+    for (int i = threadIdx.x; i < kTkBins; i += kThreads) h[i] = 0;
+    lds_barrier();
+    unit_range_hist(h, lay, tk, g, floor, st.lo, st.up);
+    lds_barrier();
+    add_range_hist(h, tk, g.row, large, 0);
+    return;
+  }
+  constexpr int kPer = kGatherTiles * kWave / kThreads;  // tiles per wave
   const int t0 = g.t0 + wave_id() * kPer, tend = g.t0 + g.n;
   uint32_t lcnt = 0;
   if (lane_id() < kPer && t0 + lane_id() < tend)
     lcnt = tk.lcnt[(int64_t)g.row * lay.n_tiles + ten.first_tile + t0 + lane_id()];
   if (threadIdx.x == 0) s_fill = 0;
-  cand_range<kRefineLevels>(tk, st, g.row, tk.tens[g.gr.l].large, h, s_scan, s_res, lo, up, need);
+  cand_range(tk, st, g.row, large, tk.levels, h, s_scan, s_res, lo, up, need);
   lds_barrier();
-  u64* slots = tk.cand + (int64_t)g.row * lay.d_pad + ten.off + (int64_t)g.t0 * kTkTileElems;
-  const CandSink sink{&s_fill, nullptr, slots, 0, (uint32_t)kGatherTiles * kTkTileElems, false};
-  if (t0 < tend) {
-    const int lane = lane_id();
-    if (floor > lo && lane < min(kPer, tend - t0)) lcnt = kTkSpecNone;  // they end above lo
-    const TileCounts tc =
-        scan_tiles<kPer, kC, 16>(sink, lay, tk, ten, g.row, t0, lcnt, g.data, lo, up);
-    if (lane < kPer && t0 + lane < tend) {
-      const int64_t ti = (int64_t)g.row * lay.n_tiles + ten.first_tile + t0 + lane;
-      tk.tile_cnt[ti] = tc.sure;
-      if (tk.refine != 0) tk.tile_cand[ti] = tc.cand;
-    }
-  }
+  gather_tiles<kPer, kC>(&s_fill, lay, tk, ten, g.row, g.t0, t0, tend, lcnt, floor, g.data, lo, up,
+                         tk.levels != 0, st.lists != 0u);
   lds_barrier();
   if (threadIdx.x == 0)
     tk.seg[(int64_t)g.row * tk.n_groups * kGatherSplit + g.part] = s_fill;
@@ -1129,72 +1243,63 @@ __device__ __forceinline__ void tile_prefix(int ntiles, uint32_t* scan, F f, P p
   }
 }
 
-// Grid: R * (p.b1 - p.b0) workgroups: large tensor p.b0 + b % n of row row0
-// + b / n.  Its threshold and tile ranks from the gathered candidates and
-// counts.  When the refine left one key, the candidates are equal and the
-// first `need` of them by index are kept: the tile counts give the tile where
-// they end, and only that tile's candidates are looked at.  Else up to
+// The threshold and tile ranks of a large (row, tensor) from its candidates in
+// [lo, up) and tile counts.  When the narrowing left one key, the candidates are
+// equal and the first `need` of them by index are kept: the tile counts give the
+// tile where they end, and only that tile's candidates are looked at.  Else up to
 // kSelTiles tiles are counted in LDS; beyond, in tile_cnt itself with device
 // atomics (read back past the L1).
-__global__ __launch_bounds__(kSelect) void k_tk_select(DevLayout lay, TkDev tk, TkPart p,
-                                                       int row0) {
-  constexpr int kSW = kSelect / kWave;
-  constexpr int kDig = 10;
-  __shared__ uint32_t s_key[kSelKeys];
-  __shared__ uint32_t h[1 << kDig];
-  __shared__ uint32_t s_t[kSelTiles / 2];
-  static_assert(kSelKeys >= kTkBins, "the range's histogram fits in s_key");
-  __shared__ uint32_t s_scan[kSW];
-  __shared__ uint32_t s_res[3];
-  __shared__ uint32_t s_fill;
-  const int nb = p.b1 - p.b0;
-  const int lg = p.b0 + (int)(blockIdx.x % (unsigned)nb);
-  const int row = row0 + (int)(blockIdx.x / (unsigned)nb);
-  const int l = tk.large[lg];
-  const TensorInfo ten = lay.tensors[l];
-  const TkTensor t = tk.tens[l];
-  TkSel* st = tk.sel + (int64_t)row * lay.L + l;
+constexpr int kSelDig = 10;
+struct SelectLds {
+  uint32_t key[kSelKeys];
+  uint32_t h[1 << kSelDig];
+  uint32_t t[kSelTiles / 2];
+  uint32_t scan[kSelect / kWave];
+  uint32_t res[3];
+  uint32_t fill;
+};
+static_assert(kSelKeys >= kTkBins, "the range's histogram fits in key");
+__device__ __forceinline__ void select_tensor(SelectLds& s, const DevLayout& lay, const TkDev& tk,
+                                              const TensorInfo& ten, const TkTensor& t, TkSel* st,
+                                              int row, uint32_t lo, uint32_t up, int64_t need) {
   const u64* slots = tk.cand + (int64_t)row * lay.d_pad + ten.off;
   const int64_t tile0 = (int64_t)row * lay.n_tiles + ten.first_tile;
   uint32_t* cnt = tk.tile_cnt + tile0;
   const uint32_t* segs = tk.seg + ((int64_t)row * tk.n_groups + t.first_group) * kGatherSplit;
   const int nseg = t.ngroups * kGatherSplit;
   constexpr uint32_t kStride = (uint32_t)kGatherTiles * kTkTileElems;
-  uint32_t lo, up;
-  int64_t need;
-  cand_range<kRefineLevels>(tk, *st, row, lg, s_key, s_scan, s_res, lo, up, need);
   uint32_t tau;
   int64_t iota;
   if (st->coarse != 0u && range_bits(lo, up) == 0) {  // workgroup-uniform
     const uint32_t* within = tk.tile_cand + tile0;
     if (threadIdx.x == 0) {
-      s_res[0] = 0;
-      s_res[1] = 0;
-      s_res[2] = kTkTileElems - 1;
+      s.res[0] = 0;
+      s.res[1] = 0;
+      s.res[2] = kTkTileElems - 1;
     }
-    if (threadIdx.x < kTkTileElems / 32) h[threadIdx.x] = 0;
+    if (threadIdx.x < kTkTileElems / 32) s.h[threadIdx.x] = 0;
     __syncthreads();
-    tile_prefix(ten.ntiles, s_scan, [=](int i) { return within[i]; },
-                [=](int i, uint32_t at, uint32_t v) {
+    tile_prefix(ten.ntiles, s.scan, [=](int i) { return within[i]; },
+                [&](int i, uint32_t at, uint32_t v) {
                   if ((int64_t)at < need && need <= (int64_t)at + v) {
-                    s_res[0] = (uint32_t)i;                 // the tile with the last one kept
-                    s_res[1] = (uint32_t)(need - at);       // how many of it are kept
+                    s.res[0] = (uint32_t)i;            // the tile with the last one kept
+                    s.res[1] = (uint32_t)(need - at);  // how many of it are kept
                   }
                 });
     __syncthreads();
-    const int last = (int)s_res[0];
-    const uint32_t take = s_res[1];
+    const int last = (int)s.res[0];
+    const uint32_t take = s.res[1];
     // the tile's candidates as bits, then the take-th of them
     const u64* seg = slots + (int64_t)(last / kGatherTiles) * kStride;
     const uint32_t n = min(segs[last / kGatherTiles], kStride);
     for (uint32_t i = threadIdx.x; i < n; i += kSelect) {
       const uint32_t idx = (uint32_t)(seg[i] >> 32);
       if (idx / kTkTileElems == (uint32_t)last)
-        atomicOr(&h[idx % kTkTileElems / 32], 1u << (idx % 32u));
+        atomicOr(&s.h[idx % kTkTileElems / 32], 1u << (idx % 32u));
     }
     __syncthreads();
     if (threadIdx.x < kWave) {
-      const uint32_t w = h[threadIdx.x];
+      const uint32_t w = s.h[threadIdx.x];
       const uint32_t c = (uint32_t)__popc(w);
       uint32_t incl = c;
 #pragma unroll
@@ -1204,25 +1309,25 @@ __global__ __launch_bounds__(kSelect) void k_tk_select(DevLayout lay, TkDev tk, 
       }
       static_assert(kTkTileElems == 32 * kWave, "a lane per word of the tile's bits");
       if (incl - c < take && take <= incl)
-        s_res[2] = threadIdx.x * 32u + (uint32_t)nth_set_bit((u64)w, take - (incl - c) - 1u);
+        s.res[2] = threadIdx.x * 32u + (uint32_t)nth_set_bit((u64)w, take - (incl - c) - 1u);
     }
     __syncthreads();
     tau = lo;
-    iota = (int64_t)last * kTkTileElems + s_res[2];
-    tile_prefix(ten.ntiles, s_scan,
+    iota = (int64_t)last * kTkTileElems + s.res[2];
+    tile_prefix(ten.ntiles, s.scan,
                 [=](int i) { return cnt[i] + (i < last ? within[i] : i == last ? take : 0u); },
                 [=](int i, uint32_t at, uint32_t) { cnt[i] = at; });
   } else {
     const bool counted = ten.ntiles <= kSelTiles;
     if (counted)
       for (int i = threadIdx.x; 2 * i < ten.ntiles; i += kSelect)
-        s_t[i] = cnt[2 * i] | (2 * i + 1 < ten.ntiles ? cnt[2 * i + 1] << 16 : 0u);
-    if (threadIdx.x == 0) s_fill = 0;
+        s.t[i] = cnt[2 * i] | (2 * i + 1 < ten.ntiles ? cnt[2 * i + 1] << 16 : 0u);
+    if (threadIdx.x == 0) s.fill = 0;
     // the number of candidates; the keys of up to kSelKeys are brought to LDS
     uint32_t mine = 0;
     for (int i = threadIdx.x; i < nseg; i += kSelect) mine += segs[i];
     uint32_t total;
-    (void)block_excl_scan(mine, s_scan, &total);  // ends with a barrier
+    (void)block_excl_scan(mine, s.scan, &total);  // ends with a barrier
     const bool in_lds = total <= (uint32_t)kSelKeys;
     const Cands cand{slots, (int64_t)total, segs, nseg, kStride};
     if (in_lds) {
@@ -1230,19 +1335,20 @@ __global__ __launch_bounds__(kSelect) void k_tk_select(DevLayout lay, TkDev tk, 
         const u64 m = __ballot(ok);
         if (m == 0ull) return;
         uint32_t base = 0;
-        if (lane_id() == 0) base = atomicAdd(&s_fill, (uint32_t)__popcll(m));
+        if (lane_id() == 0) base = atomicAdd(&s.fill, (uint32_t)__popcll(m));
         base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
         const uint32_t pos =
             base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                              __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        if (ok && pos < (uint32_t)kSelKeys) s_key[pos] = (uint32_t)e - lo;  // always holds
+        if (ok && pos < (uint32_t)kSelKeys) s.key[pos] = (uint32_t)e - lo;  // always holds
       });
       __syncthreads();
     }
-    cand_select<kDig>(h, s_scan, s_res, nullptr, in_lds ? s_key : nullptr, cand, (int64_t)total,
-                      need, lo, up, tau, iota);
+    cand_select<kSelDig>(s.h, s.scan, s.res, nullptr, in_lds ? s.key : nullptr, cand,
+                         (int64_t)total, need, lo, range_bits(lo, up), index_bits(ten.n), tau,
+                         iota);
     if (counted) {
-      tile_ranks(s_t, s_scan, cand, tau, iota, ten.ntiles, cnt);
+      tile_ranks(s.t, s.scan, cand, tau, iota, ten.ntiles, cnt);
     } else {
       cand.each([&](u64 e, bool ok) {
         const uint32_t i = (uint32_t)(e >> 32) / kTkTileElems;
@@ -1250,7 +1356,7 @@ __global__ __launch_bounds__(kSelect) void k_tk_select(DevLayout lay, TkDev tk, 
       });
       __threadfence();
       __syncthreads();
-      tile_prefix(ten.ntiles, s_scan,
+      tile_prefix(ten.ntiles, s.scan,
                   [=](int i) {
                     return __hip_atomic_load(&cnt[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                   },
@@ -1259,10 +1365,98 @@ __global__ __launch_bounds__(kSelect) void k_tk_select(DevLayout lay, TkDev tk, 
   }
   __syncthreads();  // every thread has read st
   if (threadIdx.x == 0) {
+    if (st->lists != 0u) st->floor = min(st->floor, lo);  // as the gather left the lists
     st->tau = tau;
     st->iota = iota;
     st->win = window_for(tau);
   }
+}
+
+// Grid: R * (n + m kParts) workgroups, n the part's large tensors and m its tile
+// groups.  Workgroup b < R n: the threshold and tile ranks of large tensor p.b0 +
+// b % n of row row0 + b / n from the gathered candidates and counts.  The others
+// take a part of a group each and return at once, unless the tensor's candidate
+// bin is full and the gather only counted it: then they gather its tiles from
+// the sub-range that the counts leave, and the last one of the tensor to arrive
+// (nobody waits) selects.  (One workgroup takes up to 4 ms over a full bin:
+// resnet50 K = 8 Top-1%, all values 1000 times as large as in the call before,
+// 4.4 ms a call; 1.3 ms this way.)
+template <int kParts>
+__global__ __launch_bounds__(kSelect) void k_tk_select(DevLayout lay, TkDev tk, TkPart p, int R,
+                                                       int row0,
+                                                       const float* __restrict__ data) {
+  constexpr int kSW = kSelect / kWave;
+  __shared__ SelectLds s;
+  __shared__ uint32_t s_segs[kGatherSplit];
+  const unsigned nb = (unsigned)(p.b1 - p.b0), nsel = nb * (unsigned)R;
+  const bool helps = blockIdx.x >= nsel;  // workgroup-uniform, like all of this
+  int l, lg, row, gi = 0, part = 0;
+  if (helps) {
+    const unsigned n = (unsigned)(p.g1 - p.g0) * kParts, u = blockIdx.x - nsel;
+    gi = p.g0 + (int)(u % n / kParts);
+    part = (int)(u % kParts);
+    row = row0 + (int)(u / n);
+    l = tk.groups[gi].l;
+    lg = tk.tens[l].large;
+  } else {
+    lg = p.b0 + (int)(blockIdx.x % nb);
+    row = row0 + (int)(blockIdx.x / nb);
+    l = tk.large[lg];
+  }
+  TkSel* st = tk.sel + (int64_t)row * lay.L + l;
+  const TensorInfo ten = lay.tensors[l];
+  const TkTensor t = tk.tens[l];
+  const TkSel was = *st;
+  __builtin_amdgcn_sched_barrier(0);  // these loads before the branch
+  const bool full = was.coarse != 0u && tk.levels == 0;
+  if (helps != full) return;
+  const int levels = full ? 1 : tk.levels;
+  uint32_t lo, up;
+  int64_t need;
+  cand_range(tk, was, row, lg, levels, s.key, s.scan, s.res, lo, up, need);
+  if (full) {
+    constexpr int kUnit = kTkGroup / kParts, kSegs = kGatherSplit / kParts;
+    constexpr int kPer = kUnit / kSW < 4 ? kUnit / kSW : 4, kTurns = kUnit / kSW / kPer;
+    static_assert(kGatherTiles % kPer == 0, "the tiles of a turn lie in one segment");
+    const TkGroup gr = tk.groups[gi];
+    const int g0 = gr.first - ten.first_tile, u0 = g0 + part * kUnit;
+    const int tend = min(g0 + gr.n, u0 + kUnit);
+    if (threadIdx.x < kSegs) s_segs[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll 1
+    for (int q = 0; q < kTurns; ++q) {
+      const int t0 = u0 + (wave_id() * kTurns + q) * kPer, seg = (t0 - u0) / kGatherTiles;
+      uint32_t lcnt = 0;
+      if (lane_id() < kPer && t0 + lane_id() < tend)
+        lcnt = tk.lcnt[(int64_t)row * lay.n_tiles + ten.first_tile + t0 + lane_id()];
+      gather_tiles<kPer, 1>(&s_segs[seg], lay, tk, ten, row, u0 + seg * kGatherTiles, t0, tend,
+                            lcnt, st->floor, data + (int64_t)(row - row0) * lay.d_pad, lo, up, true,
+                            st->lists != 0u);
+    }
+    __syncthreads();
+    if (threadIdx.x < kSegs)
+      tk.seg[((int64_t)row * tk.n_groups + gi) * kGatherSplit + part * kSegs + threadIdx.x] =
+          s_segs[threadIdx.x];
+    // Every wave's stores have reached the L2 before the barrier, which does not
+    // wait for them by itself; one thread then has the L2 written back for the
+    // other XCDs (each release writes back a whole L2: not one per wave), waits
+    // for that and arrives.  The last to arrive drops what its caches may hold
+    // of the others' results.
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t* arrived = tk.arrived + (int64_t)row * tk.n_large + lg;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __builtin_amdgcn_s_waitcnt(0);
+      const bool last = atomicAdd(arrived, 1u) + 1u == (uint32_t)(t.ngroups * kParts);
+      if (last) atomicExch(arrived, 0u);  // for the next call
+      s.res[0] = last ? 1u : 0u;
+    }
+    __syncthreads();
+    if (s.res[0] == 0u) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  }
+  select_tensor(s, lay, tk, ten, t, st, row, lo, up, need);
 }
 
 // ------------------------------------------------------------------ emit
@@ -1860,10 +2054,13 @@ struct Launcher {
                   s, lay, tk, p, row0);
       if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    SAEF_LAUNCH(k_tk_pick, pairs, dim3(kPick), 0, s, lay, tk, p, row0, data);
+    if (tk.pick_wide != 0 || (tk.alone != 0 && pairs.x <= (unsigned)kTkWidePairs))
+      SAEF_LAUNCH(k_tk_pick<kPickWide>, pairs, dim3(kPickWide), 0, s, lay, tk, p, row0, data);
+    else
+      SAEF_LAUNCH(k_tk_pick<kPick>, pairs, dim3(kPick), 0, s, lay, tk, p, row0, data);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     if (large) {
-      if (tk.refine != 0) {
+      if (tk.levels != 0) {
         SAEF_LAUNCH(k_tk_refine<0>, quarters, dim3(kBlock), 0, s, lay, tk, p, row0, data);
         if ((err = hipGetLastError()) != hipSuccess) return err;
         SAEF_LAUNCH(k_tk_refine<1>, quarters, dim3(kBlock), 0, s, lay, tk, p, row0, data);
@@ -1873,13 +2070,32 @@ struct Launcher {
       // holds the list of a tile of a sparse plan (up to 1/64 kept), else two
       // chunks of each tile are in flight together (Top-10%: 1064 us per
       // iteration with two, 1067 with four, 1101 against 1093 with one).
-      if (tk.total_keep * 64 <= lay.d_pad)
-        SAEF_LAUNCH(k_tk_gather<1>, quarters, dim3(kBlock), 0, s, lay, tk, p, row0, data);
-      else
-        SAEF_LAUNCH(k_tk_gather<2>, quarters, dim3(kBlock), 0, s, lay, tk, p, row0, data);
+      // Up to a workgroup per CU, in a plan that is never split: a wave per tile
+      // (with three times as many, 8.5 against 5.4 us: ragged tensors of 5 M
+      // elements, K = 3).
+      const bool sparse = tk.total_keep * 64 <= lay.d_pad;
+      const bool wide = tk.alone != 0 && quarters.x <= (unsigned)kTkWidePairs;
+      if (wide) {
+        if (sparse)
+          SAEF_LAUNCH((k_tk_gather<1, kGatherWide>), quarters, dim3(kGatherWide), 0, s, lay, tk, p,
+                      row0, data);
+        else
+          SAEF_LAUNCH((k_tk_gather<2, kGatherWide>), quarters, dim3(kGatherWide), 0, s, lay, tk, p,
+                      row0, data);
+      } else if (sparse) {
+        SAEF_LAUNCH((k_tk_gather<1, kBlock>), quarters, dim3(kBlock), 0, s, lay, tk, p, row0, data);
+      } else {
+        SAEF_LAUNCH((k_tk_gather<2, kBlock>), quarters, dim3(kBlock), 0, s, lay, tk, p, row0, data);
+      }
       if ((err = hipGetLastError()) != hipSuccess) return err;
-      SAEF_LAUNCH(k_tk_select, dim3((unsigned)((int64_t)R * (p.b1 - p.b0))), dim3(kSelect), 0, s,
-                  lay, tk, p, row0);
+      // the select, with a workgroup per group (wide: per gather workgroup) that
+      // mostly returns at once
+      const dim3 picks((unsigned)((int64_t)R * (p.b1 - p.b0)) + (wide ? quarters.x : groups.x));
+      if (wide)
+        SAEF_LAUNCH(k_tk_select<kGatherSplit>, picks, dim3(kSelect), 0, s, lay, tk, p, R, row0,
+                    data);
+      else
+        SAEF_LAUNCH(k_tk_select<1>, picks, dim3(kSelect), 0, s, lay, tk, p, R, row0, data);
       if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     if (x != nullptr)
