@@ -308,12 +308,11 @@ def main() -> int:
     # averaging due it takes the step ahead along (4 + 4 K more: x in, xh out)
     c_count, c_ms = prof["compress"]
     # Top-K: the iteration end (compression and server step) runs pipelined
-    # over tensor groups as one timed span when the plan pipelines it
-    tk_pipelined = topk is not None and c_count > 0 and prof["aggregate"][0] == 0
+    # over tensor groups as one timed span when the library pipelines it
+    tk_pipelined = topk is not None and W.topk_pipelined(L, layout.info()["n_tiles"], K)
     if topk is not None:
-        tb = W.topk_algorithmic_bytes_per_param(K, density, w.mode)
-        c_bytes = (tb["worker"] + (8 * K if mu is not None else 0)
-                   + (tb["server"] if tk_pipelined else 0)) * d
+        c_bytes = W.topk_span_bytes_per_param(K, density, w.mode, tk_pipelined,
+                                              mu is not None) * d
     else:
         c_bytes = ((20 if mu is not None else 12) * K + K / 8) * d
     stamped = list(timed_ts)[::EVENT_EVERY]

@@ -310,6 +310,26 @@ def topk_algorithmic_bytes_per_param(K: int, density: float, mode: int = 1,
             "round": step + worker + server + (4 * K if averaging else -4 * K if one_pass else 0)}
 
 
+# fewest (tile, worker) pairs of a Top-K iteration end that is pipelined over two
+# runs of tensors (the library's rule, csrc/saef_topk.h: kTkSplitTiles)
+TOPK_SPLIT_TILES = 16384
+
+
+def topk_pipelined(L: int, n_tiles: int, K: int) -> bool:
+    """Whether saef_topk_round_end takes an iteration's end as one timed span
+    (kind "compress"); otherwise that span is the worker compression alone."""
+    return L >= 2 and n_tiles * K >= TOPK_SPLIT_TILES
+
+
+def topk_span_bytes_per_param(K: int, density: float, mode: int, pipelined: bool,
+                              momentum: bool = False) -> float:
+    """Bytes per parameter of the span stamped as "compress" (without a step
+    ahead taken along): the worker compression, and the server step with it when
+    pipelined."""
+    b = topk_algorithmic_bytes_per_param(K, density, mode)
+    return b["worker"] + (8 * K if momentum else 0) + (b["server"] if pipelined else 0)
+
+
 def algorithmic_bytes_per_param(K: int, mode: int = 1, averaging: bool = False,
                                 momentum: bool = False, step_ahead: bool = True,
                                 mismatch: bool = False, one_pass: bool = False) -> float:
