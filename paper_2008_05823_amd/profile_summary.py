@@ -135,15 +135,15 @@ def trace_table(path: str, skip: int) -> None:
         print(f"  {name:40s} {wg:10d} {n:6d} {avg:10.1f} {first:10.1f}")
 
 
-def timeline(path: str, marker: str, index: int) -> None:
-    """The dispatches between the index-th and the next dispatch whose kernel
-    name starts with `marker` (one iteration), in start order: queue (HIP
+def timeline(path: str, marker: str, index: int, count: int = 1) -> None:
+    """The dispatches between the index-th and the count-th next dispatch whose
+    kernel name starts with `marker` (one iteration), in start order: queue (HIP
     stream), workgroups, start and end in microseconds from the first."""
     rows = sorted(csv.DictReader(open(path)), key=lambda r: int(r["Start_Timestamp"]))
     marks = [i for i, r in enumerate(rows) if short_name(r["Kernel_Name"]).startswith(marker)]
-    if len(marks) < index + 2:
-        raise SystemExit(f"fewer than {index + 2} dispatches of {marker!r}")
-    i0, i1 = marks[index], marks[index + 1]
+    if len(marks) < index + count + 1:
+        raise SystemExit(f"fewer than {index + count + 1} dispatches of {marker!r}")
+    i0, i1 = marks[index], marks[index + count]
     t0 = int(rows[i0]["Start_Timestamp"])
     print(f"  {'kernel':36s} {'queue':>5s} {'workgroups':>10s} {'start_us':>9s} {'end_us':>9s} "
           f"{'dur_us':>8s}")
@@ -158,9 +158,9 @@ def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--trace", default=None, help="kernel trace CSV (per launch shape table)")
     ap.add_argument("--skip", type=int, default=0, help="first dispatches of each shape left out")
-    ap.add_argument("--timeline", default=None, metavar="MARKER:INDEX",
+    ap.add_argument("--timeline", default=None, metavar="MARKER:INDEX[:N]",
                     help="with --trace: the dispatches of one iteration, from the INDEX-th "
-                         "dispatch of a kernel whose name starts with MARKER to the next")
+                         "dispatch of a kernel whose name starts with MARKER to the N-th next")
     ap.add_argument("--stats")
     ap.add_argument("--fetch")
     ap.add_argument("--write")
@@ -182,8 +182,8 @@ def main() -> int:
     args = ap.parse_args()
     if args.trace:
         if args.timeline:
-            marker, _, index = args.timeline.rpartition(":")
-            timeline(args.trace, marker, int(index))
+            marker, index, count = re.fullmatch(r"(.*?):(\d+)(?::(\d+))?", args.timeline).groups()
+            timeline(args.trace, marker, int(index), int(count or 1))
         else:
             trace_table(args.trace, args.skip)
         return 0
