@@ -104,9 +104,6 @@ void* scratch_of(int dev) {
   return g_scratch_ptr[dev];
 }
 
-// Elements per work tile of a tensor of n elements: kTileElems, or more for
-// very large tensors so that no tensor has more than kMaxTilesPerTensor tiles
-// (bounds the number of partial sums the finalize kernel adds per tensor).
 // The parts of the pipelined Top-K iteration end: runs of whole tensors in
 // order (SAEF_TK_PARTS of them, fewer when there are fewer tensors; one part
 // means no pipeline), cut where the running element count passes the first
@@ -156,6 +153,9 @@ std::vector<saef::TkPart> pipeline_parts(const saef_layout* layout,
   return out;
 }
 
+// Elements per work tile of a tensor of n elements: kTileElems, or more for
+// very large tensors so that no tensor has more than kMaxTilesPerTensor tiles
+// (bounds the number of partial sums the finalize kernel adds per tensor).
 int64_t tile_elems(int64_t n) {
   int64_t t = saef::kTileElems;
   if (n > t * saef::kMaxTilesPerTensor) {

@@ -203,9 +203,11 @@ __device__ __forceinline__ __int128 wave_sum_tile(__int128 v) {
   return v;
 }
 
-// A workgroup barrier that orders LDS accesses only: __syncthreads() also
-// waits for every global store in flight, which keeps a streaming workgroup
-// on its CU until its last store is acknowledged.
+// A workgroup barrier that orders LDS accesses only, whatever the compiler makes
+// of __syncthreads(): no wait for the global stores in flight, which would keep a
+// streaming workgroup on its CU until its last store is acknowledged.  (In the
+// compression kernels the two measure alike: this compiler's __syncthreads()
+// waits for LDS only.)
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();

@@ -115,11 +115,16 @@ hipError_t launch_finalize(const DevLayout& lay, int K, bool server, float* scal
 
 // Whether the aggregation and the in-place corrections of the single calls
 // add up the tile partials themselves: a lane per tile and kFoldRows workers
-// at most, and no more tiles than run at once (8 workgroups on each of 256
-// CUs), where the launch of a finalize kernel takes longer than its work in
-// every workgroup: resnet56 K = 8 39.3 us per iteration against 41.4 with the
-// kernel, one tensor of 65536 K = 4 18.8 against 21.0, the single calls of one
-// of 12 workers on 91 tensors of 72071 elements 32.7 against 40.6.
+// at most, and at most kFoldTiles tiles.  The aggregation's workgroups (one per
+// tile) then all run at once (8 on each of 256 CUs), and the launch of a finalize
+// kernel takes longer than its work in each of them: resnet56 K = 8 39.3 us per
+// iteration against 41.4 with the kernel, one tensor of 65536 K = 4 18.8 against
+// 21.0.  The correction's (one per tile and row, up to 16 times as many) do not
+// all run at once, but each redoes at most 1 KB of sums beside a tile of 16 KB, and
+// the call stays ahead up to the rule's edge: saef_compress at 2048 tiles, 64
+// per tensor, 15.9 us against 17.5 at K = 1, 65.5 against 65.8 at K = 4, 211
+// against 214 at K = 16; one tile per tensor, K = 16, 211 against 248;
+// saef_aggregate there 22.8 against 25.0 us at K = 1, 29.1 against 31.1 at 16.
 constexpr int kFoldRows = 16;
 constexpr int64_t kFoldTiles = 2048;
 bool folds_scales(const DevLayout& lay, int K);
