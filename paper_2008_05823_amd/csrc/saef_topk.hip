@@ -1380,7 +1380,7 @@ __device__ __forceinline__ void select_tensor(SelectLds& s, const DevLayout& lay
 // the sub-range that the counts leave, and the last one of the tensor to arrive
 // (nobody waits) selects.  (One workgroup takes up to 4 ms over a full bin:
 // resnet50 K = 8 Top-1%, all values 1000 times as large as in the call before,
-// 4.4 ms a call; 1.3 ms this way.)
+// 4.4 ms a call; 1.36 ms this way.)
 template <int kParts>
 __global__ __launch_bounds__(kSelect) void k_tk_select(DevLayout lay, TkDev tk, TkPart p, int R,
                                                        int row0,
